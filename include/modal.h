@@ -195,12 +195,13 @@ int modal_nmax(const modal_ctx* ctx);
 int modal_npairs(const modal_ctx* ctx);
 
 /* Contraction kernel the context dispatches for the cubic reduction:
- * 0 = vector-ALU with FP64 accumulation (FP64 contexts),
+ * 0 = FP64 products and sums over the cells (pair a <= b, mode >= b) (FP64 contexts),
  * 1 = FP32 MFMA (32x32x2 tiles over a cover of the triples, see modal_cubic_plan),
  * 2 = split bf16/fp16 MFMA (32x32x16 tiles over the same cover). */
 int modal_cubic_path(const modal_ctx* ctx);
 /* Multiply-adds the cubic contraction issues per pixel and map, counting tile
- * padding and every product of a split (for roofline reports; host only). */
+ * padding and every product of a split (for roofline reports; host only).  For FP64
+ * contexts the dense pair x mode count, npairs * P. */
 double modal_cubic_issued_macs(const modal_ctx* ctx);
 /* Work plan of the split contraction for P modes (host only, no device; Sec. II,
  * eq. (bbispect): beta_prs is the pixel sum of the triple product, so it may be read

@@ -57,7 +57,7 @@ struct Tables {
   int4* cslot = nullptr;       // [ncslot] (a0, b0, zlo, zhi) blocks of the split contraction's items, 32 per item
   int ncslot = 0;
   int cmult = 1;               // waves per item of the split contraction (1, 2, 4 or 8)
-  int* cell = nullptr;         // [nmax] pair * P + mode of the partial-sum cell holding beta_n (split contraction)
+  int* cell = nullptr;         // [nmax] pair * P + mode of the partial-sum cell holding beta_n
   int* cell_order = nullptr;   // [nmax] the triples sorted by their cell
   float* mscale = nullptr;     // [P] exact powers of two ~ 1/sigma_p (split-fp16 contraction)
   uint4* lamtab = nullptr;     // split synthesis: lambda operand words per (m, wave of rings, chunk)
@@ -116,6 +116,14 @@ __host__ __device__ inline size_t f_index(int seq, int ring, int m, int lmax, in
 // the compiler from moving memory operations across it.
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// helpers
+inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
+inline bool is_f64(const modal_ctx* c) { return c->prec == MODAL_F64; }
+inline size_t real_bytes(const modal_ctx* c) { return is_f64(c) ? 8 : 4; }
+inline size_t f_bytes_per_sky(const modal_ctx* c) {
+  return (size_t)c->P * f_ring_blocks(c->ntheta) * 8 * (c->lmax + 1) * 2 * real_bytes(c);
+}
+
 // ---- launchers (defined in the .hip files); all return hipSuccess or the error
 hipError_t launch_seeds(const modal_ctx* c, const double* logpref, hipStream_t st);
 
@@ -154,16 +162,17 @@ hipError_t launch_cross_spectra(const modal_ctx* c, const void* Z, const double*
 hipError_t launch_fisher_assemble(const modal_ctx* c, const double* X, double scale, double* F, hipStream_t st);
 
 // cubic pixel reduction E_(ab),t = sum_x w M_a M_b M_t into
-// partials[S][nchunk][npairs][P] float64 (VALU FP64 path / matrix-core paths)
+// partials[S][nchunk][npairs][P] float64 (FP64 contexts / FP32 and split contexts).  The
+// workspace's own region holds cubic_nchunk_ws chunks of the FP64 contraction; more chunks
+// go where the ring coefficients were (host.cpp, part_region).
+int cubic_nchunk_ws(const modal_ctx* c);
 int cubic_nchunk(const modal_ctx* c);
-hipError_t launch_cubic_valu(const modal_ctx* c, const void* maps, int S, double* partials, hipStream_t st);
+hipError_t launch_cubic_f64(const modal_ctx* c, const void* maps, int S, double* partials, hipStream_t st);
 bool cubic_mfma_available(const modal_ctx* c);
 int cubic_mfma_nchunk(const modal_ctx* c);
 int cubic_mfma_nchunk_max(const modal_ctx* c);
-// out[S][nmax] = scale (three pairings of the chunk sum of partials) + scale2 (three
-// pairings of E2[S][npairs][P]); partials or E2 may be null
-hipError_t launch_reduce_symm(const modal_ctx* c, const double* partials, int S, int nchunk, double scale,
-                              double* E, const double* E2, double scale2, double* out, hipStream_t st);
+// out[S][nmax] = the three pairings of E2[S][npairs][P]
+hipError_t launch_symm(const modal_ctx* c, int S, const double* E2, double* out, hipStream_t st);
 // matrix-core contraction on 32x32 tiles (k_cubic_split.hip; FP32 and split contexts): work
 // items of 32 blocks of 2 x 2 pairs against a 32-mode window, over a cover of the triples by
 // (block, window) cells; make_cubic_cover builds it (false if the plan fails)
@@ -263,10 +272,5 @@ hipError_t launch_power_beta(const modal_ctx* c, const void* maps, int S, const 
                              double* beta, hipStream_t st);
 hipError_t launch_power_alpha(const modal_ctx* c, const double* dcl, double* alpha, hipStream_t st);
 hipError_t launch_power_rows(const modal_ctx* c, const double* q, const double* cw, double* X, hipStream_t st);
-
-// helpers
-inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
-inline bool is_f64(const modal_ctx* c) { return c->prec == MODAL_F64; }
-inline size_t real_bytes(const modal_ctx* c) { return is_f64(c) ? 8 : 4; }
 
 }  // namespace modal

@@ -140,15 +140,18 @@ modal_status fail(modal_ctx* c, modal_status s, const std::string& msg) {
 
 size_t alm_bytes(const modal_ctx* c) { return (size_t)c->nalm * 2 * real_bytes(c); }
 // synthesis output (f_index layout; also large enough for the adjoint's [S][P][lmax+1][ntheta])
-size_t F_bytes(const modal_ctx* c, int S) {
-  return (size_t)S * c->P * f_ring_blocks(c->ntheta) * 8 * (c->lmax + 1) * 2 * real_bytes(c);
-}
+size_t F_bytes(const modal_ctx* c, int S) { return (size_t)S * f_bytes_per_sky(c); }
 size_t maps_bytes(const modal_ctx* c, int S) { return (size_t)S * c->P * c->npix * real_bytes(c); }
 int nchunk_for(const modal_ctx* c) { return cubic_mfma_available(c) ? cubic_mfma_nchunk(c) : cubic_nchunk(c); }
 // sized for the smallest chunk the autotuner may choose, so a workspace stays valid after tuning
 size_t part_bytes(const modal_ctx* c, int S) {
-  const int nc = cubic_mfma_available(c) ? cubic_mfma_nchunk_max(c) : cubic_nchunk(c);
+  const int nc = cubic_mfma_available(c) ? cubic_mfma_nchunk_max(c) : cubic_nchunk_ws(c);
   return (size_t)S * nc * c->npairs * c->P * 8;
+}
+// where the contraction's partial sums go: the workspace's own region, or, for an FP64 context
+// with more chunks than that holds, over the ring coefficients, which the maps no longer need
+double* part_region(const modal_ctx* c, void* F, void* own) {
+  return (double*)(!cubic_mfma_available(c) && cubic_nchunk(c) > cubic_nchunk_ws(c) ? F : own);
 }
 size_t E_bytes(const modal_ctx* c, int S) { return (size_t)S * c->npairs * c->P * 8; }
 size_t X_bytes(const modal_ctx* c, int S) { return (size_t)S * c->npairs * (c->lmax + 1) * 8; }
@@ -307,18 +310,13 @@ modal_status run_maps(modal_ctx* c, const void* alm, int S, void* F, void* maps,
 // pixels, and the linear term from the state's harmonic pair means.
 // out = sb beta + sl lin (lin from the state; sl = -1, sb = 1 gives beta^hat)
 modal_status run_beta(modal_ctx* c, const void* maps, const void* alm, const void* state, int S, double* part,
-                      double* E, double* X, double* L, double* out, hipStream_t st, double sb = 1.0,
-                      double sl = -1.0) {
-  // the matrix cores over the triple cover (split and FP32 contexts), the vector ALUs in FP64
-  const bool split = cubic_mfma_available(c);
-  if (split) STAGE(MODAL_STAGE_CUBIC, launch_cubic_split(c, maps, S, nchunk_for(c), cubic_chunk_px(c), part, st));
-  else STAGE(MODAL_STAGE_CUBIC, launch_cubic_valu(c, maps, S, part, st));
+                      double* X, double* L, double* out, hipStream_t st, double sb = 1.0, double sl = -1.0) {
+  // over the triple cover (split and FP32 contexts), or the cells (a <= b, t >= b) in FP64
+  if (cubic_mfma_available(c))
+    STAGE(MODAL_STAGE_CUBIC, launch_cubic_split(c, maps, S, nchunk_for(c), cubic_chunk_px(c), part, st));
+  else STAGE(MODAL_STAGE_CUBIC, launch_cubic_f64(c, maps, S, part, st));
   if (state) STAGE(MODAL_STAGE_LINEAR, launch_lin_harmonic(c, lin_Z(c, state), alm, S, X, L, st));
-  if (split)
-    STAGE(MODAL_STAGE_REDUCE, launch_reduce_single(c, part, S, nchunk_for(c), sb, state ? L : nullptr, sl, out, st));
-  else
-    STAGE(MODAL_STAGE_REDUCE,
-          launch_reduce_symm(c, part, S, nchunk_for(c), sb / 3.0, E, state ? L : nullptr, sl, out, st));
+  STAGE(MODAL_STAGE_REDUCE, launch_reduce_single(c, part, S, nchunk_for(c), sb, state ? L : nullptr, sl, out, st));
   return MODAL_OK;
 }
 
@@ -557,6 +555,8 @@ modal_status place_tables(modal_ctx* c, const double* q_host, const double* cl_h
   if (prec == MODAL_BF16X3 || prec == MODAL_F16X3 || prec == MODAL_F32) {
     if (!make_cubic_cover(P, pair_of, cslots, items, cell, &t.cmult))
       return fail(c, MODAL_EINVAL, "no cover of the triples by the contraction's items");
+  } else {
+    for (size_t n = 0; n < tri.size() / 6; ++n) cell.push_back(tri[6 * n + 3] * P + tri[6 * n + 2]);   // (pr), s
   }
   t.nitems = (int)items.size();
   t.ncslot = (int)cslots.size();
@@ -759,12 +759,12 @@ modal_status modal_beta(modal_ctx* c, const void* alm, int S, const void* state,
   Carver cv(ws);
   void* F = cv.take(F_bytes(c, S));
   void* maps = cv.take(maps_bytes(c, S));
-  double* part = (double*)cv.take(part_bytes(c, S));
-  double* E = (double*)cv.take(E_bytes(c, S));
+  double* part = part_region(c, F, cv.take(part_bytes(c, S)));
+  cv.take(E_bytes(c, S));
   double* X = (double*)cv.take(X_bytes(c, S));
   double* L = (double*)cv.take(E_bytes(c, S));
   if ((s = run_maps(c, alm, S, F, maps, st)) != MODAL_OK) return s;
-  return run_beta(c, maps, alm, state, S, part, E, X, L, beta, st);
+  return run_beta(c, maps, alm, state, S, part, X, L, beta, st);
 }
 
 modal_status modal_beta_loo(modal_ctx* c, const void* alm, int S, const void* state, double* beta, void* ws,
@@ -782,13 +782,13 @@ modal_status modal_beta_loo(modal_ctx* c, const void* alm, int S, const void* st
   Carver cv(ws);
   void* F = cv.take(F_bytes(c, S));
   void* maps = cv.take(maps_bytes(c, S));
-  double* part = (double*)cv.take(part_bytes(c, S));
-  double* E = (double*)cv.take(E_bytes(c, S));
+  double* part = part_region(c, F, cv.take(part_bytes(c, S)));
+  cv.take(E_bytes(c, S));
   double* X = (double*)cv.take(X_bytes(c, S));
   double* L = (double*)cv.take(E_bytes(c, S));
   if ((s = run_maps(c, alm, S, F, maps, st)) != MODAL_OK) return s;
   // beta - (N lin - 3 beta) / (N - 1): the sky's own pair products removed from the mean
-  return run_beta(c, maps, alm, state, S, part, E, X, L, beta, st, (N + 2.0) / (N - 1.0), -N / (N - 1.0));
+  return run_beta(c, maps, alm, state, S, part, X, L, beta, st, (N + 2.0) / (N - 1.0), -N / (N - 1.0));
 }
 
 modal_status modal_beta_noalloc(modal_ctx* c, const void* alm, int S, const void* state, double* beta,
@@ -873,7 +873,7 @@ modal_status modal_linear_term(modal_ctx* c, int mode, const void* alm, int S, v
       double* X = (double*)cv.take(X_bytes(c, S));
       double* L = (double*)cv.take(E_bytes(c, S));
       STAGE(MODAL_STAGE_LINEAR, launch_lin_harmonic(c, lin_Z(c, state), alm, S, X, L, st));
-      STAGE(MODAL_STAGE_REDUCE, launch_reduce_symm(c, nullptr, S, 0, 0.0, nullptr, L, 1.0, lin, st));
+      STAGE(MODAL_STAGE_REDUCE, launch_symm(c, S, L, lin, st));
       return MODAL_OK;
     }
     default:

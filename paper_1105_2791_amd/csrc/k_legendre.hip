@@ -84,6 +84,9 @@ struct Rec {
 // ---------------------------------------------------------------------------
 constexpr int kLch = 64;
 
+// The chunk's recurrence coefficients come with its mode coefficients, one l per lane, and are
+// read back from LDS: read one by one where they are used, each was a scalar load that the
+// recurrence waited for (one sky, l_max 32, 48 rings, P 8 in double: 18.8 us, now 15.2 us).
 template <typename T, int NSEQ>
 __global__ __launch_bounds__(64) void k_legendre(int lmax, int ntheta, int nrp, int P, int nseq, int nalm,
                                                  const double* __restrict__ x, const double* __restrict__ rec,
@@ -98,6 +101,7 @@ __global__ __launch_bounds__(64) void k_legendre(int lmax, int ntheta, int nrp, 
   const int seq0 = blockIdx.x * NSEQ;
   const bool ring_ok = j < nrp;
   __shared__ T2 coef[kLch][NSEQ];
+  __shared__ double2 rcs[kLch];
   __shared__ int lmin_s;
 
   Rec r;
@@ -122,9 +126,12 @@ __global__ __launch_bounds__(64) void k_legendre(int lmax, int ntheta, int nrp, 
   for (int q = 0; q < NSEQ; ++q) er[q] = ei[q] = orr[q] = oi[q] = T(0);
 
   const size_t off = (size_t)m * (2 * lmax + 3 - m) / 2;
-  for (int l0 = lmin; l0 <= lmax; l0 += kLch) {
+  // chunks start at an even l - m, so that the two parities alternate; entries past lmax have
+  // zero coefficients (their lambda, one or two steps past the end, is finite)
+  for (int l0 = m + ((lmin - m) & ~1); l0 <= lmax; l0 += kLch) {
     {
       const int l = l0 + lane;
+      rcs[lane] = reinterpret_cast<const double2*>(rec)[off + (l - m)];   // kRecPad entries past the last l
 #pragma unroll
       for (int q = 0; q < NSEQ; ++q) {
         T2 v;
@@ -142,23 +149,18 @@ __global__ __launch_bounds__(64) void k_legendre(int lmax, int ntheta, int nrp, 
       }
     }
     __syncthreads();
-    const int nl = min(kLch, lmax + 1 - l0);
-    for (int tt = 0; tt < nl; ++tt) {
-      const int l = l0 + tt;
-      const double lam = r.step(l, xx, rec + 2 * (off + (l - m)));
-      const T lf = T(lam);
-      if ((l - m) & 1) {
+    const int nl = min(kLch, (lmax - l0 + 2) & ~1);
+#pragma unroll 2
+    for (int tt = 0; tt < nl; tt += 2) {
+      const double2 r0 = rcs[tt], r1 = rcs[tt + 1];
+      const T le = T(r.step(l0 + tt, xx, &r0.x));
+      const T lo = T(r.step(l0 + tt + 1, xx, &r1.x));
 #pragma unroll
-        for (int q = 0; q < NSEQ; ++q) {
-          orr[q] += coef[tt][q].x * lf;
-          oi[q] += coef[tt][q].y * lf;
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < NSEQ; ++q) {
-          er[q] += coef[tt][q].x * lf;
-          ei[q] += coef[tt][q].y * lf;
-        }
+      for (int q = 0; q < NSEQ; ++q) {
+        er[q] += coef[tt][q].x * le;
+        ei[q] += coef[tt][q].y * le;
+        orr[q] += coef[tt + 1][q].x * lo;
+        oi[q] += coef[tt + 1][q].y * lo;
       }
     }
     __syncthreads();
@@ -253,18 +255,28 @@ hipError_t launch_seeds(const modal_ctx* c, const double* logpref, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_legendre(const modal_ctx* c, const void* alm, int S, void* F, hipStream_t st) {
+namespace {
+template <typename T, int NS>
+void legendre_launch(const modal_ctx* c, const void* alm, int S, const T* qw, void* F, hipStream_t st) {
+  using T2 = typename vec2<T>::type;
   const int nseq = S * c->P;
-  constexpr int NS = 8;
-  dim3 grid((nseq + NS - 1) / NS, (c->nrp + 63) / 64, c->lmax + 1);
+  hipLaunchKernelGGL((k_legendre<T, NS>), dim3((nseq + NS - 1) / NS, (c->nrp + 63) / 64, c->lmax + 1), dim3(64), 0, st,
+                     c->lmax, c->ntheta, c->nrp, c->P, nseq, c->nalm, c->t.x, c->t.rec, c->t.seed, c->t.lstart, qw,
+                     (const T2*)alm, (T2*)F);
+}
+}  // namespace
+
+// Eight sequences per wave share a recurrence; where that leaves fewer than four waves per CU
+// two do (one sky, l_max 32, P 8: 15.2 us with eight, 8.2 us with two and the
+// steps taken in even and odd pairs).
+hipError_t launch_legendre(const modal_ctx* c, const void* alm, int S, void* F, hipStream_t st) {
+  const bool few = (size_t)((S * c->P + 7) / 8) * ((c->nrp + 63) / 64) * (c->lmax + 1) < 1024;
   if (is_f64(c)) {
-    hipLaunchKernelGGL((k_legendre<double, NS>), grid, dim3(64), 0, st, c->lmax, c->ntheta, c->nrp, c->P, nseq,
-                       c->nalm, c->t.x, c->t.rec, c->t.seed, c->t.lstart, c->t.qw64, (const double2*)alm,
-                       (double2*)F);
+    if (few) legendre_launch<double, 2>(c, alm, S, c->t.qw64, F, st);
+    else legendre_launch<double, 8>(c, alm, S, c->t.qw64, F, st);
   } else {
-    hipLaunchKernelGGL((k_legendre<float, NS>), grid, dim3(64), 0, st, c->lmax, c->ntheta, c->nrp, c->P, nseq,
-                       c->nalm, c->t.x, c->t.rec, c->t.seed, c->t.lstart, c->t.qw32, (const float2*)alm,
-                       (float2*)F);
+    if (few) legendre_launch<float, 2>(c, alm, S, c->t.qw32, F, st);
+    else legendre_launch<float, 8>(c, alm, S, c->t.qw32, F, st);
   }
   return hipGetLastError();
 }

@@ -1,0 +1,52 @@
+"""Kernels at the sizes where their tiles, remainders and dispatch rules change, against the
+FP64 oracle: the smallest and largest of a range, one past a tile, odd and ragged."""
+import numpy as np
+import pytest
+
+import modal_inputs as mi
+from helpers import Case
+from oracle import modal as om
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _ctx(case, prec):
+    from paper_1105_2791_amd import ModalContext
+    return ModalContext(case.lmax, case.ntheta, case.nphi, case.P, prec, case.q, case.cl, mask=case.mask())
+
+
+# FP64 contraction: 1 to 4 column tiles of 16 modes (P 1, 16 | 17, 33 | 49, 64), row tiles that
+# end inside a wave, a chunk shorter than a staged step, more chunks than pixels to fill them,
+# and the chunk count that the ring coefficients' region bounds (l_max 2, P 64).
+F64_CASES = [(2, 3, 6, 1, 1), (2, 3, 6, 64, 2), (9, 14, 30, 16, 3), (9, 15, 32, 17, 1), (20, 31, 64, 33, 2),
+             (40, 61, 124, 49, 1), (12, 19, 40, 64, 2)]
+
+
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", F64_CASES)
+def test_f64_contraction_edges(lmax, ntheta, nphi, P, S):
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 71)
+    print(f"[case] f64 contraction lmax={lmax} {ntheta}x{nphi} P={P} S={S}", flush=True)
+    a = case.alms(0, S)
+    M, w = case.maps(a), case.grid.w
+    mc = case.maps(case.alms(50, 2))
+    V = om.pair_means(mc)
+    c = _ctx(case, "f64")
+    got = c.beta(a).cpu().numpy()
+    st = c.linear_state()
+    c.linear_reset(st)
+    c.linear_accumulate(st, case.alms(50, 2))
+    c.linear_finalize(st)
+    hat = c.beta(a, state=st).cpu().numpy()
+    for i in range(S):
+        ref, mag = om.beta(M[i], w), om.beta(np.abs(M[i]), w)
+        lin, lmag = om.linear_term(M[i], w, V), om.linear_term(np.abs(M[i]), w, np.abs(V))
+        # forward-error scale of the sums: the FP64 bound of the other beta tests
+        assert np.max(np.abs(got[i] - ref) / mag) < 1e-10
+        assert np.max(np.abs(hat[i] - (ref - lin)) / (mag + lmag)) < 1e-10
