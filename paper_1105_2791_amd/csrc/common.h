@@ -46,8 +46,6 @@ struct Tables {
   int* quad = nullptr;         // [nquad][6] pair indices of the three pairings (pr|su), (ps|ru), (pu|rs)
   int nquad = 0;
   int2* qtiles = nullptr;      // tile pairs (ti <= tj) of the pairs x pairs update
-  int4* zrows = nullptr;       // [nzrows] ideal-covariance rows: (p, r, s, mode), runs of equal (p, r)
-  int nzrows = 0;              //   padded to multiples of 4 with (p, r, r, -1)
   int* pair_of = nullptr;      // [P][P] pair index of (min, max)
   int* tri_of = nullptr;       // [P][npairs] triple index of sort(u, a, b)
   int* tri_mult = nullptr;     // [P][npairs] multiplicity of u in that triple
@@ -241,8 +239,14 @@ hipError_t launch_legendre_series(int L, int nmu, int P, int nf, const double* U
                                   double* F, hipStream_t st);
 hipError_t launch_alpha_modes(int nmax, int P, int T, int nmu, const int* tri, const double* F, const double* wmu,
                               double* alpha, hipStream_t st);
-hipError_t launch_ideal_cov(int nmax, int P, int nmu, int nrows, const int4* zrows, const double* F,
-                            const double* wmu, double* Z, hipStream_t st);
+// Q [nmu][npairs] (padded: ideal_series_bytes) of U_b B_a, a <= b; the symmetric node sums T
+// (ideal_triples_bytes) and zeta0
+hipError_t launch_pair_series(int L, int nmu, int P, const int* pair_a, const int* pair_b, const double* U,
+                              const double* B, const double* mu, double* Q, hipStream_t st);
+size_t ideal_triples_bytes(int npairs);
+size_t ideal_series_bytes(int npairs, int nmu);
+hipError_t launch_ideal_cov(int nmax, int P, int nmu, const int* tri, const int* pair_of, const double* Q,
+                            const double* wmu, double* T, double* Z, hipStream_t st);
 
 // truncated orthonormal frame: pivoted, truncated Cholesky (k_frame.hip)
 size_t frame_ws_bytes(int n);

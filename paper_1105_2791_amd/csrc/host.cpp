@@ -230,7 +230,7 @@ size_t ws_size(const modal_ctx* c, int op, int S) {
     case MODAL_OP_IDEAL_COVARIANCE: {
       const size_t nmu = shapes_nmu(c->lmax), L = c->lmax + 1;
       cv.take(nmu * 8); cv.take(nmu * 8); cv.take((size_t)c->P * L * 8); cv.take((size_t)c->P * L * 8);
-      cv.take((size_t)c->P * nmu * c->P * 8);
+      cv.take(ideal_series_bytes(c->npairs, (int)nmu)); cv.take(ideal_triples_bytes(c->npairs));
       break;
     }
     default: return 0;
@@ -520,15 +520,6 @@ modal_status place_tables(modal_ctx* c, const double* q_host, const double* cl_h
           quad.insert(quad.end(), {pr(p, r), pr(s2, u), pr(p, s2), pr(r, u), pr(p, u), pr(r, s2)});
         }
   c->t.nquad = (int)(quad.size() / 6);
-  // ideal-covariance rows: the modes in their order, each run of equal (p, r) padded to a
-  // multiple of 4, so that every aligned group of four rows shares (p, r)
-  std::vector<int4> zrows;
-  for (int p = 0; p < P; ++p)
-    for (int r = p; r < P; ++r) {
-      for (int s = r; s < P; ++s) zrows.push_back(make_int4(p, r, s, tri_index[((size_t)p * P + r) * P + s]));
-      while (zrows.size() % 4) zrows.push_back(make_int4(p, r, r, -1));
-    }
-  c->t.nzrows = (int)zrows.size();
   std::vector<int2> qtiles;
   {
     const int nt = quad_ntile(c->npairs);
@@ -573,7 +564,7 @@ modal_status place_tables(modal_ctx* c, const double* q_host, const double* cl_h
       !ok(pl.put(&t.tw64, tw64)) || !ok(pl.put(&t.tw32, tw32)) || !ok(pl.put(&t.pair_a, pa)) ||
       !ok(pl.put(&t.pair_b, pb)) || !ok(pl.put(&t.tri, tri)) || !ok(pl.put(&t.pair_of, pair_of)) ||
       !ok(pl.put(&t.tri_of, tri_of)) || !ok(pl.put(&t.tri_mult, tri_mult)) || !ok(pl.put(&t.quad, quad)) ||
-      !ok(pl.put(&t.qtiles, qtiles)) || !ok(pl.put(&t.zrows, zrows)))
+      !ok(pl.put(&t.qtiles, qtiles)))
     return MODAL_EDEVICE;
   if (!ok(pl.take(&t.seed, 2 * (size_t)(lmax + 1) * c->nrp)) || !ok(pl.take(&t.lstart, (size_t)(lmax + 1) * c->nrp)) ||
       !ok(pl.take(&t.flag, 4)))
@@ -1239,7 +1230,7 @@ modal_status modal_ideal_covariance(modal_ctx* c, const double* c_host, double* 
   if ((int)c->mu_host.size() != nmu) gauss_legendre(nmu, c->mu_host, c->wmu_host);
   const std::vector<double>& mu = c->mu_host;
   const std::vector<double>& wmu = c->wmu_host;
-  // U_b(l) = c_l q_b(l), B_a(l) = q_a(l): F[b][k][a] = Q_ab(mu_k)
+  // U_b(l) = c_l q_b(l), B_a(l) = q_a(l): Q[k][ab] = Q_ab(mu_k)
   std::vector<double> u((size_t)P * L);
   for (int b = 0; b < P; ++b)
     for (int l = 0; l < L; ++l) {
@@ -1251,15 +1242,16 @@ modal_status modal_ideal_covariance(modal_ctx* c, const double* c_host, double* 
   double* dw = (double*)cv.take((size_t)nmu * 8);
   double* U = (double*)cv.take((size_t)P * L * 8);
   double* Bq = (double*)cv.take((size_t)P * L * 8);
-  double* F = (double*)cv.take((size_t)P * nmu * P * 8);
+  double* Q = (double*)cv.take(ideal_series_bytes(c->npairs, nmu));
+  double* T = (double*)cv.take(ideal_triples_bytes(c->npairs));
   HIPTRY(hipMemcpyAsync(dmu, mu.data(), (size_t)nmu * 8, hipMemcpyHostToDevice, st));
   HIPTRY(hipMemcpyAsync(dw, wmu.data(), (size_t)nmu * 8, hipMemcpyHostToDevice, st));
   HIPTRY(hipMemcpyAsync(U, u.data(), (size_t)P * L * 8, hipMemcpyHostToDevice, st));
   HIPTRY(hipMemcpyAsync(Bq, c->q_host.data(), (size_t)P * L * 8, hipMemcpyHostToDevice, st));
   {
     StageTimer _t(c, MODAL_STAGE_COVARIANCE, st);
-    HIPTRY(launch_legendre_series(L, nmu, P, P, U, Bq, dmu, F, st));
-    HIPTRY(launch_ideal_cov(c->nmax, P, nmu, c->t.nzrows, c->t.zrows, F, dw, zeta, st));
+    HIPTRY(launch_pair_series(L, nmu, P, c->t.pair_a, c->t.pair_b, U, Bq, dmu, Q, st));
+    HIPTRY(launch_ideal_cov(c->nmax, P, nmu, c->t.tri, c->t.pair_of, Q, dw, T, zeta, st));
   }
   HIPTRY(hipStreamSynchronize(st));
   return MODAL_OK;

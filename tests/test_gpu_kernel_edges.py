@@ -50,3 +50,25 @@ def test_f64_contraction_edges(lmax, ntheta, nphi, P, S):
         # forward-error scale of the sums: the FP64 bound of the other beta tests
         assert np.max(np.abs(got[i] - ref) / mag) < 1e-10
         assert np.max(np.abs(hat[i] - (ref - lin)) / (mag + lmag)) < 1e-10
+
+
+# Theory side: one pair, a tile of pairs not filled and one past it (55 and 66 pairs of 64), an
+# odd pair count (its last i alone), a node count that is a multiple of a stage (32 of 16) and
+# ones that are not, several tiles of modes (816 of 64), and one node more than a tile (65 at l_max 43).
+@pytest.mark.parametrize("lmax,P", [(1, 1), (10, 10), (11, 11), (21, 3), (6, 16), (43, 2)])
+def test_theory_side_edges(lmax, P):
+    from oracle import shapes as osh
+    from paper_1105_2791_amd import ModalContext
+    print(f"[case] theory lmax={lmax} P={P}", flush=True)
+    rng = np.random.default_rng(100 * lmax + P)
+    q, cl = rng.uniform(-1, 1, (P, lmax + 1)), rng.uniform(0.5, 2, lmax + 1)
+    c = rng.uniform(0.5, 1.5, lmax + 1)
+    terms = rng.uniform(-1, 1, (2, 3, lmax + 1))
+    ctx = ModalContext(lmax, lmax + 1, 2 * lmax + 2, P, "f64", q, cl)
+    z = ctx.ideal_covariance(c).cpu().numpy()
+    a = ctx.alpha_separable(terms).cpu().numpy()
+    # the FP64 bound of the theory tests (1e-11) on the sums of the absolute terms
+    assert np.array_equal(z, z.T)
+    assert np.all(np.abs(z - osh.ideal_covariance(q, c)) <= 1e-11 * osh.ideal_covariance(np.abs(q), c))
+    mag = osh.alpha_separable(np.abs(terms), cl, np.abs(q))
+    assert np.all(np.abs(a - osh.alpha_separable(terms, cl, q)) <= 1e-11 * mag)
