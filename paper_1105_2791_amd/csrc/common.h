@@ -69,7 +69,7 @@ struct modal_ctx {
   int nalm = 0, npairs = 0, nmax = 0, nrp = 0, npix = 0;
   int device = 0;
   size_t max_lds = 65536;
-  bool legendre_mfma = false;   // MFMA synthesis enabled (F32 / BF16X3 when the LDS fits)
+  bool legendre_mfma = false;   // MFMA synthesis of the F32 contexts (when the LDS fits)
   // tuned launch parameters (modal_autotune); 0 = default
   int tune_chunk_px = 0;        // pixels per split-K chunk of the MFMA contraction target
   int tune_fft_rings = 0;       // rings per FFT workgroup
@@ -127,7 +127,9 @@ hipError_t launch_seeds(const modal_ctx* c, const double* logpref, hipStream_t s
 
 // Legendre synthesis: F (f_index layout) complex, double2 for F64, float2 otherwise
 hipError_t launch_legendre(const modal_ctx* c, const void* alm, int S, void* F, hipStream_t st);
-hipError_t launch_legendre_mfma(const modal_ctx* c, const void* alm, int S, void* F, hipStream_t st);
+// FP32 contexts; scratch (may be null) is overwritten
+hipError_t launch_legendre_mfma(const modal_ctx* c, const void* alm, int S, void* F, void* scratch,
+                                size_t scratch_bytes, hipStream_t st);
 // split bf16/fp16 synthesis on 32x32 tiles, lambda in registers (k_legendre_split.hip)
 hipError_t launch_legendre_split(const modal_ctx* c, const void* alm, int S, void* F, hipStream_t st);
 size_t legendre_split_lds();
@@ -136,7 +138,7 @@ hipError_t legendre_split_set_lds(size_t bytes);
 size_t lambda_table_records(const modal_ctx* c, std::vector<long long>* off);
 size_t lambda_table_bytes(const modal_ctx* c);
 hipError_t build_lambda_table(modal_ctx* c, hipStream_t st);
-size_t legendre_mfma_lds(const modal_ctx* c);
+size_t legendre_mfma_lds();
 hipError_t legendre_mfma_set_lds(size_t bytes);
 // ring c2r FFT: maps[S][P][ntheta][nphi] from F
 hipError_t launch_fft_c2r(const modal_ctx* c, const void* F, int S, void* maps, hipStream_t st);

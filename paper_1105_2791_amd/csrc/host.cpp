@@ -300,7 +300,8 @@ struct StageTimer {
 modal_status run_maps(modal_ctx* c, const void* alm, int S, void* F, void* maps, hipStream_t st) {
   if (c->prec == MODAL_BF16X3 || c->prec == MODAL_F16X3)
     STAGE(MODAL_STAGE_LEGENDRE, launch_legendre_split(c, alm, S, F, st));
-  else if (c->legendre_mfma) STAGE(MODAL_STAGE_LEGENDRE, launch_legendre_mfma(c, alm, S, F, st));
+  else if (c->legendre_mfma) 
+    STAGE(MODAL_STAGE_LEGENDRE, launch_legendre_mfma(c, alm, S, F, maps, maps_bytes(c, S), st));
   else STAGE(MODAL_STAGE_LEGENDRE, launch_legendre(c, alm, S, F, st));
   STAGE(MODAL_STAGE_FFT, launch_fft_c2r(c, F, S, maps, st));
   return MODAL_OK;
@@ -405,20 +406,17 @@ modal_status choose_kernels(modal_ctx* c, bool live) {
     }
   }
   c->legendre_mfma = false;
-  if (prec == MODAL_F32 || prec == MODAL_BF16X3 || prec == MODAL_F16X3) {
-    if (prec != MODAL_F32) {
-      const size_t lneed = legendre_split_lds();
-      if (lneed + 1024 > c->max_lds) return MODAL_EUNSUPPORTED;
-      if (live && lneed > 65536 && legendre_split_set_lds(lneed) != hipSuccess) return MODAL_EDEVICE;
-      const size_t cneed = cubic_split_lds();
-      if (cneed + 1024 > c->max_lds) return MODAL_EUNSUPPORTED;
-      if (live && cneed > 65536 && cubic_split_set_lds(cneed) != hipSuccess) return MODAL_EDEVICE;
-    }
-    const size_t need = legendre_mfma_lds(c);
-    if (need <= c->max_lds) {
-      if (live && need > 65536 && legendre_mfma_set_lds(need) != hipSuccess) return MODAL_EDEVICE;
-      c->legendre_mfma = true;
-    }
+  if (prec == MODAL_BF16X3 || prec == MODAL_F16X3) {
+    const size_t lneed = legendre_split_lds();
+    if (lneed + 1024 > c->max_lds) return MODAL_EUNSUPPORTED;
+    if (live && lneed > 65536 && legendre_split_set_lds(lneed) != hipSuccess) return MODAL_EDEVICE;
+    const size_t cneed = cubic_split_lds();
+    if (cneed + 1024 > c->max_lds) return MODAL_EUNSUPPORTED;
+    if (live && cneed > 65536 && cubic_split_set_lds(cneed) != hipSuccess) return MODAL_EDEVICE;
+  }
+  if (prec == MODAL_F32 && legendre_mfma_lds() <= c->max_lds) {
+    if (live && legendre_mfma_set_lds(legendre_mfma_lds()) != hipSuccess) return MODAL_EDEVICE;
+    c->legendre_mfma = true;
   }
   return MODAL_OK;
 }

@@ -72,3 +72,23 @@ def test_theory_side_edges(lmax, P):
     assert np.all(np.abs(z - osh.ideal_covariance(q, c)) <= 1e-11 * osh.ideal_covariance(np.abs(q), c))
     mag = osh.alpha_separable(np.abs(terms), cl, np.abs(q))
     assert np.all(np.abs(a - osh.alpha_separable(terms, cl, q)) <= 1e-11 * mag)
+
+
+# FP32 synthesis: 1 to 4 ring tiles of 16 per wave and two workgroups of rings (nrp 3, 65, 129,
+# 193, 257), l_max on both sides of a 64-l chunk, lambda on the fly (fewer than three blocks of
+# 64 columns) and from the table, a last column block that is not full, columns of one sky and
+# of more skies than a block holds.
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", [(3, 5, 8, 2, 1), (63, 129, 130, 5, 2), (64, 130, 136, 7, 5),
+                                                  (64, 257, 150, 7, 14), (130, 386, 270, 3, 33), (40, 514, 90, 6, 17),
+                                                  (127, 128, 256, 1, 100)])
+def test_f32_synthesis_edges(lmax, ntheta, nphi, P, S):
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 72)
+    print(f"[case] f32 synthesis lmax={lmax} {ntheta}x{nphi} P={P} S={S}", flush=True)
+    a = case.alms(0, S)
+    c = _ctx(case, "f32")
+    out = torch.full((S, P, ntheta, nphi), float("nan"), dtype=torch.float32, device="cuda")
+    got = c.filter_maps(a, out=out).cpu().numpy()
+    ref = case.maps(a)
+    # the FP32 bound of the map tests, per sky and mode
+    rms = np.sqrt(np.mean(ref * ref, axis=(2, 3)))
+    assert np.all(np.max(np.abs(got - ref), axis=(2, 3)) <= 1e-5 * rms)
