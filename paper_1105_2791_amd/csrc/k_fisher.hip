@@ -38,71 +38,120 @@ __global__ __launch_bounds__(256) void k_pair_maps(int npairs, int npix, const i
   G[(size_t)pair * npix + x] = T(v * (double)w[x]);
 }
 
-// Z[col][lm] = c_m sum_j lambda_lm(theta_j) (Gh_N +- Gh_S)(col, m), one thread per l,
-// NC columns per thread; the ring values are staged in LDS already folded, Gh_N + Gh_S
-// and Gh_N - Gh_S in FP64, so that each thread reads the one its parity of l - m needs.
-constexpr int NC = 16;
-constexpr int RCH = 32;
+// Z[col][lm] = c_m sum_j lambda_lm(theta_j) (Gh_N +- Gh_S)(col, m) of the FP64 and FP32 contexts:
+// FP64 products and sums on the matrix cores (v_mfma_f64_16x16x4_f64: lane l holds
+// A[l % 16][l / 16] and B[l / 16][l % 16], accumulator register r is D[4 r + l / 16][l % 16]).
+// Per m and parity of l - m a GEMM over the northern rings, rows = l, columns = the real and
+// imaginary parts of the columns, of the folded ring values H_0 = Gh_N + Gh_S (even l - m)
+// and H_1 = Gh_N - Gh_S (odd).  A workgroup owns 128 consecutive l - m and 32 complex
+// columns of one m: wave w the parity w / 2 and every second 32 of its 64 l.  Stages of 16
+// rings, the next one's loads in flight, lambda sorted by parity in LDS rows of 80 words (two
+// rows of 16 doubles fill the banks).  The workgroups of one m run back to back on one XCD.
+// Bound by the FP64 matrix cores.  On the vector ALUs (one l per thread, 16 columns) 120
+// columns at l_max 500, 768 rings took 3.50 ms; 0.81 ms now (29 TF).
+constexpr int AC_L = 128;          // l per workgroup
+constexpr int AC_C = 32;           // complex columns per workgroup
+constexpr int AC_R = 16;           // rings per stage
+constexpr int AC_S = 2 * AC_C + 16;   // LDS row stride (64 values of a parity or real columns, padded)
+typedef double d4 __attribute__((ext_vector_type(4)));
 
 template <typename T>
-__global__ __launch_bounds__(64) void k_adj_legendre_cols(int lmax, int ntheta, int nrp, int ncol, int nalm,
-                                                          const T* __restrict__ lam,
+__global__ __launch_bounds__(256) void k_adj_legendre_f64(int lmax, int ntheta, int nrp, int ncol, int nalm, int nlb,
+                                                          int ncb, const T* __restrict__ lam,
                                                           const typename vec2<T>::type* __restrict__ Gh,
                                                           typename vec2<T>::type* __restrict__ Z) {
   using T2 = typename vec2<T>::type;
-  const int m = blockIdx.y;
+  const int xcd = blockIdx.x & 7, i8 = blockIdx.x >> 3, per = nlb * ncb;
+  const int m = xcd + 8 * (i8 / per);
+  const int lb = (i8 % per) / ncb, c0 = (i8 % per) % ncb * AC_C;
   const int L = lmax + 1 - m;
-  const int li = blockIdx.x * 64 + threadIdx.x;
-  const int c0 = blockIdx.z * NC;
+  if (m > lmax || lb * AC_L >= L) return;   // whole workgroup, before any barrier
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
+  const int par = wv >> 1, half = wv & 1;
   const size_t off = (size_t)m * (2 * lmax + 3 - m) / 2;
-  const T* lrow = lam + off * nrp;
-  __shared__ double2 hp[RCH][NC];   // Gh_N + Gh_S (even l - m)
-  __shared__ double2 hm[RCH][NC];   // Gh_N - Gh_S (odd l - m)
-  double ar[NC], ai[NC];
+  // the stages' tiles, then the outputs [AC_C / 2][AC_L + 1] complex of half of the columns
+  constexpr size_t kH = sizeof(double) * 2 * AC_R * AC_S, kLam = sizeof(T) * 2 * AC_R * AC_S;
+  constexpr size_t kOut = sizeof(T2) * (AC_C / 2) * (AC_L + 1);
+  __shared__ __attribute__((aligned(16))) unsigned char raw[kH + kLam > kOut ? kH + kLam : kOut];
+  double(*H)[AC_R][AC_S] = reinterpret_cast<double(*)[AC_R][AC_S]>(raw);      // [parity][ring][real column]
+  T(*lm)[AC_R][AC_S] = reinterpret_cast<T(*)[AC_R][AC_S]>(raw + kH);          // [parity][ring][l / 2]
+  // loads of a stage (indices clamped): lambda of this thread's l at 8 rings, and the ring
+  // values of a ring of two columns, north and south
+  const int tl = tid & (AC_L - 1), tr = tid >> 7, tj = tid & (AC_R - 1), tq = tid >> 4;
+  const T* lp = lam + off * nrp + min(lb * AC_L + tl, L - 1);
+  const T2 *g0 = Gh + ((size_t)min(c0 + tq, ncol - 1) * (lmax + 1) + m) * ntheta,
+           *g1 = Gh + ((size_t)min(c0 + tq + 16, ncol - 1) * (lmax + 1) + m) * ntheta;
+  T pl[AC_R / 2];
+  T2 gn0, gs0, gn1, gs1;
+  auto load = [&](int j0) {
 #pragma unroll
-  for (int q = 0; q < NC; ++q) ar[q] = ai[q] = 0.0;
-  const bool odd = (li & 1);
-  for (int j0 = 0; j0 < nrp; j0 += RCH) {
-    const int nj = min(RCH, nrp - j0);
+    for (int u = 0; u < AC_R / 2; ++u) pl[u] = lp[(size_t)min(j0 + 2 * u + tr, nrp - 1) * L];
+    const int j = min(j0 + tj, nrp - 1);
+    gn0 = g0[j];
+    gs0 = g0[ntheta - 1 - j];
+    gn1 = g1[j];
+    gs1 = g1[ntheta - 1 - j];
+  };
+  // rings past the last contribute H = 0; the equator ring of an odd count is counted once
+  auto fold = [&](int j, const T2& n, const T2& s, int q) {
+    const bool in = j < nrp, mir = in && ntheta - 1 - j != j;
+    const double nx = in ? (double)n.x : 0.0, ny = in ? (double)n.y : 0.0;
+    const double sx = mir ? (double)s.x : 0.0, sy = mir ? (double)s.y : 0.0;
+    H[0][tj][2 * q] = nx + sx;
+    H[0][tj][2 * q + 1] = ny + sy;
+    H[1][tj][2 * q] = nx - sx;
+    H[1][tj][2 * q + 1] = ny - sy;
+  };
+  d4 acc[2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  load(0);
+  for (int j0 = 0; j0 < nrp; j0 += AC_R) {
+#pragma unroll
+    for (int u = 0; u < AC_R / 2; ++u) lm[tl & 1][2 * u + tr][tl >> 1] = pl[u];
+    fold(j0 + tj, gn0, gs0, tq);
+    fold(j0 + tj, gn1, gs1, tq + 16);
     __syncthreads();
-    for (int e = threadIdx.x; e < RCH * NC; e += 64) {
-      const int jj = e / NC, q = e - jj * NC;
-      T2 vn, vs;
-      vn.x = vn.y = vs.x = vs.y = T(0);
-      const int col = c0 + q, j = j0 + jj;
-      if (jj < nj && col < ncol) {
-        const T2* g = Gh + ((size_t)col * (lmax + 1) + m) * ntheta;   // Gh[col][m][ring]
-        vn = g[j];
-        const int js = ntheta - 1 - j;
-        if (js != j) vs = g[js];
-      }
-      hp[jj][q] = make_double2((double)vn.x + (double)vs.x, (double)vn.y + (double)vs.y);
-      hm[jj][q] = make_double2((double)vn.x - (double)vs.x, (double)vn.y - (double)vs.y);
+    load(j0 + AC_R);   // past the last ring: clamped, not used
+#pragma unroll
+    for (int ks = 0; ks < AC_R / 4; ++ks) {
+      const int kk = 4 * ks + kq;
+      double a[2], b[4];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) a[t] = (double)lm[par][kk][32 * half + 16 * t + l16];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) b[t] = H[par][kk][16 * t + l16];
+#pragma unroll
+      for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
     }
     __syncthreads();
-    if (li < L) {
-      const double2(*h)[NC] = odd ? hm : hp;
-      for (int jj = 0; jj < nj; ++jj) {
-        const double lv = (double)lrow[(size_t)(j0 + jj) * L + li];
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-          const double2 v = h[jj][q];
-          ar[q] += lv * v.x;
-          ai[q] += lv * v.y;
-        }
-      }
-    }
   }
-  if (li >= L) return;
   const double cm = (m == 0) ? 1.0 : 2.0;
+  T* out = reinterpret_cast<T*>(raw);   // [complex column of the half][l][part]
 #pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    const int col = c0 + q;
-    if (col >= ncol) break;
-    T2 z;
-    z.x = T(cm * ar[q]);
-    z.y = T(m == 0 ? 0.0 : cm * ai[q]);
-    Z[(size_t)col * nalm + off + li] = z;
+  for (int hc = 0; hc < 2; ++hc) {
+#pragma unroll
+    for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int l = 2 * (32 * half + 16 * ta + 4 * r + kq) + par, rc = 16 * tb + l16;
+          const double v = cm * acc[ta][2 * hc + tb][r];
+          out[((rc >> 1) * (AC_L + 1) + l) * 2 + (rc & 1)] = T(m == 0 && (rc & 1) ? 0.0 : v);
+        }
+    __syncthreads();
+    const int li = lb * AC_L + tl;
+    for (int q = tr; q < AC_C / 2; q += 2) {
+      const int col = c0 + (AC_C / 2) * hc + q;
+      if (col < ncol && li < L)
+        Z[(size_t)col * nalm + off + li] = reinterpret_cast<const T2*>(raw)[q * (AC_L + 1) + tl];
+    }
+    __syncthreads();
   }
 }
 
@@ -119,7 +168,7 @@ __global__ __launch_bounds__(64) void k_adj_legendre_cols(int lmax, int ntheta, 
 // round-to-nearest add.  The matrix core's FP32 accumulation raised the FP32-context
 // linear term's error against the oracle from 2.7e-6 to 6.5e-6 of rms (its bound is
 // 1e-5; a running FP64 sum did not lower it and cost 25 %), so FP32 contexts keep the
-// FP64 vector sums above; f16x3 contexts, whose operands carry 2^-22, take this kernel, and
+// FP64 sums above; f16x3 contexts, whose operands carry 2^-22, take this kernel, and
 // bf16x3 contexts the split-operand kernel below.
 constexpr int AL_RC = 32;   // rings per staged chunk
 constexpr int AL_NC = 64;   // complex columns per workgroup
@@ -519,14 +568,14 @@ hipError_t launch_pair_maps(const modal_ctx* c, const void* maps, const void* V,
 
 hipError_t launch_adj_legendre_cols(const modal_ctx* c, const void* lam, const void* Gh, int ncol, void* Z,
                                     hipStream_t st) {
+  const int nlf = (c->lmax + AC_L) / AC_L, ncf = (ncol + AC_C - 1) / AC_C;
+  const dim3 gridf(8 * ((c->lmax + 8) / 8) * nlf * ncf);
   if (is_f64(c)) {
-    dim3 grid((c->lmax + 1 + 63) / 64, c->lmax + 1, (ncol + NC - 1) / NC);
-    hipLaunchKernelGGL(k_adj_legendre_cols<double>, grid, dim3(64), 0, st, c->lmax, c->ntheta, c->nrp, ncol, c->nalm,
-                       (const double*)lam, (const double2*)Gh, (double2*)Z);
+    hipLaunchKernelGGL(k_adj_legendre_f64<double>, gridf, dim3(256), 0, st, c->lmax, c->ntheta, c->nrp, ncol, c->nalm,
+                       nlf, ncf, (const double*)lam, (const double2*)Gh, (double2*)Z);
   } else if (c->prec == MODAL_F32) {
-    dim3 grid((c->lmax + 1 + 63) / 64, c->lmax + 1, (ncol + NC - 1) / NC);
-    hipLaunchKernelGGL(k_adj_legendre_cols<float>, grid, dim3(64), 0, st, c->lmax, c->ntheta, c->nrp, ncol, c->nalm,
-                       (const float*)lam, (const float2*)Gh, (float2*)Z);
+    hipLaunchKernelGGL(k_adj_legendre_f64<float>, gridf, dim3(256), 0, st, c->lmax, c->ntheta, c->nrp, ncol, c->nalm,
+                       nlf, ncf, (const float*)lam, (const float2*)Gh, (float2*)Z);
   } else if (c->prec == MODAL_BF16X3) {
     const int nlb = (c->lmax + AS_L) / AS_L, ncb = (ncol + AS_NC - 1) / AS_NC;
     const dim3 grid(8 * ((c->lmax + 8) / 8) * nlb * ncb);

@@ -92,3 +92,28 @@ def test_f32_synthesis_edges(lmax, ntheta, nphi, P, S):
     # the FP32 bound of the map tests, per sky and mode
     rms = np.sqrt(np.mean(ref * ref, axis=(2, 3)))
     assert np.all(np.max(np.abs(got - ref), axis=(2, 3)) <= 1e-5 * rms)
+
+
+# Adjoint of the FP32 and FP64 contexts: 1, 2 and 3 row tiles of 16 modes (P 16 | 17 | 33), l on
+# both sides of a block of 128, ring counts that are and are not a multiple of a 16-ring stage,
+# with and without an equator ring, columns past one block of 32, a last chunk of few pairs.
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S,prec", [(3, 5, 8, 1, 1, "f32"), (127, 129, 256, 2, 3, "f32"),
+                                                       (128, 161, 270, 16, 1, "f32"), (20, 32, 44, 17, 2, "f32"),
+                                                       (17, 27, 54, 33, 1, "f32"), (130, 135, 264, 3, 11, "f64")])
+def test_adjoint_edges(lmax, ntheta, nphi, P, S, prec):
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 73)
+    print(f"[case] adjoint {prec} lmax={lmax} {ntheta}x{nphi} P={P} S={S}", flush=True)
+    a = case.alms(0, S)
+    rng = np.random.default_rng(lmax)
+    cot = rng.standard_normal((S, P * (P + 1) * (P + 2) // 6))
+    V = om.pair_means(case.maps(case.alms(50, 2)))
+    c = _ctx(case, prec)
+    st = c.linear_state()
+    c.linear_reset(st)
+    c.linear_accumulate(st, case.alms(50, 2))
+    c.linear_finalize(st)
+    got = c.beta_vjp(a, cot, state=st).cpu().numpy()
+    tol = 1e-5 if prec == "f32" else 1e-10   # the bounds of the other gradient tests
+    for i in range(S):
+        ref = om.vjp(a[i], case.cl, case.q, case.grid, V, cot[i])[0]
+        assert np.linalg.norm(got[i] - ref) <= tol * np.linalg.norm(ref)
