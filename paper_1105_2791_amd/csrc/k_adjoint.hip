@@ -95,102 +95,113 @@ __global__ __launch_bounds__(256) void k_pair_adjoint(int P, int npairs, int npi
   }
 }
 
-// Float maps, P <= 48: the same contraction on the matrix cores in FP32,
+// FP32 contexts, P <= 48: the same contraction on the matrix cores in FP32,
 //   G[u][x] = w(x) sum_pairs K[u][pair] M_a(x) M_b(x),
-// a GEMM with rows = modes u (three 16-row tiles), columns = pixels, inner index = pairs,
+// a GEMM with rows = modes u (NT 16-row tiles), columns = pixels, inner index = pairs,
 // on v_mfma_f32_16x16x4_f32 (lane l holds A[l % 16][l / 16], B[l / 16][l % 16], and
 // accumulator register r is D[4 (l / 16) + r][l % 16]).  A = K of a 64-pair chunk (FP32,
 // in LDS), B = the pair product of the lane's pixel and pair, formed on the fly.  Each
 // chunk is a chain of 16 MFMAs from zero, added to the running sums with a vector add.
+// A wave owns 64 pixels, four column tiles, so that a K value and a pair read from LDS serve
+// four products; the map rows are 272 floats apart, 16 banks, so that the four neighbouring
+// pairs of a step read different banks.  The row tiles are as many as P needs.  Bound by
+// the matrix cores.  Four skies of 768 x 1536 pixels, P 30: 2.52 ms with three row tiles for
+// every P, two column tiles and the four pairs on one bank; 1.69 ms now (89 TF with the row tile padding).
 // The S skies of one pixel block are consecutive workgroups on one XCD (workgroups are
 // dealt to the 8 XCDs round-robin).
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-constexpr int kMx = 128;  // pixels per workgroup (32 per wave: two 16-column tiles)
-constexpr int kMc = 64;   // pairs per staged chunk (16 MFMA steps of 4)
-constexpr int kMt = 3;    // 16-mode tiles (P <= 48)
+constexpr int kMx = 256;        // pixels per workgroup (64 per wave: four 16-column tiles)
+constexpr int kMs = kMx + 16;   // LDS row stride of the maps
+constexpr int kMc = 64;         // pairs per staged chunk (16 MFMA steps of 4)
+constexpr int kMt = 3;          // 16-mode tiles at most (P <= 48)
 
-__global__ __launch_bounds__(256) void k_pair_adjoint_mfma(int P, int npairs, int npix,
-                                                           const int* __restrict__ pair_a,
-                                                           const int* __restrict__ pair_b,
-                                                           const float* __restrict__ maps, const float* __restrict__ w,
-                                                           const double* __restrict__ K, float* __restrict__ G,
-                                                           int S, int nblk) {
+size_t pair_adjoint_f32_lds(int P, int nt) {
+  return sizeof(float) * ((size_t)P * kMs + nt * 16 * (kMc + 1) + 2 * kMc + 1);
+}
+
+template <int NT>
+__global__ __launch_bounds__(256) void k_pair_adjoint_f32(int P, int npairs, int npix, const int* __restrict__ pair_a,
+                                                          const int* __restrict__ pair_b,
+                                                          const float* __restrict__ maps, const float* __restrict__ w,
+                                                          const double* __restrict__ K, float* __restrict__ G, int S,
+                                                          int nblk) {
   const int i8 = blockIdx.x >> 3;
   const int blk = (blockIdx.x & 7) + 8 * (i8 / S);
   if (blk >= nblk) return;   // whole workgroup, before any barrier
   const int s = i8 % S, x0 = blk * kMx;
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
   const int l16 = lane & 15, kq = lane >> 4;
-  const int xl0 = wv * 32 + l16, xl1 = xl0 + 16;   // this lane's pixels within the block
-  __shared__ float Mt[kMaxP][kMx];
-  __shared__ float Ks[kMt * 16][kMc + 1];
-  __shared__ int sab[kMc];        // a | b << 8 of each pair of the chunk
+  extern __shared__ __attribute__((aligned(16))) float plds[];
+  float* Mt = plds;                                   // [P][kMs]
+  float(*Ks)[kMc + 1] = reinterpret_cast<float(*)[kMc + 1]>(plds + (size_t)P * kMs);
+  int2* sab = reinterpret_cast<int2*>(plds + (((size_t)P * kMs + NT * 16 * (kMc + 1) + 1) & ~(size_t)1));   // row offsets of a, b
   const float* Ms = maps + (size_t)s * P * npix;
   for (int e = tid; e < P * kMx; e += 256) {
     const int p = e / kMx, xx = e - p * kMx;
-    Mt[p][xx] = x0 + xx < npix ? Ms[(size_t)p * npix + x0 + xx] : 0.f;
+    const float v = Ms[(size_t)p * npix + min(x0 + xx, npix - 1)];
+    Mt[p * kMs + xx] = x0 + xx < npix ? v : 0.f;
   }
-  f32x4 acc[2][kMt];
+  f32x4 acc[4][NT];
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int t = 0; t < kMt; ++t) acc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NT; ++t) acc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   const double* Kslab = K + (size_t)s * P * npairs;
   // the next chunk's K and pair modes are loaded into registers before this chunk's
-  // MFMAs, so that their latency is hidden behind them
-  constexpr int NK = kMt * 16 * kMc / 256;
+  // MFMAs, so that their latency is hidden behind them (indices clamped: a chunk past the
+  // last is not used)
+  constexpr int NK = NT * 16 * kMc / 256;
+  const int kpc = tid & (kMc - 1), ku = tid / kMc;
   double pk[NK];
-  int pab = 0;
+  int pa = 0, pb = 0;
   auto load_chunk = [&](int c0) {
-    const int nc = min(kMc, npairs - c0);
+    const int k = min(c0 + kpc, npairs - 1);
 #pragma unroll
-    for (int i = 0; i < NK; ++i) {
-      const int e = tid + 256 * i, u = e / kMc, pc = e - u * kMc;
-      pk[i] = (u < P && pc < nc) ? Kslab[(size_t)u * npairs + c0 + pc] : 0.0;
-    }
-    if (tid < kMc) pab = tid < nc ? (pair_a[c0 + tid] | (pair_b[c0 + tid] << 8)) : 0;
+    for (int i = 0; i < NK; ++i) pk[i] = Kslab[(size_t)min(ku + 4 * i, P - 1) * npairs + k];
+    pa = pair_a[k];
+    pb = pair_b[k];
   };
   load_chunk(0);
   for (int c0 = 0; c0 < npairs; c0 += kMc) {
+    const int nc = min(kMc, npairs - c0);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NK; ++i) {
-      const int e = tid + 256 * i, u = e / kMc, pc = e - u * kMc;
-      Ks[u][pc] = (float)pk[i];
-    }
-    if (tid < kMc) sab[tid] = pab;
+    for (int i = 0; i < NK; ++i) Ks[ku + 4 * i][kpc] = (ku + 4 * i < P && kpc < nc) ? (float)pk[i] : 0.f;
+    if (tid < kMc) sab[tid] = make_int2(pa * kMs, pb * kMs);   // pairs past the last repeat it against K = 0
     __syncthreads();
-    if (c0 + kMc < npairs) load_chunk(c0 + kMc);
-    // pairs past nc have zero K columns: whatever their product is contributes nothing
-    f32x4 ch[2][kMt];
+    load_chunk(c0 + kMc);
+    f32x4 ch[4][NT];
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int t = 0; t < kMt; ++t) ch[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int ks = 0; ks < kMc / 4; ++ks) {
+      for (int t = 0; t < NT; ++t) ch[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float* Mx = Mt + 64 * wv + l16;
+    const int nks = (nc + 3) / 4;
+    for (int ks = 0; ks < nks; ++ks) {
       const int pc = 4 * ks + kq;
-      const int ab = sab[pc], a = ab & 0xff, b2 = (ab >> 8) & 0xff;
-      const float b0 = Mt[a][xl0] * Mt[b2][xl0], b1 = Mt[a][xl1] * Mt[b2][xl1];
+      const int2 ab = sab[pc];
+      float b[4], av[NT];
 #pragma unroll
-      for (int t = 0; t < kMt; ++t) {
-        const float av = Ks[16 * t + l16][pc];
-        ch[0][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b0, ch[0][t], 0, 0, 0);
-        ch[1][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b1, ch[1][t], 0, 0, 0);
-      }
+      for (int c = 0; c < 4; ++c) b[c] = Mx[ab.x + 16 * c] * Mx[ab.y + 16 * c];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) av[t] = Ks[16 * t + l16][pc];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) ch[c][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t], b[c], ch[c][t], 0, 0, 0);
     }
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int t = 0; t < kMt; ++t) acc[c][t] += ch[c][t];
+      for (int t = 0; t < NT; ++t) acc[c][t] += ch[c][t];
   }
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int x = x0 + (c ? xl1 : xl0);
+  for (int c = 0; c < 4; ++c) {
+    const int x = x0 + 64 * wv + 16 * c + l16;
     if (x >= npix) continue;
     const float wx = w[x];
 #pragma unroll
-    for (int t = 0; t < kMt; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int u = 16 * t + 4 * kq + r;
@@ -559,10 +570,15 @@ hipError_t launch_pair_adjoint(const modal_ctx* c, const void* maps, const void*
                        c->npairs, c->npix, S, c->t.pair_a, c->t.pair_b, (const double*)maps, c->t.w64,
                        (const double*)K, (double*)G);
   } else if (c->P <= kMt * 16) {
-    const int nblk = (c->npix + kMx - 1) / kMx;
-    hipLaunchKernelGGL(k_pair_adjoint_mfma, dim3(8 * ((nblk + 7) / 8) * S), dim3(256), 0, st, c->P, c->npairs,
-                       c->npix, c->t.pair_a, c->t.pair_b, (const float*)maps, c->t.w32, (const double*)K, (float*)G,
-                       S, nblk);
+    const int nblk = (c->npix + kMx - 1) / kMx, nt = (c->P + 15) / 16;
+    const size_t lds = pair_adjoint_f32_lds(c->P, nt);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(8 * ((nblk + 7) / 8) * S), dim3(256), lds, st, c->P, c->npairs, c->npix, c->t.pair_a,
+                         c->t.pair_b, (const float*)maps, c->t.w32, (const double*)K, (float*)G, S, nblk);
+    };
+    if (nt == 1) launch(k_pair_adjoint_f32<1>);
+    else if (nt == 2) launch(k_pair_adjoint_f32<2>);
+    else launch(k_pair_adjoint_f32<3>);
   } else {
     hipLaunchKernelGGL((k_pair_adjoint<float, 2>), dim3((c->npix + kPx - 1) / kPx, (S + 1) / 2), dim3(256), 0, st,
                        c->P, c->npairs, c->npix, S, c->t.pair_a, c->t.pair_b, (const float*)maps, c->t.w32,
