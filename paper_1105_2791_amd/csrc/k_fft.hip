@@ -405,6 +405,16 @@ __device__ inline void dft_plus(float2* x) {
   }
 }
 
+// A wave's passes exchange points through its LDS buffer with no barrier: its LDS accesses
+// complete in program order.  This keeps the order in the program: between the reads and the
+// writes of a pass, and between passes, no access moves and no branch on the lane is carried
+// over (where the last round of a pass has idle lanes, the compiler otherwise may run the next
+// pass's reads of those lanes before the other lanes' writes).
+__device__ inline void wave_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // one Stockham pass of radix R over the ring buffer b (length K); twp is this pass's
 // twiddle table, twp[(q - 1) Ns + k] = e^{2 pi i q k / (Ns R)}, laid out so that the
 // lanes of a wave (consecutive k) read consecutive entries
@@ -428,6 +438,7 @@ __device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float
       for (int q = 0; q < R; ++q) v[i][q] = b[padr(bi + q * KR)];
     }
   }
+  wave_order();
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const int bi = lane + 64 * i;
@@ -450,6 +461,7 @@ __device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float
       }
     }
   }
+  wave_order();
 }
 
 // cos and sin of 2 pi j / 47, j < 47, rounded to float
@@ -483,6 +495,7 @@ __device__ inline void rg_pass47_first(float2* b, int lane) {
   float2 x[47];
 #pragma unroll
   for (int r = 0; r < 47; ++r) x[r] = b[padr(lane + 64 * r)];
+  wave_order();
 #pragma unroll
   for (int r = 1; r < 24; ++r) {
     const float2 sr = cadd(x[r], x[47 - r]), dr = csub(x[r], x[47 - r]);
@@ -508,6 +521,7 @@ __device__ inline void rg_pass47_first(float2* b, int lane) {
     b[padr(ob + q)] = make_float2(A.x - B.y, A.y + B.x);
     b[padr(ob + 47 - q)] = make_float2(A.x + B.y, A.y - B.x);
   }
+  wave_order();
 }
 
 template <int PTS, int KC>
@@ -515,7 +529,11 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
                                             const float2* __restrict__ F, float* __restrict__ maps,
                                             const float2* __restrict__ twg, const float2* __restrict__ twpg) {
   extern __shared__ __attribute__((aligned(16))) float2 rbuf[];
-  const int K = KC ? KC : plan.K;   // KC: a plan compiled in (24 x 8 x 8 of K = 1536, 47 x 8 x 8 of 3008)
+  // KC: a plan compiled in (24 x 8 x 8 of K = 1536, 47 x 8 x 8 of 3008, 8 x 8 x 4 x 3 of 768).
+  // The last keeps K an argument outside the passes: with it constant the compiler contracts
+  // the spectrum formula below into other FMAs, and the maps would differ in their last bit
+  // from the plan run with all its lengths as arguments.
+  const int K = KC && KC != 768 ? KC : plan.K;
   const int KP = padr(K) + 1;
   float2* tw = rbuf + RG_RINGS * KP;   // e^{2 pi i t / N}, t <= K / 2, shared by the workgroup's rings
   float2* twp = tw + K / 2 + 1;          // the passes' twiddle tables, K - 1 entries in all
@@ -530,6 +548,23 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
   const int b = blockIdx.x;
   const int xcd = b & 7, half = (b >> 3) & 1, slot = b >> 4;
   const int nslot = gridDim.x >> 4;
+  // Spectrum loads: ZE elements per thread per round, as many as the register budget holds
+  // (rounds of 4, one of 6, 3 or 12: 8 skies of 768 x 1536 pixels, 30 modes, 0.52 -> 0.46 ms; of
+  // 1536 x 3072, 40 modes, 2.35 -> 2.20; 4 of 3008 x 6016, 50 modes, 12.2 -> 11.6; everything of a
+  // unit in one round is slower for the first two, which then lose a wave per SIMD).
+  constexpr int ZE = KC == 3008 ? 12 : KC == 1536 ? 6 : KC == 768 ? 3 : 4;
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  f4 xa[ZE], xb[ZE];
+  auto load_spectra = [&](int unit, int e0) {
+    const f4* src = reinterpret_cast<const f4*>(F + (size_t)unit * (lmax + 1) * 8 + RG_RINGS * half);
+#pragma unroll
+    for (int i = 0; i < ZE; ++i) {
+      const int e = min(e0 + tid + i * 64 * RG_RINGS, 2 * K - 1);
+      const int m = e >> 1, rp = e & 1;
+      xa[i] = src[(size_t)min(m, lmax) * 4 + rp];
+      xb[i] = src[(size_t)min(K - m, lmax) * 4 + rp];
+    }
+  };
   for (int unit = xcd + 8 * slot; unit < units; unit += 8 * nslot) {
     const int seq = unit / nrb8, rb = unit - seq * nrb8;
     // previous unit's buffers (and the twiddle table) are settled; its map stores stay in
@@ -540,19 +575,9 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
     // of the half-length complex transform:
     //   Z_m = (X_m + conj X_{K-m}) + i e^{2 pi i m / N} (X_m - conj X_{K-m}),  m < K,
     // with X_m = F_m for m <= lmax (X_0 real) and 0 otherwise.  Element e = (m, rp), both
-    // loads unconditional (index clamped, value selected after), ZE elements per thread
-    // per round.
-    const float4* src = reinterpret_cast<const float4*>(F + (size_t)unit * (lmax + 1) * 8 + RG_RINGS * half);
-    constexpr int ZE = 4;
+    // loads unconditional (index clamped, value selected after).
     for (int e0 = 0; e0 < 2 * K; e0 += ZE * 64 * RG_RINGS) {
-      float4 xa[ZE], xb[ZE];
-#pragma unroll
-      for (int i = 0; i < ZE; ++i) {
-        const int e = min(e0 + tid + i * 64 * RG_RINGS, 2 * K - 1);
-        const int m = e >> 1, rp = e & 1;
-        xa[i] = src[(size_t)min(m, lmax) * 4 + rp];
-        xb[i] = src[(size_t)min(K - m, lmax) * 4 + rp];
-      }
+      load_spectra(unit, e0);
 #pragma unroll
       for (int i = 0; i < ZE; ++i) {
         const int e = e0 + tid + i * 64 * RG_RINGS;
@@ -562,9 +587,9 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
           const float2 ew = (m <= K / 2) ? tw[m] : make_float2(-tw[K - m].x, tw[K - m].y);
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
-            float2 X = ha ? (j ? make_float2(xa[i].z, xa[i].w) : make_float2(xa[i].x, xa[i].y)) : make_float2(0.f, 0.f);
+            float2 X = ha ? make_float2(xa[i][2 * j], xa[i][2 * j + 1]) : make_float2(0.f, 0.f);
             if (m == 0) X.y = 0.f;
-            const float2 Y = hb ? (j ? make_float2(xb[i].z, xb[i].w) : make_float2(xb[i].x, xb[i].y)) : make_float2(0.f, 0.f);
+            const float2 Y = hb ? make_float2(xb[i][2 * j], xb[i][2 * j + 1]) : make_float2(0.f, 0.f);
             const float2 sa = make_float2(X.x + Y.x, X.y - Y.y), d = make_float2(X.x - Y.x, X.y + Y.y);
             rbuf[(2 * rp + j) * KP + padr(m)] =
                 make_float2(sa.x - (ew.x * d.y + ew.y * d.x), sa.y + (ew.x * d.x - ew.y * d.y));
@@ -572,7 +597,7 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
         }
       }
     }
-    __syncthreads();
+    lds_barrier();   // (the previous unit's map stores stay in flight here too)
 
     float2* bw = rbuf + w * KP;
     // z = sum_m Z_m e^{+2 pi i m n / K}; the last pass writes the map row directly:
@@ -584,6 +609,12 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
       rg_pass<24, PTS, false, KC, 1>(bw, K, 1, lane, twp);
       rg_pass<8, PTS, false, KC, 24>(bw, K, 24, lane, twp + 23);
       rg_pass<8, PTS, true, KC, 192>(bw, K, 192, lane, twp + 23 + 7 * 24, dst);
+    } else if constexpr (KC == 768) {
+      // passes 8, 8, 4, 3 (strides 1, 8, 64, 256; twiddle tables at 0, 7, 63, 255)
+      rg_pass<8, PTS, false, KC, 1>(bw, K, 1, lane, twp);
+      rg_pass<8, PTS, false, KC, 8>(bw, K, 8, lane, twp + 7);
+      rg_pass<4, PTS, false, KC, 64>(bw, K, 64, lane, twp + 63);
+      rg_pass<3, PTS, true, KC, 256>(bw, K, 256, lane, twp + 255, dst);
     } else if constexpr (KC == 3008) {
       // passes 47, 8, 8 (strides 1, 47, 376; twiddle tables at 46, 46 + 7 * 47)
       rg_pass47_first(bw, lane);
@@ -593,17 +624,17 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
       int Ns = 1;
       const float2* tf = twp;
       // (a last pass of radix 8, the common case, stores straight to the row; other plans
-      // finish in LDS and copy the row out)
+      // finish in LDS and copy the row out; radix 24 occurs only where 24 points fit a lane)
       const bool direct = plan.radix[plan.nf - 1] == 8;
       for (int f = 0; f < plan.nf; ++f) {
         const int R = plan.radix[f];
         if (direct && f == plan.nf - 1) rg_pass<8, PTS, true>(bw, K, Ns, lane, tf, dst);
-        else if (R == 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
         else if (R == 8) rg_pass<8, PTS>(bw, K, Ns, lane, tf);
         else if (R == 4) rg_pass<4, PTS>(bw, K, Ns, lane, tf);
         else if (R == 2) rg_pass<2, PTS>(bw, K, Ns, lane, tf);
         else if (R == 3) rg_pass<3, PTS>(bw, K, Ns, lane, tf);
-        else rg_pass<5, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 5) rg_pass<5, PTS>(bw, K, Ns, lane, tf);
+        else if constexpr (PTS >= 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
         tf += (R - 1) * Ns;
         Ns *= R;
       }
@@ -628,6 +659,16 @@ __global__ __launch_bounds__(64 * RG_RINGS) __attribute__((amdgpu_waves_per_eu(2
     FftPlan plan, int lmax, int ntheta, int nseq, const float2* __restrict__ F, float* __restrict__ maps,
     const float2* __restrict__ twg, const float2* __restrict__ twpg) {
   c2r_rg_body<24, 1536>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
+}
+
+// the plan 8 x 8 x 4 x 3 of K = 768 (the rings of nphi 1536, the l_max 500 grid): 117 registers
+// and four waves per SIMD where the plan run from its arguments takes 172 and two (8 skies of
+// 768 rings, 30 modes: 0.80 -> 0.46 ms, 4.1 TB/s, near the rate of a copy; r2c of 64 planes
+// 0.25 -> 0.15 ms)
+__global__ __launch_bounds__(64 * RG_RINGS) __attribute__((amdgpu_waves_per_eu(4))) void k_fft_c2r_rg_k768(
+    FftPlan plan, int lmax, int ntheta, int nseq, const float2* __restrict__ F, float* __restrict__ maps,
+    const float2* __restrict__ twg, const float2* __restrict__ twpg) {
+  c2r_rg_body<16, 768>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
 }
 
 // the plan 47 x 8 x 8 of K = 3008 (the rings of nphi 6016, the l_max 2000 grid): its
@@ -695,10 +736,16 @@ __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_r2c_rg(FftPlan plan, int 
           bw[padr(n)] = make_float2(v.x, -v.y);
         }
       }
+      wave_order();
       if constexpr (KC == 1536) {
         rg_pass<24, PTS, false, KC, 1>(bw, K, 1, lane, twp);
         rg_pass<8, PTS, false, KC, 24>(bw, K, 24, lane, twp + 23);
         rg_pass<8, PTS, false, KC, 192>(bw, K, 192, lane, twp + 23 + 7 * 24);
+      } else if constexpr (KC == 768) {
+        rg_pass<8, PTS, false, KC, 1>(bw, K, 1, lane, twp);
+        rg_pass<8, PTS, false, KC, 8>(bw, K, 8, lane, twp + 7);
+        rg_pass<4, PTS, false, KC, 64>(bw, K, 64, lane, twp + 63);
+        rg_pass<3, PTS, false, KC, 256>(bw, K, 256, lane, twp + 255);
       } else if constexpr (KC == 3008) {
         rg_pass47_first(bw, lane);
         rg_pass<8, PTS, false, KC, 47>(bw, K, 47, lane, twp + 46);
@@ -708,12 +755,12 @@ __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_r2c_rg(FftPlan plan, int 
         const float2* tf = twp;
         for (int f = 0; f < plan.nf; ++f) {
           const int R = plan.radix[f];
-          if (R == 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 8) rg_pass<8, PTS>(bw, K, Ns, lane, tf);
+          if (R == 8) rg_pass<8, PTS>(bw, K, Ns, lane, tf);
           else if (R == 4) rg_pass<4, PTS>(bw, K, Ns, lane, tf);
           else if (R == 2) rg_pass<2, PTS>(bw, K, Ns, lane, tf);
           else if (R == 3) rg_pass<3, PTS>(bw, K, Ns, lane, tf);
-          else rg_pass<5, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 5) rg_pass<5, PTS>(bw, K, Ns, lane, tf);
+          else if constexpr (PTS >= 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
           tf += (R - 1) * Ns;
           Ns *= R;
         }
@@ -846,6 +893,11 @@ bool plan_is_k1536(const FftPlan& p) {
   return p.K == 1536 && p.nf == 3 && p.radix[0] == 24 && p.radix[1] == 8 && p.radix[2] == 8;
 }
 
+// K = 768 (the rings of nphi 1536, the l_max 500 grid)
+bool plan_is_k768(const FftPlan& p) {
+  return p.K == 768 && p.nf == 4 && p.radix[0] == 8 && p.radix[1] == 8 && p.radix[2] == 4 && p.radix[3] == 3;
+}
+
 // K = 3008 (nphi 6016, the l_max 2000 grid); the register kernels run it only compiled in
 bool plan_is_k3008(const FftPlan& p) {
   return p.K == 3008 && p.nf == 3 && p.radix[0] == 47 && p.radix[1] == 8 && p.radix[2] == 8;
@@ -868,6 +920,10 @@ hipError_t launch_fft_c2r(const modal_ctx* c, const void* F, int S, void* maps, 
       hipLaunchKernelGGL(k_fft_c2r_rg_k1536, dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st,
                          c->fft_rg_plan, c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps,
                          (const float2*)c->t.tw32, (const float2*)c->t.twp32);
+    else if (plan_is_k768(c->fft_rg_plan))
+      hipLaunchKernelGGL(k_fft_c2r_rg_k768, dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st, c->fft_rg_plan,
+                         c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps, (const float2*)c->t.tw32,
+                         (const float2*)c->t.twp32);
     else if (plan_is_k3008(c->fft_rg_plan))   // one workgroup per CU: 256 of them
       hipLaunchKernelGGL(k_fft_c2r_rg_k3008, dim3(std::min(blocks, 256)), dim3(64 * RG_RINGS), fft_rg_lds(c), st,
                          c->fft_rg_plan, c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps,
@@ -911,6 +967,10 @@ hipError_t launch_fft_r2c_rows(const modal_ctx* c, const void* G, size_t nseq, v
                      (const float2*)c->t.twp32)
     if (plan_is_k1536(c->fft_rg_plan) && pts == 24)
       hipLaunchKernelGGL((k_fft_r2c_rg<24, 1536>), dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st,
+                         c->fft_rg_plan, c->lmax, c->ntheta, (int)nseq, (const float*)G, (float2*)Gh,
+                         (const float2*)c->t.tw32, (const float2*)c->t.twp32);
+    else if (plan_is_k768(c->fft_rg_plan))
+      hipLaunchKernelGGL((k_fft_r2c_rg<16, 768>), dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st,
                          c->fft_rg_plan, c->lmax, c->ntheta, (int)nseq, (const float*)G, (float2*)Gh,
                          (const float2*)c->t.tw32, (const float2*)c->t.twp32);
     else if (plan_is_k3008(c->fft_rg_plan))

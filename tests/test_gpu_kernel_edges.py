@@ -117,3 +117,24 @@ def test_adjoint_edges(lmax, ntheta, nphi, P, S, prec):
     for i in range(S):
         ref = om.vjp(a[i], case.cl, case.q, case.grid, V, cot[i])[0]
         assert np.linalg.norm(got[i] - ref) <= tol * np.linalg.norm(ref)
+
+
+# Ring transforms compiled in (nphi 1536, 3072, 6016) and a general one (1440), both directions,
+# with ring groups of 8 that are not full, l_max far below and at the ring's limit.
+@pytest.mark.parametrize("lmax,ntheta,nphi", [(20, 21, 1536), (767, 770, 1536), (20, 21, 3072), (20, 27, 6016),
+                                              (20, 21, 1440)])
+def test_ring_transform_edges(lmax, ntheta, nphi):
+    P = 2
+    case = Case("edge", lmax, ntheta, nphi, P, 1, "wmap", 74)
+    print(f"[case] ring transforms lmax={lmax} {ntheta}x{nphi}", flush=True)
+    a = case.alms(0, 1)
+    c = _ctx(case, "f32")
+    out = torch.full((1, P, ntheta, nphi), float("nan"), dtype=torch.float32, device="cuda")
+    got = c.filter_maps(a, out=out).cpu().numpy()[0]
+    ref = case.maps(a)[0]
+    rms = np.sqrt(np.mean(ref * ref, axis=(1, 2)))
+    assert np.all(np.max(np.abs(got - ref), axis=(1, 2)) <= 1e-5 * rms)
+    cot = np.random.default_rng(5).standard_normal((1, 4))
+    g = c.beta_vjp(a, cot).cpu().numpy()[0]
+    gref = om.vjp(a[0], case.cl, case.q, case.grid, None, cot[0])[0]
+    assert np.linalg.norm(g - gref) <= 1e-5 * np.linalg.norm(gref)
