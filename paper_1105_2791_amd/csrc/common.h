@@ -145,6 +145,8 @@ hipError_t launch_fft_c2r(const modal_ctx* c, const void* F, int S, void* maps, 
 // ring r2c FFT: Gh[S][P][lmax+1][ntheta] complex from G[S][P][ntheta][nphi]
 hipError_t launch_fft_r2c(const modal_ctx* c, const void* G, int S, void* Gh, hipStream_t st);
 hipError_t launch_fft_r2c_rows(const modal_ctx* c, const void* G, size_t nseq, void* Gh, hipStream_t st);
+// register-pass contexts: nk planes U of a state -> V = U scale in place, Gh of w V
+hipError_t launch_fft_r2c_state(const modal_ctx* c, void* U, int nk, double scale, void* Gh, hipStream_t st);
 int fft_rings_per_block(const modal_ctx* c);
 bool fft_plan_rg(int N, FftPlan& p);
 std::vector<float> fft_rg_twiddles(const FftPlan& p);

@@ -834,7 +834,9 @@ modal_status modal_linear_term(modal_ctx* c, int mode, const void* alm, int S, v
       if (state != c->lin_state || c->lin_final || c->lin_count <= 0)
         return fail(c, MODAL_ENOTREADY, "linear_term: FINALIZE needs an accumulated, unfinalised state");
       if ((s = check_ws(c, MODAL_OP_LINEAR_FINALIZE, 1, ws, ws_bytes)) != MODAL_OK) return s;
-      HIPTRY(launch_lin_scale(c, state, 1.0 / (double)c->lin_count, st));
+      // V = U / count: with the register-pass transforms as their rows are loaded, else first
+      const double inv = 1.0 / (double)c->lin_count;
+      if (!c->fft_rg) HIPTRY(launch_lin_scale(c, state, inv, st));
       // Z = c_m sum_j lambda_lm sum_k w V e^{-i m phi_k} for every pair plane
       Carver cv(ws);
       void* lam = cv.take(lam_bytes(c));
@@ -845,9 +847,13 @@ modal_status modal_linear_term(modal_ctx* c, int mode, const void* alm, int S, v
       char* Z = (char*)state + lin_V_bytes(c);
       for (int p0 = 0; p0 < c->npairs; p0 += nch) {
         const int nk = std::min(nch, c->npairs - p0);
-        const void* Vp = (const char*)state + (size_t)p0 * c->npix * real_bytes(c);
-        STAGE(MODAL_STAGE_ADJ_PAIR, launch_weight_planes(c, Vp, nk, G, st));
-        STAGE(MODAL_STAGE_ADJ_FFT, launch_fft_r2c_rows(c, G, (size_t)nk, Gh, st));
+        void* Vp = (char*)state + (size_t)p0 * c->npix * real_bytes(c);
+        if (c->fft_rg) {
+          STAGE(MODAL_STAGE_ADJ_FFT, launch_fft_r2c_state(c, Vp, nk, inv, Gh, st));
+        } else {
+          STAGE(MODAL_STAGE_ADJ_PAIR, launch_weight_planes(c, Vp, nk, G, st));
+          STAGE(MODAL_STAGE_ADJ_FFT, launch_fft_r2c_rows(c, G, (size_t)nk, Gh, st));
+        }
         STAGE(MODAL_STAGE_ADJ_LEGENDRE,
               launch_adj_legendre_cols(c, lam, Gh, nk, Z + (size_t)p0 * c->nalm * 2 * real_bytes(c), st));
       }

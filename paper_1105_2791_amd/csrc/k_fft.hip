@@ -13,6 +13,8 @@
 // table (rounded to the working precision).
 #include "common.h"
 
+#include <type_traits>
+
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -685,11 +687,18 @@ __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_c2r_rg_k3008(
 // workgroup barrier every thread forms Gh_m of one (m, ring) of the four rings from
 // Z_m and Z_{K-m} (see the top of the file), and consecutive threads write the four
 // rings of one m, the contiguous run of the [seq][m][ring] layout.
-template <int PTS, int KC = 0>
+//
+// STATE: the rows are pair sums U of a linear-term state.  A row is scaled to the pair means
+// V = U scale (rounded to float, written back in place) and weighted, G = w V, as it is loaded;
+// as passes of their own over the planes the scaling and the weighting read and wrote 8 bytes
+// per pixel each (820 planes of 768 x 1536: 1.67 and 1.82 ms).
+template <int PTS, int KC = 0, bool STATE = false>
 __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_r2c_rg(FftPlan plan, int lmax, int ntheta, int nseq,
-                                                              const float* __restrict__ G, float2* __restrict__ Gh,
+                                                              std::conditional_t<STATE, float, const float>* __restrict__ G,
+                                                              float2* __restrict__ Gh,
                                                               const float2* __restrict__ twg,
-                                                              const float2* __restrict__ twpg) {
+                                                              const float2* __restrict__ twpg,
+                                                              const float* __restrict__ wpix, double scale) {
   extern __shared__ __attribute__((aligned(16))) float2 rbuf[];
   const int K = KC ? KC : plan.K;   // KC: a plan compiled in (24 x 8 x 8 of K = 1536, 47 x 8 x 8 of 3008)
   const int KP = padr(K) + 1;
@@ -712,28 +721,42 @@ __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_r2c_rg(FftPlan plan, int 
     const int j = jb + w;
     float2* bw = rbuf + w * KP;
     if (j < ntheta) {   // wave-uniform
-      const float2* src = reinterpret_cast<const float2*>(G + ((size_t)seq * ntheta + j) * plan.N);
+      auto* src = reinterpret_cast<std::conditional_t<STATE, float2, const float2>*>(G + ((size_t)seq * ntheta + j) * plan.N);
+      const float2* wrow = reinterpret_cast<const float2*>(wpix + (size_t)j * plan.N);   // STATE only
+      // U -> V in place, the transform's input w V
+      auto weighted = [&](float2 u, float2 ww, int n) {
+        if constexpr (STATE) {
+          u = make_float2((float)((double)u.x * scale), (float)((double)u.y * scale));
+          src[n] = u;
+          u = make_float2((float)((double)u.x * (double)ww.x), (float)((double)u.y * (double)ww.y));
+        }
+        return make_float2(u.x, -u.y);
+      };
       if constexpr (PTS <= 24) {
         // the row in rounds of 8 loads per lane issued before their stores (64 PTS >= K):
         // a round trip per 512 points instead of per 64 (at more points per lane the extra
         // registers would cost the second wave per SIMD)
-        const float2* srcl = src + lane;
+        const auto* srcl = src + lane;
         float2* dstb = bw + padr(lane);   // padr(n + 64) = padr(n) + 72: constant offsets
         constexpr int RL = 8;
 #pragma unroll
         for (int i0 = 0; i0 < PTS; i0 += RL) {
-          float2 v[RL];
+          float2 v[RL], ww[RL];
 #pragma unroll
           for (int i = 0; i < RL; ++i)
-            if (i0 + i < PTS && lane + 64 * (i0 + i) < K) v[i] = srcl[64 * (i0 + i)];
+            if (i0 + i < PTS && lane + 64 * (i0 + i) < K) {
+              v[i] = srcl[64 * (i0 + i)];
+              if (STATE) ww[i] = wrow[lane + 64 * (i0 + i)];
+            }
 #pragma unroll
           for (int i = 0; i < RL; ++i)
-            if (i0 + i < PTS && lane + 64 * (i0 + i) < K) dstb[72 * (i0 + i)] = make_float2(v[i].x, -v[i].y);
+            if (i0 + i < PTS && lane + 64 * (i0 + i) < K)
+              dstb[72 * (i0 + i)] = weighted(v[i], STATE ? ww[i] : v[i], lane + 64 * (i0 + i));
         }
       } else {
         for (int n = lane; n < K; n += 64) {
           const float2 v = src[n];
-          bw[padr(n)] = make_float2(v.x, -v.y);
+          bw[padr(n)] = weighted(v, STATE ? wrow[n] : v, n);
         }
       }
       wave_order();
@@ -873,9 +896,18 @@ hipError_t fft_rg_set_lds(size_t bytes) {
     e = hipFuncSetAttribute((const void*)k_fft_c2r_rg_k1536, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e == hipSuccess)
     e = hipFuncSetAttribute((const void*)k_fft_c2r_rg_k3008, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  const void* r2c[] = {(const void*)k_fft_r2c_rg<16>,       (const void*)k_fft_r2c_rg<24>,
-                       (const void*)k_fft_r2c_rg<32>,       (const void*)k_fft_r2c_rg<48>,
-                       (const void*)k_fft_r2c_rg<24, 1536>, (const void*)k_fft_r2c_rg<48, 3008>};
+  const void* r2c[] = {(const void*)k_fft_r2c_rg<16>,
+                       (const void*)k_fft_r2c_rg<24>,
+                       (const void*)k_fft_r2c_rg<32>,
+                       (const void*)k_fft_r2c_rg<48>,
+                       (const void*)k_fft_r2c_rg<24, 1536>,
+                       (const void*)k_fft_r2c_rg<48, 3008>,
+                       (const void*)k_fft_r2c_rg<16, 0, true>,
+                       (const void*)k_fft_r2c_rg<24, 0, true>,
+                       (const void*)k_fft_r2c_rg<32, 0, true>,
+                       (const void*)k_fft_r2c_rg<48, 0, true>,
+                       (const void*)k_fft_r2c_rg<24, 1536, true>,
+                       (const void*)k_fft_r2c_rg<48, 3008, true>};
   for (const void* f : r2c)
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   return e;
@@ -954,36 +986,39 @@ hipError_t launch_fft_r2c(const modal_ctx* c, const void* G, int S, void* Gh, hi
   return launch_fft_r2c_rows(c, G, (size_t)S * c->P, Gh, st);
 }
 
+namespace {
+// register-pass r2c of nseq sequences of ring rows; STATE: U scaled to V in place, transform of w V
+template <bool STATE>
+hipError_t fft_r2c_rg(const modal_ctx* c, std::conditional_t<STATE, float, const float>* G, size_t nseq, void* Gh,
+                      double scale, hipStream_t st) {
+  const int units = (int)nseq * f_ring_blocks(c->ntheta);
+  const int blocks = std::min(16 * ((units + 7) / 8), 16 * 64);
+  const FftPlan& p = c->fft_rg_plan;
+  const int pts = fft_rg_points(p);
+  auto launch = [&](auto kernel, int grid) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * RG_RINGS), fft_rg_lds(c), st, p, c->lmax, c->ntheta, (int)nseq, G,
+                       (float2*)Gh, (const float2*)c->t.tw32, (const float2*)c->t.twp32, (const float*)c->t.w32, scale);
+  };
+  if (plan_is_k1536(p) && pts == 24) launch(k_fft_r2c_rg<24, 1536, STATE>, blocks);
+  else if (plan_is_k768(p)) launch(k_fft_r2c_rg<16, 768, STATE>, blocks);
+  else if (plan_is_k3008(p)) launch(k_fft_r2c_rg<48, 3008, STATE>, std::min(blocks, 256));
+  else if (pts <= 16) launch(k_fft_r2c_rg<16, 0, STATE>, blocks);
+  else if (pts <= 24) launch(k_fft_r2c_rg<24, 0, STATE>, blocks);
+  else if (pts <= 32) launch(k_fft_r2c_rg<32, 0, STATE>, blocks);
+  else launch(k_fft_r2c_rg<48, 0, STATE>, blocks);
+  return hipGetLastError();
+}
+}  // namespace
+
+// nk pair planes of a state, scaled in place and weighted as they are loaded
+hipError_t launch_fft_r2c_state(const modal_ctx* c, void* U, int nk, double scale, void* Gh, hipStream_t st) {
+  if (!c->fft_rg) return hipErrorInvalidValue;
+  return fft_r2c_rg<true>(c, (float*)U, (size_t)nk, Gh, scale, st);
+}
+
 // nseq sequences of ntheta ring rows each
 hipError_t launch_fft_r2c_rows(const modal_ctx* c, const void* G, size_t nseq, void* Gh, hipStream_t st) {
-  if (c->fft_rg) {
-    const int units = (int)nseq * f_ring_blocks(c->ntheta);
-    int blocks = 16 * ((units + 7) / 8);
-    blocks = std::min(blocks, 16 * 64);
-    const int pts = fft_rg_points(c->fft_rg_plan);
-#define LAUNCH(PT)                                                                                                \
-  hipLaunchKernelGGL(k_fft_r2c_rg<PT>, dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st, c->fft_rg_plan,        \
-                     c->lmax, c->ntheta, (int)nseq, (const float*)G, (float2*)Gh, (const float2*)c->t.tw32,       \
-                     (const float2*)c->t.twp32)
-    if (plan_is_k1536(c->fft_rg_plan) && pts == 24)
-      hipLaunchKernelGGL((k_fft_r2c_rg<24, 1536>), dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st,
-                         c->fft_rg_plan, c->lmax, c->ntheta, (int)nseq, (const float*)G, (float2*)Gh,
-                         (const float2*)c->t.tw32, (const float2*)c->t.twp32);
-    else if (plan_is_k768(c->fft_rg_plan))
-      hipLaunchKernelGGL((k_fft_r2c_rg<16, 768>), dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st,
-                         c->fft_rg_plan, c->lmax, c->ntheta, (int)nseq, (const float*)G, (float2*)Gh,
-                         (const float2*)c->t.tw32, (const float2*)c->t.twp32);
-    else if (plan_is_k3008(c->fft_rg_plan))
-      hipLaunchKernelGGL((k_fft_r2c_rg<48, 3008>), dim3(std::min(blocks, 256)), dim3(64 * RG_RINGS), fft_rg_lds(c),
-                         st, c->fft_rg_plan, c->lmax, c->ntheta, (int)nseq, (const float*)G, (float2*)Gh,
-                         (const float2*)c->t.tw32, (const float2*)c->t.twp32);
-    else if (pts <= 16) LAUNCH(16);
-    else if (pts <= 24) LAUNCH(24);
-    else if (pts <= 32) LAUNCH(32);
-    else LAUNCH(48);
-#undef LAUNCH
-    return hipGetLastError();
-  }
+  if (c->fft_rg) return fft_r2c_rg<false>(c, (const float*)G, nseq, Gh, 0.0, st);
   const int R = fft_rings_per_block(c);
   const size_t blocks = nseq * ((c->ntheta + R - 1) / R);
   const size_t lds = (size_t)R * 2 * c->fft.K * 2 * real_bytes(c);
