@@ -7,7 +7,7 @@
 // The products run on the FP64 matrix cores (v_mfma_f64_16x16x4_f64: lane l holds
 // A[l % 16][l / 16] and B[l / 16][l % 16], accumulator register r is
 // D[4 r + l / 16][l % 16], checked on the device).  The sample covariance and the Cholesky's trailing update
-// are one lower-triangle tile kernel (64 x 64 tiles, four waves of 32 x 32, 16 k per
+// are one lower-triangle tile kernel (128 x 64 tiles, four waves of 64 x 32, 16 k per
 // LDS stage).  The Cholesky is right-looking with 64-wide panels: the diagonal block is
 // factored in LDS by one workgroup, which also inverts it (W = L_kk^-1, kept in the
 // block's unused upper triangle); the panel is then the product A_panel W^T on the matrix
@@ -24,122 +24,123 @@ constexpr int NB = 64;
 // blocked by 16 so that the dependent chain is 4 x 16 short steps instead of 64 long ones.
 // The block is in LDS; for each 16-column sub-block:
 //   1. wave 0 factors its 16 x 16 diagonal block D (lane r holds row r in registers; the
-//      pivot and the column of each step are broadcast by shuffles, no barrier) and inverts
-//      it (lane c forms column c of D^-1);
-//   2. the rows below it in the block become A_panel D^-T;
-//   3. the trailing rows and columns of the block are updated.
+//      pivot and the column of each step are broadcast by readlane).  Sixteen more lanes
+//      hold the rows of the identity and take the same column operations, which leaves
+//      D^-T in them: the inverse costs no step of its own;
+//   2. the 16 x 16 blocks below it become A_I D^-T, one wave each on the matrix cores;
+//   3. the trailing blocks of the lower triangle are updated, dealt to the waves.
 // Then W = L^-1 from the four inverted diagonal blocks, by block distance:
 //   W_IJ = -D_I^-1 (sum_{J <= K < I} L_IK W_KJ).
 // L goes back to the lower triangle and W's strictly lower part, transposed, to the
 // block's upper triangle (A[k0 + c][k0 + q] = W[q][c]).  Rows and columns past kb are an
 // identity block.  A non-positive pivot is recorded in flag and turns into NaN.
-constexpr int SB = 16;   // sub-block
+// Bound by the chain of 64 pivots, which the look-ahead cannot hide: with LDS shuffles, a
+// square root and a division per entry in the chain and scalar block products it took 57 us,
+// 22.6 us
+// now, 33 of them with the inverses formed by substitution.
+constexpr int SB = 16;       // sub-block
+constexpr int DS = NB + 2;   // LDS row stride: 16 rows x 2 columns of doubles fill the 64 banks
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+__device__ inline double lane_value(double v, int i) {   // lane i's v, i uniform
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, i), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), i);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// acc += X Y^T of two 16 x 16 blocks in LDS rows x0.., y0.., columns xc.., yc.. (YT: acc += X Y,
+// Y's rows y0.. being the inner index)
+template <bool YT>
+__device__ inline d4 block_product(d4 acc, const double (*X)[DS], int x0, int xc, const double (*Y)[DS], int y0, int yc,
+                                   int lane) {
+  const int l16 = lane & 15, kq = lane >> 4;
+#pragma unroll
+  for (int ks = 0; ks < SB / 4; ++ks) {
+    const int k = 4 * ks + kq;
+    const double b = YT ? Y[y0 + k][yc + l16] : Y[y0 + l16][yc + k];
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[x0 + l16][xc + k], b, acc, 0, 0, 0);
+  }
+  return acc;   // register r of lane l: row 4 r + l / 16, column l % 16
+}
 
 __global__ __launch_bounds__(256) void k_potrf_diag(int n, double* __restrict__ A, int k0, int kb, int* flag) {
-  __shared__ double a[NB][NB + 1];
-  __shared__ double Wf[NB][NB + 1];   // W = L^-1 (diagonal blocks first, then the rest)
-  __shared__ double T[NB][NB + 1];    // block products of the inverse
+  __shared__ double a[NB][DS];
+  __shared__ double Wf[NB][DS];   // W = L^-1 (diagonal blocks first, then the rest)
+  __shared__ double T[NB][DS];    // block products of the inverse
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  for (int e = t; e < NB * NB; e += 256) {
-    const int r = e / NB, c = e - r * NB;
-    const double v = A[(size_t)(k0 + min(r, kb - 1)) * n + k0 + min(c, kb - 1)];
-    a[r][c] = (r < kb && c < kb && c <= r) ? v : (c == r ? 1.0 : 0.0);
+  const int l16 = lane & 15, kq = lane >> 4;
+  double av[NB * NB / 256];
+#pragma unroll
+  for (int u = 0; u < NB * NB / 256; ++u) {
+    const int e = t + 256 * u, r = e / NB, c = e - r * NB;
+    av[u] = A[(size_t)(k0 + min(r, kb - 1)) * n + k0 + min(c, kb - 1)];
+  }
+#pragma unroll
+  for (int u = 0; u < NB * NB / 256; ++u) {
+    const int e = t + 256 * u, r = e / NB, c = e - r * NB;
+    a[r][c] = (r < kb && c < kb && c <= r) ? av[u] : (c == r ? 1.0 : 0.0);
     Wf[r][c] = 0.0;
   }
   __syncthreads();
   for (int kk = 0; kk < NB / SB; ++kk) {
     const int c0 = SB * kk;
-    if (wv == 0) {   // 1. factor and invert the 16 x 16 diagonal block (lanes 0..15 own rows)
-      const int r = lane & (SB - 1);
+    if (wv == 0) {   // 1. factor and invert the 16 x 16 diagonal block (every 16 lanes own its rows)
+      const int r = l16;
+      const bool id = lane & 16;   // lanes 16..31 (and 48..63) carry the rows of the identity along
       double d[SB];
 #pragma unroll
-      for (int c = 0; c < SB; ++c) d[c] = a[c0 + r][c0 + c];
+      for (int c = 0; c < SB; ++c) d[c] = id ? (c == r ? 1.0 : 0.0) : a[c0 + r][c0 + c];
 #pragma unroll
       for (int j = 0; j < SB; ++j) {
-        const double p = __shfl(d[j], j);
+        const double p = lane_value(d[j], j);
         const bool ok = p > 0.0;
         if (lane == 0 && !ok && c0 + j < kb) atomicCAS(flag, 0, k0 + c0 + j + 1);
-        const double sd = ok ? sqrt(p) : __builtin_nan("");
-        const double l = r > j ? d[j] / sd : (r == j ? sd : 0.0);
-        d[j] = l;
+        const double rp = ok ? 1.0 / sqrt(p) : __builtin_nan("");   // uniform
+        d[j] *= rp;   // the pivot's own lane: p / sqrt(p)
 #pragma unroll
-        for (int c = j + 1; c < SB; ++c) d[c] -= l * __shfl(l, c);   // entries past the diagonal are never read
+        for (int c = j + 1; c < SB; ++c) d[c] -= d[j] * lane_value(d[j], c);   // entries past the diagonal are never read
       }
-      if (lane < SB) {
+      // lane 16 + r holds row r of I D^-T, which is column r of D^-1.  Lane r's entries past the
+      // diagonal are no part of L and never read.
+      if (lane < 2 * SB) {
+        double* q = id ? &Wf[c0][c0 + r] : &a[c0 + r][c0];
+        const int step = id ? DS : 1;
 #pragma unroll
-        for (int c = 0; c < SB; ++c)
-          if (c <= r) a[c0 + r][c0 + c] = d[c];
-      }
-      // column c = r of D^-1: w_q = -(sum_{c <= k < q} L_qk w_k) / L_qq
-      double Ld[SB];   // this lane's row of L (for broadcasting L_qk below)
-#pragma unroll
-      for (int c = 0; c < SB; ++c) Ld[c] = d[c];
-      double w[SB];
-#pragma unroll
-      for (int q = 0; q < SB; ++q) {
-        double v = 0.0;
-#pragma unroll
-        for (int k = 0; k < q; ++k) {
-          const double lqk = __shfl(Ld[k], q);
-          v += k >= r ? lqk * w[k] : 0.0;
-        }
-        const double lqq = __shfl(Ld[q], q);
-        w[q] = q > r ? -v / lqq : (q == r ? 1.0 / lqq : 0.0);
-      }
-      if (lane < SB) {
-#pragma unroll
-        for (int q = 0; q < SB; ++q) Wf[c0 + q][c0 + r] = w[q];
+        for (int c = 0; c < SB; ++c) q[c * step] = d[c];
       }
     }
     __syncthreads();
-    // 2. panel rows below: X[i][j] = sum_{k <= j} a[i][c0 + k] W_D[j][k]
-    const int r0 = c0 + SB, nr = NB - r0;
-    double xo[3];
-    for (int u = 0; u < 3; ++u) {
-      const int e = t + 256 * u;
-      xo[u] = 0.0;
-      if (e < nr * SB) {
-        const int i = r0 + e / SB, j = e % SB;
-        double v = 0.0;
-        for (int k = 0; k <= j; ++k) v += a[i][c0 + k] * Wf[c0 + j][c0 + k];
-        xo[u] = v;
-      }
-    }
-    __syncthreads();
-    for (int u = 0; u < 3; ++u) {
-      const int e = t + 256 * u;
-      if (e < nr * SB) a[r0 + e / SB][c0 + e % SB] = xo[u];
-    }
-    __syncthreads();
-    // 3. trailing update inside the block: a[i][j] -= sum_k a[i][c0 + k] a[j][c0 + k], r0 <= j <= i
-    for (int e = t; e < nr * nr; e += 256) {
-      const int i = r0 + e / nr, j = r0 + e % nr;
-      if (j <= i) {
-        double v = 0.0;
+    // 2. blocks below: A_I <- A_I D^-T (each read and written by one wave)
+    if (const int I = kk + 1 + wv; I < NB / SB) {
+      const d4 x = block_product<false>(d4{0.0, 0.0, 0.0, 0.0}, a, SB * I, c0, Wf, c0, c0, lane);
 #pragma unroll
-        for (int k = 0; k < SB; ++k) v += a[i][c0 + k] * a[j][c0 + k];
-        a[i][j] -= v;
-      }
+      for (int r = 0; r < 4; ++r) a[SB * I + 4 * r + kq][c0 + l16] = x[r];
+    }
+    __syncthreads();
+    // 3. trailing blocks (I, J), kk < J <= I
+    const int nt = NB / SB - 1 - kk;
+    for (int e = wv; e < nt * (nt + 1) / 2; e += 4) {
+      const int i = e < 1 ? 0 : e < 3 ? 1 : 2, I = kk + 1 + i, J = kk + 1 + e - i * (i + 1) / 2;
+      const d4 x = block_product<false>(d4{0.0, 0.0, 0.0, 0.0}, a, SB * I, c0, a, SB * J, c0, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a[SB * I + 4 * r + kq][SB * J + l16] -= x[r];
     }
     __syncthreads();
   }
-  // the off-diagonal blocks of W, by block distance
+  // the off-diagonal blocks of W, by block distance: wave b forms (I, J) = (b + dist, b)
   for (int dist = 1; dist < NB / SB; ++dist) {
-    const int nbk = NB / SB - dist;   // blocks (I, J = I - dist)
-    for (int e = t; e < nbk * SB * SB; e += 256) {   // T_IJ = sum_{J <= K < I} L_IK W_KJ
-      const int b = e / (SB * SB), rc = e - b * SB * SB, I = b + dist, J = b;
-      const int i = SB * I + rc / SB, j = SB * J + rc % SB;
-      double v = 0.0;
-      for (int k = SB * J; k < SB * I; ++k) v += a[i][k] * Wf[k][j];
-      T[i][j] = v;
+    const int J = wv, I = wv + dist;
+    if (I < NB / SB) {   // T_IJ = sum_{J <= K < I} L_IK W_KJ
+      d4 x = d4{0.0, 0.0, 0.0, 0.0};
+      for (int K = J; K < I; ++K) x = block_product<true>(x, a, SB * I, SB * K, Wf, SB * K, SB * J, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) T[SB * I + 4 * r + kq][SB * J + l16] = x[r];
     }
     __syncthreads();
-    for (int e = t; e < nbk * SB * SB; e += 256) {   // W_IJ = -D_I^-1 T_IJ
-      const int b = e / (SB * SB), rc = e - b * SB * SB, I = b + dist, J = b;
-      const int i = SB * I + rc / SB, j = SB * J + rc % SB;
-      double v = 0.0;
-      for (int k = SB * I; k <= i; ++k) v += Wf[i][k] * T[k][j];
-      Wf[i][j] = -v;
+    if (I < NB / SB) {   // W_IJ = -D_I^-1 T_IJ
+      const d4 x = block_product<true>(d4{0.0, 0.0, 0.0, 0.0}, Wf, SB * I, SB * I, T, SB * I, SB * J, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Wf[SB * I + 4 * r + kq][SB * J + l16] = -x[r];
     }
     __syncthreads();
   }
@@ -266,102 +267,173 @@ __global__ __launch_bounds__(256) void k_dots(int n, const double* __restrict__ 
   if (threadIdx.x == 0) out[blockIdx.x] = red[0];
 }
 
-typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));   // rows of odd length: 8-byte aligned
 constexpr int TK = 16;     // k per LDS stage of the matrix-core update kernel
+constexpr int TR = 128;    // rows per tile
+constexpr int TC = 64;     // columns per tile
 
-// Lower-triangle tile update on the matrix cores, tile (bi, bj), bi >= bj:
-//   C[i][j] = alpha sum_k P(i, k) P(j, k) (+ C[i][j] when ACCUM),
-// with P(i, k) = X[k][i] (COLS: rows of X [K][n] are the samples) or
-// P(i, k) = X[(r0 + i) ld + k] (rows of a panel).  Rows and columns start at r0 for C.
-// MIRROR: the upper triangle gets the same values (a symmetric result).
-template <int TT, bool COLS, bool ACCUM, bool MIRROR>
-__global__ __launch_bounds__(256) void k_tile_update(int n, int K, int r0, const double* __restrict__ X, int ld,
-                                                     double alpha, double* __restrict__ C) {
-  constexpr int WT = TT / 2, MT = WT / 16;   // wave tile, 16 x 16 MFMA tiles per wave side
-  constexpr int NL = TK * TT / 256;           // staged values per thread and operand
-  const int bi = blockIdx.y, bj = blockIdx.x;
-  if (bj > bi) return;   // whole workgroup, before any barrier
-  const int i0 = r0 + bi * TT, j0 = r0 + bj * TT;
+// Lower-triangle tile update on the matrix cores, tile (bi, bj) of 128 x 64, j0 <= i0 + 127:
+//   C[i][j] = alpha sum_k P(i, k) P(j, k)                 (COLS: P(i, k) = X[k][i], rows of X
+//                                                          [K][n] are the samples), or
+//   C[i][j] -= sum_k P(i, k) P(j, k)                      (P(i, k) = X[(r0 + i) ld + k], a panel;
+//                                                          the old values start the sums).
+// Rows and columns start at r0 for C.  MIRROR: the upper triangle gets the same values (a
+// symmetric result), transposed through LDS.  Four waves of 64 x 32; a wave wholly above the
+// diagonal only stages.  COLS numbers the lower triangle's tiles alone (row bi has 2 (bi + 1)), so
+// that the workgroups which leave at once are not dealt unevenly over the chip.  LDS: k-major rows of COLS 16 doubles past a multiple of 64 words, so
+// that two k of 16 rows fill the banks; row-major of 18 doubles for a panel, the same.
+// Bound by the matrix cores and by the staging's L2 reads (10.7 flop per byte; 64 x 64 tiles
+// had 8).  6000 x 4960 samples: 4.93 ms with 64 x 64 tiles and two-way bank conflicts, 3.35 ms
+// (44 TFLOP/s of the triangle's flops) now, 3.64 with the triangle cut out of a square grid.
+template <bool COLS, bool MIRROR>
+__global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, const double* __restrict__ X, int ld,
+                                                        double alpha, double* __restrict__ C) {
+  int bi = blockIdx.y, bj = blockIdx.x;
+  if (COLS) {
+    const int t = blockIdx.x;
+    bi = (int)((sqrtf(1.0f + 4.0f * t) - 1.0f) * 0.5f);
+    while (bi * (bi + 1) > t) --bi;
+    while ((bi + 1) * (bi + 2) <= t) ++bi;
+    bj = t - bi * (bi + 1);
+  }
+  const int i0 = r0 + bi * TR, j0 = r0 + bj * TC;
+  if (j0 > i0 + TR - 1 || i0 >= n || j0 >= n) return;   // whole workgroup, before any barrier
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
   const int wr = wv >> 1, wc = wv & 1, l16 = lane & 15, kq = lane >> 4;
-  __shared__ double Pi[TK][TT + 1];
-  __shared__ double Pj[TK][TT + 1];
-  // this thread's outputs; with ACCUM their old values are loaded first and stay in flight
-  // through the contraction (indices clamped, the loads unconditional)
-  double cold[MT][MT][4];
+  const int iw = i0 + 64 * wr, jw = j0 + 32 * wc;         // the wave's first row and column
+  const bool live = jw <= iw + 63 && iw < n && jw < n;    // uniform
+  constexpr int SI = COLS ? TR + 16 : TK + 2, SJ = COLS ? TC + 16 : TK + 2;   // row strides
+  constexpr int NI = COLS ? TK : TR, NJ = COLS ? TK : TC;                     // LDS rows
+  constexpr int TS = 17;                                                      // mirror staging row
+  constexpr size_t kBytes = sizeof(double) * (NI * SI + NJ * SJ), kMir = MIRROR ? sizeof(double) * 4 * 32 * TS : 0;
+  __shared__ __attribute__((aligned(16))) unsigned char raw[kBytes > kMir ? kBytes : kMir];
+  double(*Pi)[SI] = reinterpret_cast<double(*)[SI]>(raw);
+  double(*Pj)[SJ] = reinterpret_cast<double(*)[SJ]>(raw + sizeof(double) * NI * SI);
+  // acc starts from -C (panel update) or 0
+  d4 acc[4][2];
 #pragma unroll
-  for (int ta = 0; ta < MT; ++ta)
+  for (int ta = 0; ta < 4; ++ta)
 #pragma unroll
-    for (int tb = 0; tb < MT; ++tb)
+    for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = min(i0 + WT * wr + 16 * ta + 4 * r + kq, n - 1), j = min(j0 + WT * wc + 16 * tb + l16, n - 1);
-        cold[ta][tb][r] = ACCUM ? C[(size_t)i * n + j] : 0.0;
+        const int i = min(iw + 16 * ta + 4 * r + kq, n - 1), j = min(jw + 16 * tb + l16, n - 1);
+        acc[ta][tb][r] = COLS ? 0.0 : -C[(size_t)i * n + j];
       }
-  d4 acc[MT][MT];
-#pragma unroll
-  for (int a = 0; a < MT; ++a)
-#pragma unroll
-    for (int b = 0; b < MT; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
-  // the next stage's operands are loaded into registers while this stage multiplies
-  double pi[NL], pj[NL];
+  // The next stage's operands are loaded, two doubles at a time, while this stage multiplies.
+  // COLS: 16 k x 64 pairs of rows and 16 k x 32 of columns; panel: rows of 8 pairs of k.
+  constexpr int LI = TR * TK / 512, LJ = TC * TK / 512;
+  d2 pi[LI], pj[LJ];
+  const bool inside = i0 + TR <= n && j0 + TC <= n;   // every row and column of the tile exists
+  auto at = [&](int idx, int base, int k) {   // pair idx of a stage: (k, column pair) or (row, k pair)
+    d2 v;
+    if (COLS) {
+      const double* row = X + (size_t)min(k, K - 1) * ld;
+      v.x = row[min(base + idx, n - 1)];
+      v.y = row[min(base + idx + 1, n - 1)];
+      if (k >= K) v = d2{0.0, 0.0};
+    } else {
+      const double* row = X + (size_t)min(base + idx, n - 1) * ld;
+      v.x = k < K ? row[min(k, K - 1)] : 0.0;
+      v.y = k + 1 < K ? row[min(k + 1, K - 1)] : 0.0;
+    }
+    return v;
+  };
   auto load = [&](int k0) {
+    if (inside && k0 + TK <= K) {   // uniform
 #pragma unroll
-    for (int u = 0; u < NL; ++u) {
-      const int e = tid + 256 * u;
-      int kk, c;
-      if (COLS) { kk = e / TT; c = e - kk * TT; }   // consecutive threads: consecutive columns of X
-      else { c = e / TK; kk = e - c * TK; }          // consecutive threads: consecutive k of a row
-      const int k = k0 + kk, kc = min(k, K - 1), ic = min(i0 + c, n - 1), jc = min(j0 + c, n - 1);
-      const double vi = COLS ? X[(size_t)kc * ld + ic] : X[(size_t)ic * ld + kc];
-      const double vj = COLS ? X[(size_t)kc * ld + jc] : X[(size_t)jc * ld + kc];
-      pi[u] = (k < K && i0 + c < n) ? vi : 0.0;
-      pj[u] = (k < K && j0 + c < n) ? vj : 0.0;
+      for (int u = 0; u < LI; ++u) {
+        const int e = tid + 256 * u;
+        pi[u] = COLS ? *reinterpret_cast<const d2*>(X + (size_t)(k0 + e / (TR / 2)) * ld + i0 + 2 * (e % (TR / 2)))
+                     : *reinterpret_cast<const d2*>(X + (size_t)(i0 + e / (TK / 2)) * ld + k0 + 2 * (e % (TK / 2)));
+      }
+#pragma unroll
+      for (int u = 0; u < LJ; ++u) {
+        const int e = tid + 256 * u;
+        pj[u] = COLS ? *reinterpret_cast<const d2*>(X + (size_t)(k0 + e / (TC / 2)) * ld + j0 + 2 * (e % (TC / 2)))
+                     : *reinterpret_cast<const d2*>(X + (size_t)(j0 + e / (TK / 2)) * ld + k0 + 2 * (e % (TK / 2)));
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < LI; ++u) {
+        const int e = tid + 256 * u;
+        pi[u] = COLS ? at(2 * (e % (TR / 2)), i0, k0 + e / (TR / 2)) : at(e / (TK / 2), i0, k0 + 2 * (e % (TK / 2)));
+      }
+#pragma unroll
+      for (int u = 0; u < LJ; ++u) {
+        const int e = tid + 256 * u;
+        pj[u] = COLS ? at(2 * (e % (TC / 2)), j0, k0 + e / (TC / 2)) : at(e / (TK / 2), j0, k0 + 2 * (e % (TK / 2)));
+      }
     }
   };
   load(0);
   for (int k0 = 0; k0 < K; k0 += TK) {
 #pragma unroll
-    for (int u = 0; u < NL; ++u) {
+    for (int u = 0; u < LI; ++u) {
       const int e = tid + 256 * u;
-      int kk, c;
-      if (COLS) { kk = e / TT; c = e - kk * TT; }
-      else { c = e / TK; kk = e - c * TK; }
-      Pi[kk][c] = pi[u];
-      Pj[kk][c] = pj[u];
+      constexpr int W = COLS ? TR / 2 : TK / 2;
+      *reinterpret_cast<d2*>(&Pi[e / W][2 * (e % W)]) = pi[u];
+    }
+#pragma unroll
+    for (int u = 0; u < LJ; ++u) {
+      const int e = tid + 256 * u;
+      constexpr int W = COLS ? TC / 2 : TK / 2;
+      *reinterpret_cast<d2*>(&Pj[e / W][2 * (e % W)]) = pj[u];
     }
     __syncthreads();
     if (k0 + TK < K) load(k0 + TK);
+    if (live) {
 #pragma unroll
-    for (int ks = 0; ks < TK / 4; ++ks) {
-      const int kk = 4 * ks + kq;
-      double a[MT], b[MT];
+      for (int ks = 0; ks < TK / 4; ++ks) {
+        const int kk = 4 * ks + kq;
+        double a[4], b[2];
 #pragma unroll
-      for (int t = 0; t < MT; ++t) {
-        a[t] = Pi[kk][WT * wr + 16 * t + l16];
-        b[t] = Pj[kk][WT * wc + 16 * t + l16];
+        for (int t = 0; t < 4; ++t) {
+          const int r = 64 * wr + 16 * t + l16;
+          a[t] = COLS ? Pi[kk][r] : Pi[r][kk];
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int c = 32 * wc + 16 * t + l16;
+          b[t] = COLS ? Pj[kk][c] : Pj[c][kk];
+        }
+#pragma unroll
+        for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+          for (int tb = 0; tb < 2; ++tb) acc[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
       }
-#pragma unroll
-      for (int ta = 0; ta < MT; ++ta)
-#pragma unroll
-        for (int tb = 0; tb < MT; ++tb)
-          acc[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int ta = 0; ta < MT; ++ta)
+  for (int ta = 0; ta < 4; ++ta)
 #pragma unroll
-    for (int tb = 0; tb < MT; ++tb)
+    for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = i0 + WT * wr + 16 * ta + 4 * r + kq, j = j0 + WT * wc + 16 * tb + l16;
-        if (i < n && j < n && j <= i) {
-          const double v = cold[ta][tb][r] + alpha * acc[ta][tb][r];
-          C[(size_t)i * n + j] = v;
-          if (MIRROR && j < i) C[(size_t)j * n + i] = v;
-        }
+        const int i = iw + 16 * ta + 4 * r + kq, j = jw + 16 * tb + l16;
+        acc[ta][tb][r] = COLS ? alpha * acc[ta][tb][r] : -acc[ta][tb][r];
+        if (live && i < n && j <= i) C[(size_t)i * n + j] = acc[ta][tb][r];
       }
+  if constexpr (MIRROR) {   // 16 rows x 32 columns at a time: row j of the upper triangle, 16 consecutive i
+    double(*tr)[TS] = reinterpret_cast<double(*)[TS]>(raw) + 32 * wv;
+    for (int ta = 0; ta < 4; ++ta) {
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tr[16 * tb + l16][4 * r + kq] = ta == 0   ? acc[0][tb][r]
+                                                                  : ta == 1 ? acc[1][tb][r]
+                                                                  : ta == 2 ? acc[2][tb][r]
+                                                                            : acc[3][tb][r];
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int j = jw + 4 * u + kq, i = iw + 16 * ta + l16;
+        if (live && i < n && j < i) C[(size_t)j * n + i] = tr[4 * u + kq][l16];
+      }
+      __syncthreads();
+    }
+  }
 }
 
 // Panel: rows i >= k0 + kb, A[i, k0:k0+kb] <- A[i, k0:k0+kb] W^T with W = L_kk^-1, whose
@@ -444,9 +516,8 @@ hipError_t launch_center_rows(int n, int N, const double* B, double* C, hipStrea
 }
 
 hipError_t launch_syrk(int n, int N, const double* B, double scale, double* Z, hipStream_t st) {
-  constexpr int T = 64;
-  const int nb = (n + T - 1) / T;
-  hipLaunchKernelGGL((k_tile_update<T, true, false, true>), dim3(nb, nb), dim3(256), 0, st, n, N, 0, B, n, scale, Z);
+  const int nb = (n + TR - 1) / TR;
+  hipLaunchKernelGGL((k_tile_update<true, true>), dim3(nb * (nb + 1)), dim3(256), 0, st, n, N, 0, B, n, scale, Z);
   return hipGetLastError();
 }
 
@@ -458,13 +529,12 @@ hipError_t launch_copy_lower(int n, const double* src, double* dst, hipStream_t 
 
 hipError_t launch_cholesky_lookahead(int n, double* A, int* flag, hipStream_t st, hipStream_t side, hipEvent_t ev_a,
                                      hipEvent_t ev_p, int nrhs, double* B, double* Y) {
-  constexpr int T = 64;
+  constexpr int T = TC;
   // A[i][j] -= sum_c A[i][k0 + c] A[j][k0 + c], i >= j >= r0, tile columns [bj0, ...) of the
   // (n - r0)-square trailing grid; nbx tile columns
   auto update = [&](int k0, int kb, int r0, int nbx, hipStream_t s) {
-    const int nb = (n - r0 + T - 1) / T;
-    hipLaunchKernelGGL((k_tile_update<T, false, true, false>), dim3(nbx, nb), dim3(256), 0, s, n, kb, r0, A + k0, n,
-                       -1.0, A);
+    hipLaunchKernelGGL((k_tile_update<false, false>), dim3(nbx, (n - r0 + TR - 1) / TR), dim3(256), 0, s, n, kb, r0, A + k0,
+                       n, -1.0, A);
   };
   // Factor the block column [k, k + 2 NB) (its two NB-wide halves), all updates from the
   // columns left of k applied: diagonal block and panel of the first half, its update of the

@@ -138,3 +138,50 @@ def test_ring_transform_edges(lmax, ntheta, nphi):
     g = c.beta_vjp(a, cot).cpu().numpy()[0]
     gref = om.vjp(a[0], case.cl, case.q, case.grid, None, cot[0])[0]
     assert np.linalg.norm(g - gref) <= 1e-5 * np.linalg.norm(gref)
+
+
+# FP64 linear algebra: n = P (P + 1) (P + 2) / 6 modes that end inside a 16-block, a 64 or 128 tile
+# (35, 165), on none of them (4, 1), odd and even row lengths, one block column and several,
+# sample counts on both sides of a 16-sample stage.  Tolerances: sums of N products agree to
+# N eps of their absolute sum; the estimator to the condition number (below 100 here) times n eps.
+@pytest.mark.parametrize("P,N", [(1, 1), (2, 17), (5, 33), (8, 16), (9, 165), (10, 250), (11, 40)])
+@pytest.mark.parametrize("centered", [False, True])
+def test_covariance_and_cholesky_edges(P, N, centered):
+    case = Case("edge", 4, 6, 12, P, 1, "wmap", 73)
+    c = _ctx(case, "f64")
+    n = P * (P + 1) * (P + 2) // 6
+    print(f"[case] linalg n={n} N={N} centered={centered}", flush=True)
+    rng = np.random.default_rng(100 * P + N)
+    b = rng.standard_normal((N, n)) + 0.5
+    if not centered or N > 1:
+        Z = c.covariance_sample(b, centered=centered).cpu().numpy()
+        d = b - b.mean(0) if centered else b
+        scale = 6.0 * (N - 1 if centered else N)
+        bound = 4 * N * np.finfo(float).eps * (np.abs(d).T @ np.abs(d)) / scale
+        if centered:
+            bound += 4 * N * np.finfo(float).eps * np.abs(b).max() ** 2
+        assert np.all(np.abs(Z - d.T @ d / scale) <= bound)
+        assert np.array_equal(Z, Z.T)
+    A = np.eye(n) + b.T @ b / (n + N)
+    assert np.linalg.cond(A) < 100
+    alpha, beta = rng.standard_normal(n), rng.standard_normal((3, n))
+    E, s2, Lg = c.fnl(A, alpha, beta, want_L=True)
+    ref = np.linalg.cholesky(A)
+    tol = 100 * n * np.finfo(float).eps
+    assert np.linalg.norm(Lg.cpu().numpy() - ref) <= tol * np.linalg.norm(ref)
+    y = np.linalg.solve(A, alpha)
+    assert abs(s2 * (alpha @ y) - 6.0) <= 6.0 * tol
+    assert np.abs(E - beta @ y / (alpha @ y)).max() <= tol * np.abs(beta).sum(1).max()
+
+
+# The first pivot that fails, wherever it lies in its 16-row block and its 64-row panel.
+@pytest.mark.parametrize("bad", [0, 15, 16, 63, 64, 130, 164])
+def test_cholesky_reports_first_bad_pivot(bad):
+    from paper_1105_2791_amd import ModalError
+    c = _ctx(Case("edge", 4, 6, 12, 9, 1, "wmap", 73), "f64")
+    A = np.eye(165) * 2.0
+    A[bad, bad] = -1.0
+    if bad < 164:
+        A[164, 164] = 0.0
+    with pytest.raises(ModalError, match=rf"pivot {bad}\b"):
+        c.fnl(A, np.ones(165), np.ones((1, 165)))
