@@ -114,6 +114,16 @@ __host__ __device__ inline size_t f_index(int seq, int ring, int m, int lmax, in
 // the compiler from moving memory operations across it.
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Order of a wave's own LDS accesses where its lanes exchange data with no barrier: they
+// complete in program order, and this keeps that order in the program.  No access moves over it
+// and no branch on the lane is carried over (where the last round of a ring transform's pass has
+// idle lanes, the compiler otherwise may run the next pass's reads of those lanes before the
+// other lanes' writes).
+__device__ inline void wave_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // helpers
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 inline bool is_f64(const modal_ctx* c) { return c->prec == MODAL_F64; }

@@ -407,16 +407,6 @@ __device__ inline void dft_plus(float2* x) {
   }
 }
 
-// A wave's passes exchange points through its LDS buffer with no barrier: its LDS accesses
-// complete in program order.  This keeps the order in the program: between the reads and the
-// writes of a pass, and between passes, no access moves and no branch on the lane is carried
-// over (where the last round of a pass has idle lanes, the compiler otherwise may run the next
-// pass's reads of those lanes before the other lanes' writes).
-__device__ inline void wave_order() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // one Stockham pass of radix R over the ring buffer b (length K); twp is this pass's
 // twiddle table, twp[(q - 1) Ns + k] = e^{2 pi i q k / (Ns R)}, laid out so that the
 // lanes of a wave (consecutive k) read consecutive entries

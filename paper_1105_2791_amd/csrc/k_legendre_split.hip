@@ -15,13 +15,24 @@
 //     at l-index 8 (l / 32) + i: lanes 0-31 keep their first 8 indices, lanes 32-63
 //     their last 8, and one v_permlane32_swap per register hands the other halves
 //     across, so lambda never goes through LDS;
-//   * the workgroup stages the coefficient tile (hi/lo, padded rows) in LDS;
+//   * the workgroup stages the coefficient tile (hi/lo, padded rows) in LDS, two tiles in turn
+//     (one barrier per chunk), Re and Im of a pair 32 rows apart;
 //   * each wave runs 2 parities x 2 ring tiles x 2 column tiles, accumulating
 //     2 K steps x 3 products (hi.hi + hi.lo + lo.hi; lo.lo is below the operand
 //     split error) per chunk in place: an output takes at most about 130
 //     accumulations, so the matrix core's addend truncation stays far below the split
 //     error.
-// Output goes through LDS so that F (f_index layout) is written in runs of rings.
+// A lane then holds Re and Im of four consecutive rings of a pair and stores them straight
+// into F (f_index layout).
+//
+// Bound by memory on both ends of a short loop: F's 64-byte runs (about 4.2 TB/s with the loop
+// left out) and lambda's records from L2 and HBM, which the other workgroup of the CU hides
+// only in part.  l_max 1000, 1536 rings, 640 columns (3.9 GB of F, 1.6 GB of records):
+// 2.90 ms with the next chunk's loads waited for at the head of the loop, coefficients read
+// 16 per lane (a cache line per lane and load) and outputs staged through LDS, 2.57 now;
+// l_max 2000, 3008 rings, 400 columns: 11.8 -> 10.3 ms.  The order of the units (m ascending over
+// the XCDs) lets neighbouring m share DRAM pages: m from both ends in turn takes 3.04 ms,
+// non-temporal stores 3.54.  The recurrence in the kernel (no table) takes 3.7 ms.
 #include "common.h"
 
 #include <type_traits>
@@ -40,14 +51,17 @@ constexpr int LHP = LH + 8; // padded LDS row (16-bit elements)
 constexpr int NCOL = 64;    // columns per workgroup
 constexpr int NWAVE = 4;
 constexpr int RW = 64;      // rings per wave
-constexpr int SS = NCOL + 1;  // output staging row (floats)
 
-struct CoefTile {
-  uint16_t h[2][NCOL][LHP];
-  uint16_t l[2][NCOL][LHP];
+// One parity's columns: row p is pair p's Re, row 32 + p its Im.  32 words past a multiple of 64, so
+// that the writes of both parities and of pairs p and p + 4 fill the banks.
+struct CoefHalf {
+  uint16_t v[NCOL][LHP];
+  uint16_t pad[64];
 };
-constexpr size_t kStageBytes = (size_t)NWAVE * RW * SS * 4;
-constexpr size_t kLdsBytes = sizeof(CoefTile) > kStageBytes ? sizeof(CoefTile) : kStageBytes;
+struct CoefTile {
+  CoefHalf h[2], l[2];
+};
+constexpr size_t kLdsBytes = 2 * sizeof(CoefTile);
 
 __device__ inline uint32_t bf16x2_bits(float a, float b) {
   typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
@@ -118,6 +132,10 @@ __device__ inline void lambda_chunk(int l0, int m, int lmax, const uint32_t (&rr
   }
 }
 
+// keeps loads for the next iteration where they are written: without it the compiler merges
+// them with the prologue's and issues them at the head of the loop, where they are waited for
+__device__ inline void loads_stay() { asm volatile("" ::: "memory"); }
+
 constexpr int RECUR = 0, BUILD = 1, TABLE = 2;
 
 // MODE: RECUR computes lambda in the kernel; BUILD only computes it and stores the
@@ -131,7 +149,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr bool F16 = PREC == MODAL_F16X3;
   typedef typename std::conditional<F16, f16x8, bf16x8>::type vec8;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  CoefTile& C = *reinterpret_cast<CoefTile*>(lds);
   __shared__ int lmin_blk;
   __shared__ int lmax_ls_wave[NWAVE];
 
@@ -152,7 +169,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     cbk = blockIdx.x;
   }
   const int c0 = cbk * NCOL;
-  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int lrow = lane & 31, kh = lane >> 5;
   const int jring = rbk * (NWAVE * RW) + wv * RW + lane;
   // lambda records of this wave: one per chunk k (from l = m), 16 x 64 lanes x 16 bytes
@@ -189,20 +206,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[a][b][c][r] = 0.f;
 
-  // this thread's coefficient column (col, quarter q): pointers offset so that element l
-  // of the column is pa2[l] (a_{s,lm}, of which the column takes Re or Im) and pq[l]
-  // (qw_p(l)) for l = 16 q + i of a chunk starting at 0; a chunk at l0 adds l0
-  const int ccol = tid >> 2, cq = tid & 3;
-  const bool col_ok = c0 + ccol < ncols;
-  const float2* pa2;
-  const float* pq;
-  const int creim = min(c0 + ccol, ncols - 1) & 1;
-  {
-    const int sq = min(c0 + ccol, ncols - 1) >> 1;
-    const int s = sq / P, p = sq - s * P;
-    pa2 = alm + (size_t)s * nalm + off + 16 * cq - m;
-    pq = qw + (size_t)p * (lmax + 1) + 16 * cq;
+  // Coefficient loads of this thread: pairs (s, p) c0 / 2 + 8 wv + 4 half + i, i < 4, at
+  // l = l0 + 4 k + par and + 2: 32 lanes cover the chunk's 64 l of a pair in a few lines, and
+  // each lane forms whole words (two l of one parity) of the pair's Re and Im columns.
+  const int cpar = lane & 1, ck = (lane >> 1) & 15, cp0 = 8 * wv + 4 * kh;
+  int csp[4];   // kMaxP s + p
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int sq = min(c0 / 2 + cp0 + i, ncols / 2 - 1);
+    csp[i] = sq / P * kMaxP + sq % P;
   }
+  const float2* alm_m = alm + off - m;
+  float2 va[4][2];
+  float vq[4][2];
+  auto load_coef = [&](int l0n) {   // unconditional, indices clamped (values selected when staged)
+    const int la = min(l0n + 4 * ck + cpar, lmax), lb = min(l0n + 4 * ck + 2 + cpar, lmax);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int sp = csp[i];
+      if (MODE == RECUR) asm volatile("" : "+v"(sp));   // addresses formed anew: kept over the loop they spill
+      const float2* pa = alm_m + (size_t)((uint32_t)sp / kMaxP) * nalm;
+      const float* pq = qw + (uint32_t)sp % kMaxP * (lmax + 1);
+      va[i][0] = pa[la];
+      va[i][1] = pa[lb];
+      vq[i][0] = pq[la];
+      vq[i][1] = pq[lb];
+    }
+  };
 
   // chunks start at l = m + 64 k so that parity(l - m) = parity(l - l0)
   const int kfirst = (lmin > m) ? (lmin - m) / LCH : 0;
@@ -218,52 +248,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   };
   if (MODE != TABLE && m + kfirst * LCH <= lmax) load_rr(m + kfirst * LCH);
 
-  for (int l0 = m + kfirst * LCH; l0 <= lmax; l0 += LCH) {
-    uint4* trec = tab + (size_t)(rec0 + (l0 - m) / LCH) * 16 * 64 + lane;
-    if (MODE != BUILD) __syncthreads();
-    // ---- coefficient loads: thread (col, quarter) takes 16 consecutive l of one column.
-    //      All 16 pairs are unconditional (index clamped in the last chunk, value selected
-    //      after) and in flight together while the recurrence below runs.
-    const int col = ccol, q = cq;
-    float va[16], vq[16];
-    const float* pa = reinterpret_cast<const float*>(pa2) + creim;
-    if (MODE == BUILD) {
+  // lambda words [par][ks][half][k]: l-indices 16 ks + 8 half + 2 k, + 1 of the parity.  TABLE: a
+  // parity's words and the coefficients of the next chunk are loaded as soon as this chunk's
+  // products have read them, so they arrive under the other parity's products.
+  uint32_t Lh[2][2][2][4], Ll[2][2][2][4];
+  auto load_lambda = [&](int l0n, int par) {
+    // record word i: Lh (i < 8) or Ll (i >= 8) at [par][ks][half] = i % 8
+    const uint4* trec = tab + (size_t)(rec0 + (l0n - m) / LCH) * 16 * 64 + lane;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) va[i] = vq[i] = 0.f;
-    } else if (l0 + LCH - 1 <= lmax) {   // wave-uniform: one base, immediate offsets
-      const float* a = pa + 2 * l0;
-      const float* b = pq + l0;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        va[i] = a[2 * i];
-        vq[i] = b[i];
-      }
-    } else {
-      // the last chunk of an m: clamped indices, and the product is formed here (vq = 1),
-      // which also keeps this path from being merged with the one above
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int li = min(l0 + 16 * q + i, lmax) - 16 * q;
-        va[i] = pq[li] * pa[2 * li];
-        vq[i] = 1.f;
-      }
+    for (int j = 0; j < 8; ++j) {
+      const int i = (j & 4) * 2 + 4 * par + (j & 3);
+      const uint4 u = trec[i * 64];
+      uint32_t(&dst)[4] = (j < 4) ? Lh[par][(j >> 1) & 1][j & 1] : Ll[par][(j >> 1) & 1][j & 1];
+      dst[0] = u.x;
+      dst[1] = u.y;
+      dst[2] = u.z;
+      dst[3] = u.w;
     }
+  };
+  const int l0last = m + (lmax - m) / LCH * LCH;
+  if (MODE == TABLE) {
+    const int l0f = min(m + kfirst * LCH, l0last);
+    load_coef(l0f);
+    load_lambda(l0f, 0);
+    load_lambda(l0f, 1);
+    loads_stay();
+  }
 
-    // ---- lambda for this lane's ring, l0 .. l0 + 63, as hi/lo words: lw index
-    //      [par][ks][half][k] holds l-indices 16 ks + 8 half + 2 k, + 1
-    uint32_t Lh[2][2][2][4], Ll[2][2][2][4];
-    if (MODE == TABLE) {
-      // record word i: Lh (i < 8) or Ll (i >= 8) at [par][ks][half] = i % 8
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const uint4 u = trec[i * 64];
-        uint32_t(&dst)[4] = (i < 8) ? Lh[(i >> 2) & 1][(i >> 1) & 1][i & 1] : Ll[(i >> 2) & 1][(i >> 1) & 1][i & 1];
-        dst[0] = u.x;
-        dst[1] = u.y;
-        dst[2] = u.z;
-        dst[3] = u.w;
-      }
-    } else {
+  for (int l0 = m + kfirst * LCH; l0 <= lmax; l0 += LCH) {
+    const int l0n = min(l0 + LCH, l0last);
+    // two tiles in turn: a wave writes one while others still read the other, and passes the
+    // barrier below only when all have
+    CoefTile& C = reinterpret_cast<CoefTile*>(lds)[((l0 - m) / LCH) & 1];
+    if (MODE == RECUR) load_coef(l0);   // in flight while the recurrence runs
+    if (MODE != TABLE) {
       // wave-uniform: every lane is past its seeds and the chunk ends inside l <= lmax,
       // so the steps need no selects (the general form handles seeds and the tail)
       if (l0 > wls + 1 && l0 + LCH - 1 <= lmax) {
@@ -289,6 +307,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       if (l0 + LCH <= lmax) load_rr(l0 + LCH);
     }
     if (MODE == BUILD) {
+      uint4* trec = tab + (size_t)(rec0 + (l0 - m) / LCH) * 16 * 64 + lane;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const uint32_t(&w)[4] = (i < 8) ? Lh[(i >> 2) & 1][(i >> 1) & 1][i & 1] : Ll[(i >> 2) & 1][(i >> 1) & 1][i & 1];
@@ -297,35 +316,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       continue;
     }
 
-    // ---- coefficient tile: qw_p(l) Re/Im a_lm, split, stored; l = l0 + 16 q + i has
-    //      parity i & 1 and index 8 q + i / 2 (zero past lmax and for padding columns)
-    {
-      float v[16];
+    // ---- coefficient tile: qw_p(l) Re/Im a_lm, split, stored: words of l-indices 2 ck, + 1
+    //      (zero past lmax and for padding columns)
+    const bool oka = l0 + 4 * ck + cpar <= lmax, okb = l0 + 4 * ck + 2 + cpar <= lmax;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = (col_ok && l0 + 16 * q + i <= lmax) ? vq[i] * va[i] : 0.f;
-      uint32_t h[2][4], lw[2][4];
-#pragma unroll
-      for (int par = 0; par < 2; ++par)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) split2<PREC>(v[4 * k + par], v[4 * k + 2 + par], h[par][k], lw[par][k]);
-#pragma unroll
-      for (int par = 0; par < 2; ++par) {
-        *reinterpret_cast<u32x4*>(&C.h[par][col][8 * q]) = u32x4{h[par][0], h[par][1], h[par][2], h[par][3]};
-        *reinterpret_cast<u32x4*>(&C.l[par][col][8 * q]) = u32x4{lw[par][0], lw[par][1], lw[par][2], lw[par][3]};
-      }
+    for (int i = 0; i < 4; ++i) {
+      const int col = cp0 + i;   // Re; Im 32 rows on
+      const bool ok = c0 + 2 * col < ncols;
+      const float q0 = vq[i][0], q1 = vq[i][1];
+      uint32_t h, lw;
+      split2<PREC>(ok && oka ? q0 * va[i][0].x : 0.f, ok && okb ? q1 * va[i][1].x : 0.f, h, lw);
+      *reinterpret_cast<uint32_t*>(&C.h[cpar].v[col][2 * ck]) = h;
+      *reinterpret_cast<uint32_t*>(&C.l[cpar].v[col][2 * ck]) = lw;
+      split2<PREC>(ok && oka ? q0 * va[i][0].y : 0.f, ok && okb ? q1 * va[i][1].y : 0.f, h, lw);
+      *reinterpret_cast<uint32_t*>(&C.h[cpar].v[col + 32][2 * ck]) = h;
+      *reinterpret_cast<uint32_t*>(&C.l[cpar].v[col + 32][2 * ck]) = lw;
     }
     __syncthreads();
 
     // ---- MFMA: per (parity, ring tile, column tile) a chain over the 2 K steps
 #pragma unroll
-    for (int par = 0; par < 2; ++par)
+    for (int par = 0; par < 2; ++par) {
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct) {
         vec8 bh[2], bl[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-          bh[ks] = *reinterpret_cast<const vec8*>(&C.h[par][32 * ct + lrow][16 * ks + 8 * kh]);
-          bl[ks] = *reinterpret_cast<const vec8*>(&C.l[par][32 * ct + lrow][16 * ks + 8 * kh]);
+          bh[ks] = *reinterpret_cast<const vec8*>(&C.h[par].v[32 * ct + lrow][16 * ks + 8 * kh]);
+          bl[ks] = *reinterpret_cast<const vec8*>(&C.l[par].v[32 * ct + lrow][16 * ks + 8 * kh]);
         }
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
@@ -347,41 +365,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
           }
         }
       }
+      if (MODE == TABLE) {
+        if (par == 0) load_coef(l0n);
+        load_lambda(l0n, par);
+        loads_stay();
+      }
+    }
   }
 
   if (MODE == BUILD) return;
 
-  // ---- output: stage N = E + O then S = E - O through LDS, one [RW][SS] slab per wave;
-  // acc[par][rt][ct][j] is ring 32 rt + 8 (j / 4) + 4 kh + j % 4, column 32 ct + lrow
-  __syncthreads();
-  float* stg = reinterpret_cast<float*>(lds) + (size_t)wv * RW * SS;
+  // ---- output: N = E + O and S = E - O.  acc[par][rt][ct][4 g + i] is ring 32 rt + 8 g + 4 kh + i
+  // of pair lrow, Re in column tile 0 and Im in 1: a lane stores two rings at a time, its and
+  // lane + 32's four rings of a group together the group's 64 bytes.
+  if (c0 + 2 * lrow >= ncols) return;
+  const size_t ms = (size_t)(lmax + 1) * 8;   // of F, per ring group
+  float2* f = F + (size_t)((c0 >> 1) + lrow) * f_ring_blocks(ntheta) * ms + (size_t)m * 8;
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const int jb = rbk * (NWAVE * RW) + wv * RW;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const float sg = half ? -1.f : 1.f;
+  for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int g = 0; g < 4; ++g)
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-          stg[(32 * rt + 8 * (j >> 2) + 4 * kh + (j & 3)) * SS + 32 * ct + lrow] =
-              acc[0][rt][ct][j] + sg * acc[1][rt][ct][j];
-    __syncthreads();
-    if (ring_ok) {
-      const int jw = half ? ntheta - 1 - jring : jring;
-      if (!(half && jw == jring)) {
-        for (int cc = 0; cc < NCOL; cc += 2) {
-          const int cg = c0 + cc;
-          if (cg >= ncols) break;
-          float2 v;
-          v.x = stg[lane * SS + cc];
-          v.y = stg[lane * SS + cc + 1];
-          F[f_index(cg >> 1, jw, m, lmax, f_ring_blocks(ntheta))] = v;
+      for (int h = 0; h < 2; ++h) {
+        const int j = jb + 32 * rt + 8 * g + 4 * kh + 2 * h, r = 4 * g + 2 * h;
+        const float2 n0 = make_float2(acc[0][rt][0][r] + acc[1][rt][0][r], acc[0][rt][1][r] + acc[1][rt][1][r]);
+        const float2 n1 = make_float2(acc[0][rt][0][r + 1] + acc[1][rt][0][r + 1], acc[0][rt][1][r + 1] + acc[1][rt][1][r + 1]);
+        const float2 s0 = make_float2(acc[0][rt][0][r] - acc[1][rt][0][r], acc[0][rt][1][r] - acc[1][rt][1][r]);
+        const float2 s1 = make_float2(acc[0][rt][0][r + 1] - acc[1][rt][0][r + 1], acc[0][rt][1][r + 1] - acc[1][rt][1][r + 1]);
+        const int jw = ntheta - 1 - j;   // j's south ring; j + 1's is jw - 1
+        float2* fn = f + (j >> 3) * ms + (j & 7);
+        float2* fs = f + (jw >> 3) * ms + (jw & 7);
+        if (j + 1 < nrp) {
+          *reinterpret_cast<f4*>(fn) = f4{n0.x, n0.y, n1.x, n1.y};
+          if (!(ntheta & 1)) {
+            *reinterpret_cast<f4*>(fs - 1) = f4{s1.x, s1.y, s0.x, s0.y};
+          } else {
+            *fs = s0;
+            if (jw - 1 != j + 1) f[((jw - 1) >> 3) * ms + ((jw - 1) & 7)] = s1;
+          }
+        } else if (j < nrp) {
+          *fn = n0;
+          if (jw != j) *fs = s0;
         }
       }
-    }
-    __syncthreads();
-  }
 }
 
 }  // namespace

@@ -185,3 +185,25 @@ def test_cholesky_reports_first_bad_pivot(bad):
         A[164, 164] = 0.0
     with pytest.raises(ModalError, match=rf"pivot {bad}\b"):
         c.fnl(A, np.ones(165), np.ones((1, 165)))
+
+
+# Split synthesis: ring counts whose south rings are stored in pairs (even), one by one (odd, with
+# the equator ring) and with a last pair cut by the ring count (2 mod 4), one and several blocks
+# of 256 north rings, l_max on both sides of a chunk of 64 l, column blocks that are not full,
+# pairs of several skies in a block; lambda from the table and from the recurrence.
+@pytest.mark.parametrize("prec", ["bf16x3", "f16x3"])
+@pytest.mark.parametrize("table", [True, False])
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", [(3, 5, 8, 2, 1), (63, 66, 130, 5, 2), (64, 129, 136, 7, 5),
+                                                  (130, 514, 270, 3, 11), (40, 517, 90, 6, 6), (127, 128, 256, 1, 33)])
+def test_split_synthesis_edges(lmax, ntheta, nphi, P, S, table, prec):
+    from paper_1105_2791_amd import ModalContext
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 74)
+    print(f"[case] split synthesis {prec} lmax={lmax} {ntheta}x{nphi} P={P} S={S} table={table}", flush=True)
+    a = case.alms(0, S)
+    c = ModalContext(lmax, ntheta, nphi, P, prec, case.q, case.cl, mask=case.mask(), lambda_table=table)
+    out = torch.full((S, P, ntheta, nphi), float("nan"), dtype=torch.float32, device="cuda")
+    got = c.filter_maps(a, out=out).cpu().numpy()
+    ref = case.maps(a)
+    tol = 1e-4 if prec == "bf16x3" else 1e-5   # the bounds of the map tests
+    rms = np.sqrt(np.mean(ref * ref, axis=(2, 3)))
+    assert np.all(np.max(np.abs(got - ref), axis=(2, 3)) <= tol * rms)
