@@ -522,7 +522,8 @@ modal_status place_tables(modal_ctx* c, const double* q_host, const double* cl_h
   {
     const int nt = quad_ntile(c->npairs);
     for (int ti = 0; ti < nt; ++ti)
-      for (int tj = ti; tj < nt; ++tj) qtiles.push_back(make_int2(ti, tj));
+      for (int tj = ti + 1; tj < nt; ++tj) qtiles.push_back(make_int2(ti, tj));
+    for (int ti = 0; ti < nt; ++ti) qtiles.push_back(make_int2(ti, ti));
   }
 
   // exact power-of-two scales for the split-fp16 contraction: whitened maps have
@@ -1077,8 +1078,7 @@ modal_status modal_trispectrum(modal_ctx* c, const void* alm, int S, const void*
       HIPTRY(launch_quad_vtile(c, maps, c->P, S, Mt, st));
       M = Mt;
     }
-    HIPTRY(launch_quad_syrk(c, M, V, S, 0, c->t.qtiles, part, K, st));
-    if (state) HIPTRY(launch_quad_syrk(c, nullptr, V, 1, 1, c->t.qtiles, part, KVV, st));
+    HIPTRY(launch_quad_syrk(c, M, V, S, c->t.qtiles, part, K, KVV, st));
   }
   {
     StageTimer _t(c, MODAL_STAGE_REDUCE, st);

@@ -4,17 +4,22 @@
 //   K_(ab),(cd) = sum_x w A_ab A_cd - 6 sum_x w V_ab V_cd,   A_ab = M_a M_b - 3 V_ab,
 //   tau_prsu = (K_(pr),(su) + K_(ps),(ru) + K_(pu),(rs)) / 3,
 // since the three pairings of A A expand to 3 MMMM - 3 (6 pairs) V M M + 9 (3 pairings) V V.
-// Without a linear-term state V = 0.  The V V term is sky-independent and computed once
-// per call by the same kernels with A = V.
+// Without a linear-term state V = 0.  The V V term is sky-independent and formed once
+// per call as one more sky of the same launch, with A = V.
 //
 // The update is a pairs x pairs SYRK with K = pixels.  Operands sqrt(w) A are formed on
 // the fly (w >= 0 splits evenly over both sides), never stored in HBM:
-//   * float maps (bf16x3 / f16x3 / f32 contexts): split-bf16 MFMA 32x32x16 with three
-//     products, 128 x 128 output tiles, two skies per workgroup (one per half, 64 x 64
-//     per wave), operands of a 32-pixel step formed once per half into LDS (each thread
-//     4 pixels of 8 operand rows), maps and pair means read from pixel-block-major copies
+//   * float maps (bf16x3 / f16x3 contexts): split-bf16 MFMA 32x32x16 with three
+//     products, 128 x 128 output tiles, two skies per workgroup, operands of the next 32
+//     pixels formed into LDS between the products of these (each thread 4 pixels of 4
+//     operand rows of both skies), maps and pair means read from pixel-block-major copies
 //     (k_quad_vtile), FP32 chains of CH steps joined in FP32, FP32 partial sums per pixel
-//     chunk reduced in FP64;
+//     chunk reduced in FP64.  Bound by the operands' vector work (about 240 instructions per
+//     wave and step against 24 products) and the two barriers of a step; one workgroup per CU (150
+//     KB of LDS).  4 skies, 465 pairs, 1.18 M pixels, with pair means: 13.7 ms for the skies and 5.5
+//     for the means with a sky per half, operands and products in turn (three barriers, one operand
+//     buffer) and means exchanged through LDS; 9.1 ms for both in one launch with the two
+//     overlapped, 7.5 now with the longest workgroups first and a row's next means loaded in place;
 //   * double maps (f64 contexts): FP64 on the vector ALUs, 64 x 64 tiles, 4 x 4 per thread.
 #include "common.h"
 
@@ -27,22 +32,24 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
+typedef float f4 __attribute__((ext_vector_type(4)));
+
 constexpr int TT = 128;      // output tile of the MFMA kernel (rows = cols)
 constexpr int PXS = 32;      // pixels per staged step (two MFMA K = 16 steps)
-constexpr int OPS = PXS;     // operand row stride in LDS (bf16; 16-byte fragments stay aligned)
 constexpr int MPS = PXS + 4; // map row stride in LDS (floats; rows stay 16-byte aligned)
 constexpr int CH = 16;       // staged steps per MFMA accumulation chain (96 MFMAs per tile)
 constexpr int GPR = PXS / 4; // 4-pixel groups per row
-constexpr int RPT = 2 * TT * GPR / 256;   // operand rows per thread (8)
-constexpr int SKW = 2;       // skies per workgroup, one per half: the pair means are loaded once
-constexpr int NTQ = 256 * SKW;
+constexpr int NTQ = 512;     // threads
+constexpr int RPT = 2 * TT * GPR / NTQ;   // operand rows per thread (4)
+constexpr int SKW = 2;       // skies per workgroup: the pair means are loaded once for both
 
 struct TriLds {
+  // operand words, two steps in turn; rows 0..127 of tile ti, then tile tj's.  A row is four
+  // 16-byte quads, quad q at place q ^ ((row >> 2) & 3): 16 rows' reads of a quad fill the banks.
+  uint16_t oh[2][SKW][2 * TT][PXS];
+  uint16_t ol[2][SKW][2 * TT][PXS];
   float ms[SKW][kMaxP][MPS];
-  float4 vs[RPT][256];     // pair means of thread t's rows and pixels (read by t of both halves)
-  float4 sw[256];          // sqrt(w) of thread t's 4 pixels
-  uint16_t oh[SKW][2 * TT][OPS];
-  uint16_t ol[SKW][2 * TT][OPS];
+  float sw[PXS];           // sqrt(w)
 };
 
 __device__ inline uint32_t bf16_pair(float a, float b) {
@@ -60,215 +67,246 @@ __device__ inline void split2(float v0, float v1, uint32_t& hi, uint32_t& lo) {
   lo = bf16_pair(v0 - __builtin_bit_cast(float, hi << 16), v1 - __builtin_bit_cast(float, hi & 0xffff0000u));
 }
 
-// Tile pair (ti, tj), ti <= tj, of the R x R result, pixel chunk c, skies SKW z + h for the
-// two halves h of the workgroup (vmode: operands are the pair means themselves, one
-// "sky").  part[s][c][tp][TT][TT] FP32 sums of the chunk.
-// Thread t of a half forms the operands of the 4 pixels 4 (t % 8) .. + 3 of the rows
-// t / 8 + 32 j, j < 8 (rows 0..127 of tile ti, then 128..255 of tile tj): its pair-mean and
-// weight loads are float4 and coalesced along each row, its map reads and operand writes
-// are 16- and 8-byte LDS accesses.  The pair means of a step are the same for both skies:
-// half h loads the rows j = 4 h .. 4 h + 3 and both halves read all eight, so each pair
-// mean is read from HBM once per two skies.  V and the maps are pixel-block-major copies
-// made by k_quad_vtile, so the rows of a step are contiguous runs.
-__global__ __launch_bounds__(NTQ) __attribute__((amdgpu_waves_per_eu(2))) void k_quad_syrk(int P, int R, int npix, int S, int nchunk, int chunk_px, int ntp,
-                                                   const int2* __restrict__ tpairs, const int* __restrict__ pair_a,
-                                                   const int* __restrict__ pair_b, const float* __restrict__ maps,
-                                                   const float* __restrict__ V, const float* __restrict__ w,
-                                                   int vmode, int vec, float* __restrict__ part) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char traw[];
-  TriLds& L = *reinterpret_cast<TriLds*>(traw);
-  const int tp = blockIdx.x, chunk = blockIdx.y;
-  const int2 tt = tpairs[tp];
-  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-  const int h = tid >> 8, t = tid & 255;           // sky half, thread within the half
-  const int s = SKW * blockIdx.z + h;
-  const bool skyok = s < S;                        // uniform over the half's four waves
-  const int wq = wv & 3, wi = wq >> 1, wj = wq & 1;
-  const int g = t & (GPR - 1), rsub = t / GPR;
-  // this thread's operand rows r = rsub + 32 j (j < 4 in tile ti, j >= 4 in tile tj):
-  // pair index rowp(j); its two modes, 8 bits each, packed two rows to a word
-  const int rb0 = tt.x * TT + rsub, rb1 = tt.y * TT + rsub - TT;
-  auto rowp = [&](int j) { return (j < RPT / 2 ? rb0 : rb1) + 32 * j; };
-  uint32_t pab[RPT / 2] = {};
-  unsigned rokm = 0;
+// One chunk of one tile pair (ti, tj), ti <= tj, for NSK skies s0, s0 + 1 (index S: the pair means
+// themselves, A = V, formed as 0 * 0 + 1 * V): part[s][c][tp][TT][TT], the FP32 sums of the chunk.
+//   * thread t forms the operands of the 4 pixels 4 (t % 8) .. + 3 of the rows t / 8 + 64 j,
+//     j < 4 (j < 2 in tile ti), for both skies: it loads the pair means it needs straight to
+//     registers, a step ahead, and reads the maps from LDS (staged a step ahead too);
+//   * NSK 2: waves 0..3 multiply for sky s0 and waves 4..7 for s0 + 1, 64 x 64 each; NSK 1: all
+//     eight for s0, 64 x 32 each;
+//   * the operands of step k + 1 are formed between the products of step k (operand words in
+//     two buffers): a group is one row and sky's words (its maps read a group ahead) and its
+//     share of the products; a row's next pair means are loaded when its last sky has used them.
+// DIAG: ti == tj, tile tj's operands are tile ti's and half the rows are formed.
+// Rows past R compute on row R - 1's data (their outputs are not read); pixels past npix are
+// zero in the block-major copies.
+template <int NSK, bool DIAG, bool STATE>
+__device__ __forceinline__ void quad_chunk(TriLds& L, int P, int R, int npix, int S, int s0, int2 tt, int x0, int x1,
+                                           const int* __restrict__ pair_a, const int* __restrict__ pair_b,
+                                           const float* __restrict__ maps, const float* __restrict__ V,
+                                           const float* __restrict__ w, float* __restrict__ dst, size_t dst_sky) {
+  constexpr int NB = NSK;                     // 32-column tiles per wave
+  constexpr int NR = DIAG ? RPT / 2 : RPT;    // rows formed per thread
+  constexpr int NG = NR * NSK, NP = 12 * NB;  // groups and products per step
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int h = wv >> 2, wi = (wv >> 1) & 1, wj = wv & 1;
+  const int g = tid & (GPR - 1), rsub = tid / GPR;
+  const int nblk = (npix + PXS - 1) / PXS, xb = x0 / PXS, n = (x1 - x0 + PXS - 1) / PXS;
+  // operand rows: offsets of the two modes' maps in LDS (bytes, 16 bits each) and of V's row
+  uint32_t mo[NR], vo[NR];
 #pragma unroll
-  for (int j = 0; j < RPT; ++j) {
-    const int orow = rowp(j);
-    const bool ok = orow < R;
-    const uint32_t ab = ok ? (uint32_t)(pair_a[orow] | (pair_b[orow] << 8)) : 0u;
-    pab[j >> 1] |= ab << (16 * (j & 1));
-    rokm |= ok ? (1u << j) : 0u;
+  for (int j = 0; j < NR; ++j) {
+    const int row = min((j < RPT / 2 ? tt.x : tt.y) * TT + rsub + 64 * (j & 1), R - 1);
+    mo[j] = (uint32_t)(pair_a[row] * MPS + 4 * g) * 4 | (uint32_t)(pair_b[row] * MPS + 4 * g) * 4 << 16;
+    vo[j] = (uint32_t)(row * PXS + 4 * g);
   }
-  const bool hasV = V != nullptr;   // no state: V = 0 (never read); vmode always has V
-  const int nblk = (npix + PXS - 1) / PXS;
-  const float* Msky = maps + (size_t)min(s, S - 1) * nblk * P * PXS;   // block-major copy of the maps
-  const int x0 = chunk * chunk_px, x1 = min(npix, x0 + chunk_px);
+  // map groups this thread stages: at most SKW kMaxP GPR / NTQ = 2
+  constexpr int NML = (NSK * kMaxP * GPR + NTQ - 1) / NTQ;
+  const float* mp[NML];
+  f4* md[NML];
+  bool mok[NML];
+  const int nmg = NSK * P * GPR;
+#pragma unroll
+  for (int q = 0; q < NML; ++q) {
+    const int e = min(tid + NTQ * q, nmg - 1), k = e / (P * GPR), r = (e - k * P * GPR) / GPR, gg = e % GPR;
+    mok[q] = s0 + k < S;
+    mp[q] = maps + ((size_t)min(s0 + k, S - 1) * nblk + xb) * P * PXS + r * PXS + 4 * gg;
+    md[q] = reinterpret_cast<f4*>(&L.ms[k][r][4 * gg]);
+  }
+  float cv[NSK];   // A = M_a M_b + cv V
+#pragma unroll
+  for (int k = 0; k < NSK; ++k) cv[k] = s0 + k < S ? -3.f : 1.f;
 
-  f32x16 acc[2][2], cha[2][2];
+  f4 pm[NML], pv[NR];
+  float pw;
+  auto load_maps = [&](int k) {   // steps past the chunk repeat its last
+    const size_t o = (size_t)min(k, n - 1) * P * PXS;
+#pragma unroll
+    for (int q = 0; q < NML; ++q) pm[q] = *reinterpret_cast<const f4*>(mp[q] + o);
+    pw = w[min(x0 + min(k, n - 1) * PXS + (tid & (PXS - 1)), npix - 1)];
+  };
+  auto load_mean = [&](int j, int k) {
+    if (STATE) pv[j] = *reinterpret_cast<const f4*>(V + (size_t)(xb + min(k, n - 1)) * R * PXS + vo[j]);
+  };
+  auto stage_maps = [&]() {
+#pragma unroll
+    for (int q = 0; q < NML; ++q) {
+      const f4 z = {0.f, 0.f, 0.f, 0.f};
+      *md[q] = mok[q] ? pm[q] : z;
+    }
+    if (tid < PXS) L.sw[tid] = sqrtf(pw);
+  };
+  // operand words of row j, sky k into buffer b; the maps read beforehand
+  const int wo = rsub * PXS + (((g >> 1) ^ ((rsub >> 2) & 3)) << 3) + 4 * (g & 1);
+  auto form = [&](int j, int k, int b, const f4 ma, const f4 mb, const f4 sq) {
+    const float c = cv[k];
+    f4 v;
+    if (STATE) {
+      v.x = fmaf(ma.x, mb.x, c * pv[j].x) * sq.x;
+      v.y = fmaf(ma.y, mb.y, c * pv[j].y) * sq.y;
+      v.z = fmaf(ma.z, mb.z, c * pv[j].z) * sq.z;
+      v.w = fmaf(ma.w, mb.w, c * pv[j].w) * sq.w;
+    } else {
+      v.x = ma.x * mb.x * sq.x;
+      v.y = ma.y * mb.y * sq.y;
+      v.z = ma.z * mb.z * sq.z;
+      v.w = ma.w * mb.w * sq.w;
+    }
+    uint32_t h0, l0, h1, l1;
+    split2(v.x, v.y, h0, l0);
+    split2(v.z, v.w, h1, l1);
+    *reinterpret_cast<uint2*>(&L.oh[b][k][64 * j][0] + wo) = make_uint2(h0, h1);
+    *reinterpret_cast<uint2*>(&L.ol[b][k][64 * j][0] + wo) = make_uint2(l0, l1);
+  };
+  auto map_at = [&](int k, uint32_t o) {
+    return *reinterpret_cast<const f4*>(reinterpret_cast<const unsigned char*>(&L.ms[k][0][0]) + o);
+  };
+
+  f32x16 acc[2][NB], cha[2][NB];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = cha[a][b][r] = 0.f;
-  int link = 0;
-  // Staging in 4-pixel groups (float4; npix % 4 == 0 and 32-pixel chunk starts keep a
-  // group wholly inside or wholly past the chunk end).  The next step's loads are issued
-  // into registers before this step's operand formation and MFMAs, so their latency is
-  // hidden behind that work.
-  constexpr int NML = (kMaxP * GPR + 255) / 256;        // map groups per thread (2)
-  constexpr int RPH = RPT / SKW;                        // pair-mean rows loaded per thread (4)
-  float4 pv[RPH], pm[NML], pw;
-  auto load_step = [&](int xs) {
+
+  // step 0's operands
+  load_maps(0);
 #pragma unroll
-    for (int k = 0; k < NML; ++k) {
-      const int e = t + 256 * k, r = e / GPR, gg = e - r * GPR, x = xs + 4 * gg;
-      pm[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (!vmode && skyok && r < P && x < x1)
-        pm[k] = *reinterpret_cast<const float4*>(Msky + ((size_t)(x >> 5) * P + r) * PXS + (x & 31));
-    }
-    const int x = xs + 4 * g;
+  for (int j = 0; j < NR; ++j) load_mean(j, 0);
+  stage_maps();
+  load_maps(1);
+  __syncthreads();
+  {
+    const f4 sq = *reinterpret_cast<const f4*>(&L.sw[4 * g]);
 #pragma unroll
-    for (int jj = 0; jj < RPH; ++jj) {
-      const int j = RPH * h + jj;
-      pv[jj] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (hasV && x < x1 && ((rokm >> j) & 1u))
-        pv[jj] = *reinterpret_cast<const float4*>(V + ((size_t)(x >> 5) * R + rowp(j)) * PXS + (x & 31));
-    }
-    pw = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (h == 0 && x < x1) pw = *reinterpret_cast<const float4*>(w + x);
-  };
-  auto store_step = [&]() {
+    for (int j = 0; j < NR; ++j) {
 #pragma unroll
-    for (int k = 0; k < NML; ++k) {
-      const int e = t + 256 * k, r = e / GPR, gg = e - r * GPR;
-      if (r < kMaxP) *reinterpret_cast<float4*>(&L.ms[h][r][4 * gg]) = pm[k];
-    }
-#pragma unroll
-    for (int jj = 0; jj < RPH; ++jj) L.vs[RPH * h + jj][t] = pv[jj];
-    if (h == 0) L.sw[t] = make_float4(sqrtf(pw.x), sqrtf(pw.y), sqrtf(pw.z), sqrtf(pw.w));
-  };
-  // element-wise staging (npix % 4 != 0): the same layout, scalar loads
-  auto stage_scalar = [&](int xs) {
-    if (!vmode)
-      for (int e = t; e < P * PXS; e += 256) {
-        const int r = e / PXS, i = e - r * PXS, x = xs + i;
-        L.ms[h][r][i] = (skyok && x < x1) ? Msky[((size_t)(x >> 5) * P + r) * PXS + (x & 31)] : 0.f;
-      }
-    float q[4], sq[4];
-#pragma unroll
-    for (int jj = 0; jj < RPH; ++jj) {
-      const int j = RPH * h + jj;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int x = xs + 4 * g + k;
-        q[k] = (hasV && x < x1 && ((rokm >> j) & 1u)) ? V[((size_t)(x >> 5) * R + rowp(j)) * PXS + (x & 31)] : 0.f;
-      }
-      L.vs[j][t] = make_float4(q[0], q[1], q[2], q[3]);
-    }
-    if (h == 0) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int x = xs + 4 * g + k;
-        sq[k] = x < x1 ? sqrtf(w[x]) : 0.f;
-      }
-      L.sw[t] = make_float4(sq[0], sq[1], sq[2], sq[3]);
-    }
-  };
-  if (vec) load_step(x0);
-  for (int xs = x0; xs < x1; xs += PXS) {
-    __syncthreads();
-    if (vec) store_step();
-    else stage_scalar(xs);
-    __syncthreads();
-    if (vec && xs + PXS < x1) load_step(xs + PXS);
-    // operands sqrt(w) (M_a M_b - 3 V_ab), or sqrt(w) V_ab, split hi/lo, 4 pixels x 8 rows
-    if (skyok) {
-      const float4 sq = L.sw[t];
-#pragma unroll
-      for (int j = 0; j < RPT; ++j) {
-        const int r = rsub + 32 * j;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if ((rokm >> j) & 1u) {
-          const float4 vv = hasV ? L.vs[j][t] : make_float4(0.f, 0.f, 0.f, 0.f);
-          if (vmode) {
-            v = vv;
-          } else {
-            const uint32_t ab = pab[j >> 1] >> (16 * (j & 1));
-            const float4 ma = *reinterpret_cast<const float4*>(&L.ms[h][ab & 0xff][4 * g]);
-            const float4 mb = *reinterpret_cast<const float4*>(&L.ms[h][(ab >> 8) & 0xff][4 * g]);
-            v.x = fmaf(ma.x, mb.x, -3.f * vv.x);
-            v.y = fmaf(ma.y, mb.y, -3.f * vv.y);
-            v.z = fmaf(ma.z, mb.z, -3.f * vv.z);
-            v.w = fmaf(ma.w, mb.w, -3.f * vv.w);
-          }
-          v.x *= sq.x;
-          v.y *= sq.y;
-          v.z *= sq.z;
-          v.w *= sq.w;
-        }
-        uint32_t h0, l0, h1, l1;
-        split2(v.x, v.y, h0, l0);
-        split2(v.z, v.w, h1, l1);
-        *reinterpret_cast<uint2*>(&L.oh[h][r][4 * g]) = make_uint2(h0, h1);
-        *reinterpret_cast<uint2*>(&L.ol[h][r][4 * g]) = make_uint2(l0, l1);
-        if (j & 1) __builtin_amdgcn_sched_barrier(0);   // two rows in flight at a time (registers)
-      }
-    }
-    __syncthreads();
-    if (skyok) {
-#pragma unroll
-      for (int ks = 0; ks < PXS / 16; ++ks) {
-        const int kx = 16 * ks + 8 * (lane >> 5);
-        bf16x8 ah[2], al[2], bh[2], bl[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int ra = 64 * wi + 32 * u + (lane & 31);
-          const int rb = TT + 64 * wj + 32 * u + (lane & 31);
-          ah[u] = *reinterpret_cast<const bf16x8*>(&L.oh[h][ra][kx]);
-          al[u] = *reinterpret_cast<const bf16x8*>(&L.ol[h][ra][kx]);
-          bh[u] = *reinterpret_cast<const bf16x8*>(&L.oh[h][rb][kx]);
-          bl[u] = *reinterpret_cast<const bf16x8*>(&L.ol[h][rb][kx]);
-        }
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) cha[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[b], cha[a][b], 0, 0, 0);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) cha[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[b], cha[a][b], 0, 0, 0);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) cha[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[b], cha[a][b], 0, 0, 0);
-      }
-      if (++link == CH || xs + PXS >= x1) {   // uniform
-        link = 0;
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            acc[a][b] += cha[a][b];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) cha[a][b][r] = 0.f;
-          }
-      }
+      for (int k = 0; k < NSK; ++k) form(j, k, 0, map_at(k, mo[j] & 0xffff), map_at(k, mo[j] >> 16), sq);
+      load_mean(j, 1);
     }
   }
-  if (!skyok) return;
-  // acc[a][b][r] = D[64 wi + 32 a + 8 (r / 4) + 4 (lane / 32) + r % 4][64 wj + 32 b + lane % 32]
-  float* dst = part + (((size_t)s * nchunk + chunk) * ntp + tp) * TT * TT;
+  __syncthreads();
+  stage_maps();
+  __syncthreads();
+
+  // this wave's operand fragments: rows fr + 32 u of tile ti and fc + 32 u of tile tj
+  const int sk = NSK == 2 ? h : 0;
+  const int l32 = lane & 31, z = (l32 >> 2) & 3, kh = lane >> 5;
+  const int fr = 64 * wi + l32, fc = (DIAG ? 0 : TT) + 64 * wj + (NSK == 2 ? 0 : 32 * h) + l32;
+  int link = 0;
+  for (int k = 0; k < n; ++k) {
+    const int b = k & 1;
+    load_maps(k + 2);
+    const f4 sq = *reinterpret_cast<const f4*>(&L.sw[4 * g]);
+    f4 ma = map_at(0, mo[0] & 0xffff), mb = map_at(0, mo[0] >> 16);
+    bf16x8 ah[2], al[2], bh[NB], bl[NB];
+#pragma unroll
+    for (int gi = 0; gi < NG; ++gi) {
+      const int j = gi / NSK, k2 = gi % NSK;   // the group's row and sky
+      if (gi % (NG / 2) == 0) {
+        const int q = ((2 * (gi / (NG / 2)) + kh) ^ z) << 3;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          ah[u] = *reinterpret_cast<const bf16x8*>(&L.oh[b][sk][fr + 32 * u][q]);
+          al[u] = *reinterpret_cast<const bf16x8*>(&L.ol[b][sk][fr + 32 * u][q]);
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+          bh[u] = *reinterpret_cast<const bf16x8*>(&L.oh[b][sk][fc + 32 * u][q]);
+          bl[u] = *reinterpret_cast<const bf16x8*>(&L.ol[b][sk][fc + 32 * u][q]);
+        }
+      }
+      f4 na = ma, nb = mb;
+      if (gi + 1 < NG) {
+        const int jn = (gi + 1) / NSK, kn = (gi + 1) % NSK;
+        na = map_at(kn, mo[jn] & 0xffff);
+        nb = map_at(kn, mo[jn] >> 16);
+      }
+#pragma unroll
+      for (int i = 0; i < NP / NG; ++i) {   // 2 NB each of lo hi, hi lo, hi hi, in this order per output
+        const int e = NP / NG * (gi % (NG / 2)) + i, t = e / (2 * NB), a = e / NB % 2, c = e % NB;
+        cha[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t == 0 ? al[a] : ah[a], t == 1 ? bl[c] : bh[c], cha[a][c], 0, 0, 0);
+      }
+      form(j, k2, b ^ 1, ma, mb, sq);
+      if (k2 == NSK - 1) load_mean(j, k + 2);
+      ma = na;
+      mb = nb;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (++link == CH || k + 1 == n) {   // uniform
+      link = 0;
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+          acc[a][c] += cha[a][c];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) cha[a][c][r] = 0.f;
+        }
+    }
+    __syncthreads();   // every wave has read this step's words and the next step's maps
+    stage_maps();
+    __syncthreads();
+  }
+  // acc[a][c][r] = D[64 wi + 32 a + 8 (r / 4) + 4 (lane / 32) + r % 4][column fc + 32 c]
+  dst += sk * dst_sky;
+  const int cb = 64 * wj + (NSK == 2 ? 0 : 32 * h) + l32;
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int c = 0; c < NB; ++c)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = 64 * wi + 32 * a + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int j = 64 * wj + 32 * b + (lane & 31);
-        dst[i * TT + j] = acc[a][b][r];
-      }
+      for (int r = 0; r < 16; ++r)
+        dst[(64 * wi + 32 * a + 8 * (r >> 2) + 4 * kh + (r & 3)) * TT + cb + 32 * c] = acc[a][c][r];
+}
+
+// Units (sky pair, chunk), each with its ntp tile pairs (tpairs: off the diagonal first).  With eight
+// units or more, unit u runs on XCD u % 8, with 8 or 16 chunks then all sky pairs of a chunk, so that
+// the pair means come from that XCD's L2.  The means' own product is sky S of S + 1: it fills
+// the last pair instead of a launch of its own.  On each XCD the longest workgroups come first:
+// two skies before one, tiles off the diagonal before those on it (half the rows to form).
+template <bool STATE>
+__global__ __launch_bounds__(NTQ) __attribute__((amdgpu_waves_per_eu(2))) void k_quad_syrk(
+    int P, int R, int npix, int S, int nchunk, int chunk_px, int ntile, const int2* __restrict__ tpairs,
+    const int* __restrict__ pair_a, const int* __restrict__ pair_b, const float* __restrict__ maps,
+    const float* __restrict__ V, const float* __restrict__ w, float* __restrict__ part) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char traw[];
+  TriLds& L = *reinterpret_cast<TriLds*>(traw);
+  const int ntp = ntile * (ntile + 1) / 2, noff = ntp - ntile;
+  const int nsky = S + (STATE ? 1 : 0), nf = nsky / SKW * nchunk, nu = (nsky + SKW - 1) / SKW * nchunk;
+  const int nx = nu >= 8 ? 8 : 1, x = blockIdx.x % nx;
+  const int uf = (nf - x + nx - 1) / nx, uh = (nu - x + nx - 1) / nx - uf;   // this XCD's units of two skies, of one
+  int i = blockIdx.x / nx, v = 0, q = -1;
+  auto take = [&](int v0, int units, int q0, int pairs) {
+    if (q >= 0) return;
+    if (i < units * pairs) {
+      v = v0 + i / pairs;
+      q = q0 + i % pairs;
+    } else {
+      i -= units * pairs;
+    }
+  };
+  take(0, uf, 0, noff);
+  take(0, uf, noff, ntile);
+  take(uf, uh, 0, noff);
+  take(uf, uh, noff, ntile);
+  if (q < 0) return;   // whole workgroup
+  const int u = x + nx * v, s0 = SKW * (u / nchunk), chunk = u % nchunk;
+  const int2 tt = tpairs[q];
+  const int tp = tt.x * ntile - tt.x * (tt.x - 1) / 2 + tt.y - tt.x;
+  const int x0 = chunk * chunk_px, x1 = min(npix, x0 + chunk_px);
+  const size_t sky = (size_t)nchunk * ntp * TT * TT;
+  float* dst = part + s0 * sky + ((size_t)chunk * ntp + tp) * TT * TT;
+#define RUN(NSK, DIAG) quad_chunk<NSK, DIAG, STATE>(L, P, R, npix, S, s0, tt, x0, x1, pair_a, pair_b, maps, V, w, dst, sky)
+  if (s0 + 1 < nsky) {
+    if (tt.x != tt.y) RUN(2, false);
+    else RUN(2, true);
+  } else {
+    if (tt.x != tt.y) RUN(1, false);
+    else RUN(1, true);
+  }
+#undef RUN
 }
 
 // Pixel-block-major copy of the pair means: Vt[b][pair][i] = V[pair][32 b + i] (zero past
@@ -300,9 +338,10 @@ __global__ __launch_bounds__(256) void k_quad_vtile(int R, int npix, int nblk, i
   }
 }
 
-// K[s][i][j] (i, j < R, FP64, both triangles) = sum over chunks of the tile partials.
-__global__ __launch_bounds__(256) void k_quad_reduce(int R, int nchunk, int ntp, int ntile, const float* __restrict__ part,
-                                                     double* __restrict__ K) {
+// K[s][i][j] (i, j < R, FP64, both triangles) = sum over chunks of the tile partials; sky S is KVV.
+__global__ __launch_bounds__(256) void k_quad_reduce(int R, int nchunk, int ntp, int ntile, int S,
+                                                     const float* __restrict__ part, double* __restrict__ K,
+                                                     double* __restrict__ KVV) {
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   const int s = blockIdx.y;
   if (e >= (size_t)R * R) return;
@@ -315,7 +354,7 @@ __global__ __launch_bounds__(256) void k_quad_reduce(int R, int nchunk, int ntp,
   const int tp = ti * ntile - ti * (ti - 1) / 2 + (tj - ti);
   double acc = 0.0;
   for (int c = 0; c < nchunk; ++c) acc += (double)part[(((size_t)s * nchunk + c) * ntp + tp) * TT * TT + ii * TT + jj];
-  K[(size_t)s * R * R + e] = acc;
+  (s < S ? K + (size_t)s * R * R : KVV)[e] = acc;
 }
 
 // FP64 path: K[s][i][j] for a 64 x 64 tile (bi, bj), bj <= bi, mirrored; whole pixel range.
@@ -396,19 +435,27 @@ int quad_ntile(int R) { return (R + TT - 1) / TT; }
 size_t quad_lds() { return sizeof(TriLds); }
 
 hipError_t quad_set_lds() {
-  return hipFuncSetAttribute((const void*)k_quad_syrk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TriLds));
+  hipError_t e =
+      hipFuncSetAttribute((const void*)k_quad_syrk<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TriLds));
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute((const void*)k_quad_syrk<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)sizeof(TriLds));
 }
 
-// K [S][R][R] FP64 for the S skies' maps (vmode 0) or for V itself (vmode 1, S = 1).  For
+// K [S][R][R] FP64 for the S skies' maps and, with pair means V, KVV [R][R] for V itself.  For
 // the float contexts the maps and V are pixel-block-major copies (launch_quad_vtile), for
 // FP64 the maps and the pair-major planes of the state.
-hipError_t launch_quad_syrk(const modal_ctx* c, const void* maps, const void* V, int S, int vmode, const int2* tpairs,
-                            float* part, double* K, hipStream_t st) {
+hipError_t launch_quad_syrk(const modal_ctx* c, const void* maps, const void* V, int S, const int2* tpairs, float* part,
+                            double* K, double* KVV, hipStream_t st) {
   const int R = c->npairs;
   if (c->prec == MODAL_F64) {
     const int nb = (R + 63) / 64;
-    hipLaunchKernelGGL(k_quad_syrk64, dim3(nb, nb, S), dim3(256), 0, st, c->P, R, c->npix, c->t.pair_a, c->t.pair_b,
-                       (const double*)maps, (const double*)V, c->t.w64, vmode, K);
+    auto run = [&](int skies, int vmode, double* out) {
+      hipLaunchKernelGGL(k_quad_syrk64, dim3(nb, nb, skies), dim3(256), 0, st, c->P, R, c->npix, c->t.pair_a, c->t.pair_b,
+                         (const double*)maps, (const double*)V, c->t.w64, vmode, out);
+    };
+    run(S, 0, K);
+    if (V) run(1, 1, KVV);
     return hipGetLastError();
   }
   const int ntile = quad_ntile(R), ntp = ntile * (ntile + 1) / 2;
@@ -416,12 +463,16 @@ hipError_t launch_quad_syrk(const modal_ctx* c, const void* maps, const void* V,
   const int chunk_px = ((c->npix + nchunk - 1) / nchunk + PXS - 1) / PXS * PXS;
   hipError_t e = quad_set_lds();
   if (e != hipSuccess) return e;
-  const int vec = c->npix % 4 == 0 ? 1 : 0;
-  hipLaunchKernelGGL(k_quad_syrk, dim3(ntp, nchunk, (S + SKW - 1) / SKW), dim3(NTQ), sizeof(TriLds), st, c->P, R,
-                     c->npix, S, nchunk, chunk_px, ntp, tpairs, c->t.pair_a, c->t.pair_b, (const float*)maps, (const float*)V, c->t.w32,
-                     vmode, vec, part);
+  const int nsky = S + (V ? 1 : 0), nu = (nsky + SKW - 1) / SKW * nchunk;
+  const dim3 grid((nu >= 8 ? (nu + 7) / 8 * 8 : nu) * ntp);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(NTQ), sizeof(TriLds), st, c->P, R, c->npix, S, nchunk, chunk_px, ntile, tpairs,
+                       c->t.pair_a, c->t.pair_b, (const float*)maps, (const float*)V, c->t.w32, part);
+  };
+  if (V) run(k_quad_syrk<true>);
+  else run(k_quad_syrk<false>);
   const size_t tot = (size_t)R * R;
-  hipLaunchKernelGGL(k_quad_reduce, dim3((tot + 255) / 256, S), dim3(256), 0, st, R, nchunk, ntp, ntile, part, K);
+  hipLaunchKernelGGL(k_quad_reduce, dim3((tot + 255) / 256, nsky), dim3(256), 0, st, R, nchunk, ntp, ntile, S, part, K, KVV);
   return hipGetLastError();
 }
 
@@ -449,10 +500,10 @@ size_t quad_mtile_bytes(const modal_ctx* c, int S) {
   return (size_t)S * ((c->npix + PXS - 1) / PXS) * c->P * PXS * 4;
 }
 
-size_t quad_part_bytes(const modal_ctx* c, int S) {
+size_t quad_part_bytes(const modal_ctx* c, int S) {   // S skies and the pair means
   if (c->prec == MODAL_F64) return 0;
   const int ntile = quad_ntile(c->npairs), ntp = ntile * (ntile + 1) / 2;
-  return (size_t)S * quad_chunks(c->npix) * ntp * TT * TT * 4;
+  return (size_t)(S + 1) * quad_chunks(c->npix) * ntp * TT * TT * 4;
 }
 
 }  // namespace modal

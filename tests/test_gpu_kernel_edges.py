@@ -207,3 +207,43 @@ def test_split_synthesis_edges(lmax, ntheta, nphi, P, S, table, prec):
     tol = 1e-4 if prec == "bf16x3" else 1e-5   # the bounds of the map tests
     rms = np.sqrt(np.mean(ref * ref, axis=(2, 3)))
     assert np.all(np.max(np.abs(got - ref), axis=(2, 3)) <= tol * rms)
+
+
+# Trispectrum update: one tile of 128 pairs and several (P 15 | 16 | 23 | 33), pairs that end inside
+# a tile, 1, 2, 8 and 16 pixel chunks, pixel counts off a multiple of 4, skies alone and in
+# pairs, with and without the pair means (whose own product fills or opens a pair).  Against FP64
+# sums of the library's own maps: each operand is kept to 2^-17, their low parts' product
+# (2^-18) is dropped and the FP32 chains round up to 100 times, which makes 2.6e-5 of the sums of
+# the absolute terms; the bound is 4e-5 of them.
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", [(3, 5, 8, 1, 1), (20, 45, 90, 15, 2), (20, 64, 136, 16, 3),
+                                                  (30, 130, 260, 23, 1), (40, 181, 370, 12, 5), (10, 40, 130, 33, 2)])
+def test_trispectrum_edges(lmax, ntheta, nphi, P, S):
+    from oracle import trispectrum as otr
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 75)
+    print(f"[case] trispectrum lmax={lmax} {ntheta}x{nphi} P={P} S={S}", flush=True)
+    a, mc = case.alms(0, S), case.alms(60, 2)
+    c = _ctx(case, "bf16x3")
+    st = c.linear_state()
+    c.linear_reset(st)
+    c.linear_accumulate(st, mc)
+    c.linear_finalize(st)
+    M = c.filter_maps(a).cpu().numpy().astype(np.float64).reshape(S, P, -1)
+    V = om.pair_means(c.filter_maps(mc).cpu().numpy().astype(np.float64)).reshape(P * (P + 1) // 2, -1)
+    w = np.broadcast_to(np.asarray(case.grid.w), (ntheta, nphi)).reshape(-1)
+    pid = otr._pair_index(P)
+    q = np.array(otr.quad_list(P))
+    pair = np.array([[pid[(min(i, j), max(i, j))] for j in range(P)] for i in range(P)])
+    pa, pb = np.triu_indices(P)
+    order = pair[pa, pb]
+    for state, Vs in ((None, 0.0 * V), (st, V)):
+        got = c.trispectrum(a, state=state).cpu().numpy()
+        for s in range(S):
+            MM = np.empty_like(V)
+            MM[order] = M[s][pa] * M[s][pb]
+            A, B = MM - 3 * Vs, np.abs(MM) + 3 * np.abs(Vs)
+            K = (A * w) @ A.T - 6 * ((Vs * w) @ Vs.T)
+            Kabs = (B * np.abs(w)) @ B.T + 6 * ((np.abs(Vs) * np.abs(w)) @ np.abs(Vs).T)
+            parts = [(pair[q[:, i], q[:, j]], pair[q[:, k], q[:, l]]) for i, j, k, l in ((0, 1, 2, 3), (0, 2, 1, 3), (0, 3, 1, 2))]
+            ref = sum(K[x, y] for x, y in parts) / 3
+            bound = 4e-5 * sum(Kabs[x, y] for x, y in parts) / 3
+            assert np.all(np.abs(got[s] - ref) <= bound), (s, state is None, np.max(np.abs(got[s] - ref) / bound))
