@@ -407,6 +407,12 @@ __device__ inline void dft_plus(float2* x) {
   }
 }
 
+template <int WPR>
+__device__ inline void rg_order() {
+  if (WPR == 1) wave_order();
+  else lds_barrier();
+}
+
 // one Stockham pass of radix R over the ring buffer b (length K); twp is this pass's
 // twiddle table, twp[(q - 1) Ns + k] = e^{2 pi i q k / (Ns R)}, laid out so that the
 // lanes of a wave (consecutive k) read consecutive entries
@@ -415,25 +421,28 @@ __device__ inline void dft_plus(float2* x) {
 // of back to b (nothing when out is null: a padding ring)
 // KC, NSC: the ring length and the pass's stride when known at compile time (0: from
 // the arguments), so that the index arithmetic of a specialised plan folds to constants
-template <int R, int PTS, bool OUT = false, int KC = 0, int NSC = 0>
+// WPR: the waves that share a ring (lane counts through them); with two, every wave of the
+// workgroup runs the pass and barriers keep its order
+template <int R, int PTS, bool OUT = false, int KC = 0, int NSC = 0, int WPR = 1>
 __device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float2* twp, float2* out = nullptr) {
-  constexpr int NB = KC ? (KC / R + 63) / 64 : (PTS + R - 1) / R;
+  static_assert(WPR == 1 || KC, "shared rings: compiled-in plans only");
+  constexpr int NB = KC ? (KC / R + 64 * WPR - 1) / (64 * WPR) : (PTS + R - 1) / R;
   const int K = KC ? KC : K_;
   const int Ns = NSC ? NSC : Ns_;
   const int KR = K / R;
   float2 v[NB][R];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    const int bi = lane + 64 * i;
+    const int bi = lane + 64 * WPR * i;
     if (bi < KR) {
 #pragma unroll
       for (int q = 0; q < R; ++q) v[i][q] = b[padr(bi + q * KR)];
     }
   }
-  wave_order();
+  rg_order<WPR>();
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    const int bi = lane + 64 * i;
+    const int bi = lane + 64 * WPR * i;
     if (bi < KR) {
       const int k = bi % Ns;
       if (NSC != 1) {   // (the first pass's twiddles are all 1)
@@ -453,7 +462,7 @@ __device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float
       }
     }
   }
-  wave_order();
+  if (WPR == 1 || !OUT) rg_order<WPR>();
 }
 
 // cos and sin of 2 pi j / 47, j < 47, rounded to float
@@ -481,13 +490,15 @@ __device__ constexpr float kS47[47] = {
 // outputs:
 //   y_q = A_q + i B_q,  y_{47-q} = A_q - i B_q,
 //   A_q = x_0 + sum_r s_r cos(2 pi r q / 47),  B_q = sum_r d_r sin(2 pi r q / 47),
-// each pair stored as soon as it is formed.  All the wave's loads precede its stores in
-// program order, and LDS accesses of one wave complete in order, so the pass is in place.
-__device__ inline void rg_pass47_first(float2* b, int lane) {
+// each pair stored as soon as it is formed.  All the loads precede the stores (of one wave in
+// program order, of two by a barrier), so the pass is in place.  Of two waves both form all
+// sums s, d and half the outputs each.
+template <int WPR = 1>
+__device__ inline void rg_pass47_first(float2* b, int lane, int half = 0) {
   float2 x[47];
 #pragma unroll
   for (int r = 0; r < 47; ++r) x[r] = b[padr(lane + 64 * r)];
-  wave_order();
+  rg_order<WPR>();
 #pragma unroll
   for (int r = 1; r < 24; ++r) {
     const float2 sr = cadd(x[r], x[47 - r]), dr = csub(x[r], x[47 - r]);
@@ -495,28 +506,39 @@ __device__ inline void rg_pass47_first(float2* b, int lane) {
     x[47 - r] = dr;
   }
   const int ob = 47 * lane;
-  float2 y0 = x[0];
+  auto outputs = [&](auto first, auto last) {
 #pragma unroll
-  for (int r = 1; r < 24; ++r) y0 = cadd(y0, x[r]);
-  b[padr(ob)] = y0;
+    for (int q = first; q < last; ++q) {
+      float2 A = x[0], B = make_float2(0.f, 0.f);
 #pragma unroll
-  for (int q = 1; q < 24; ++q) {
-    float2 A = x[0], B = make_float2(0.f, 0.f);
-#pragma unroll
-    for (int r = 1; r < 24; ++r) {
-      const int j = (r * q) % 47;
-      A.x = fmaf(x[r].x, kC47[j], A.x);
-      A.y = fmaf(x[r].y, kC47[j], A.y);
-      B.x = fmaf(x[47 - r].x, kS47[j], B.x);
-      B.y = fmaf(x[47 - r].y, kS47[j], B.y);
+      for (int r = 1; r < 24; ++r) {
+        const int j = (r * q) % 47;
+        A.x = fmaf(x[r].x, kC47[j], A.x);
+        A.y = fmaf(x[r].y, kC47[j], A.y);
+        B.x = fmaf(x[47 - r].x, kS47[j], B.x);
+        B.y = fmaf(x[47 - r].y, kS47[j], B.y);
+      }
+      b[padr(ob + q)] = make_float2(A.x - B.y, A.y + B.x);
+      b[padr(ob + 47 - q)] = make_float2(A.x + B.y, A.y - B.x);
+      if (WPR > 1) __builtin_amdgcn_sched_barrier(0);   // output by output (registers)
     }
-    b[padr(ob + q)] = make_float2(A.x - B.y, A.y + B.x);
-    b[padr(ob + 47 - q)] = make_float2(A.x + B.y, A.y - B.x);
+  };
+  if (half == 0) {   // wave-uniform
+    float2 y0 = x[0];
+#pragma unroll
+    for (int r = 1; r < 24; ++r) y0 = cadd(y0, x[r]);
+    b[padr(ob)] = y0;
   }
-  wave_order();
+  typedef std::integral_constant<int, 1> one;
+  typedef std::integral_constant<int, 12> mid;
+  typedef std::integral_constant<int, 24> end;
+  if (WPR == 1) outputs(one{}, end{});
+  else if (half == 0) outputs(one{}, mid{});
+  else outputs(mid{}, end{});
+  rg_order<WPR>();
 }
 
-template <int PTS, int KC>
+template <int PTS, int KC, int WPR = 1>
 __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, int nseq,
                                             const float2* __restrict__ F, float* __restrict__ maps,
                                             const float2* __restrict__ twg, const float2* __restrict__ twpg) {
@@ -531,27 +553,29 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
   float2* twp = tw + K / 2 + 1;          // the passes' twiddle tables, K - 1 entries in all
   const int nrb8 = f_ring_blocks(ntheta);
   const int units = nseq * nrb8;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: the ring row base stays scalar
-  for (int t = tid; t <= K / 2; t += 64 * RG_RINGS) tw[t] = twg[t];
-  for (int t = tid; t < K - 1; t += 64 * RG_RINGS) twp[t] = twpg[t];
+  constexpr int NTH = 64 * RG_RINGS * WPR;
+  const int tid = threadIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), w = wv / WPR;   // wave-uniform: the ring row base stays scalar
+  for (int t = tid; t <= K / 2; t += NTH) tw[t] = twg[t];
+  for (int t = tid; t < K - 1; t += NTH) twp[t] = twpg[t];
   // persistent: workgroups b and b + 8 (one XCD) take the two halves of the same ring
   // groups, xcd + 8 (slot + k nslot), k = 0, 1, ...
   const int b = blockIdx.x;
   const int xcd = b & 7, half = (b >> 3) & 1, slot = b >> 4;
   const int nslot = gridDim.x >> 4;
   // Spectrum loads: ZE elements per thread per round, as many as the register budget holds
-  // (rounds of 4, one of 6, 3 or 12: 8 skies of 768 x 1536 pixels, 30 modes, 0.52 -> 0.46 ms; of
-  // 1536 x 3072, 40 modes, 2.35 -> 2.20; 4 of 3008 x 6016, 50 modes, 12.2 -> 11.6; everything of a
-  // unit in one round is slower for the first two, which then lose a wave per SIMD).
-  constexpr int ZE = KC == 3008 ? 12 : KC == 1536 ? 6 : KC == 768 ? 3 : 4;
+  // (rounds of 4, one of 6 or 3: 8 skies of 768 x 1536 pixels, 30 modes, 0.52 -> 0.46 ms; of
+  // 1536 x 3072, 40 modes, 2.35 -> 2.20; everything of a unit in one round costs a wave per SIMD).
+  // 3008 with two waves per ring: 12 8.88 ms, 6 8.27, 4 8.07, 3 7.99; the next round's or unit's
+  // loads ahead of their use 8.3 to 8.7.
+  constexpr int ZE = KC == 3008 ? 3 : KC == 1536 ? 6 : KC == 768 ? 3 : 4;
   typedef float f4 __attribute__((ext_vector_type(4)));
   f4 xa[ZE], xb[ZE];
   auto load_spectra = [&](int unit, int e0) {
     const f4* src = reinterpret_cast<const f4*>(F + (size_t)unit * (lmax + 1) * 8 + RG_RINGS * half);
 #pragma unroll
     for (int i = 0; i < ZE; ++i) {
-      const int e = min(e0 + tid + i * 64 * RG_RINGS, 2 * K - 1);
+      const int e = min(e0 + tid + i * NTH, 2 * K - 1);
       const int m = e >> 1, rp = e & 1;
       xa[i] = src[(size_t)min(m, lmax) * 4 + rp];
       xb[i] = src[(size_t)min(K - m, lmax) * 4 + rp];
@@ -568,11 +592,11 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
     //   Z_m = (X_m + conj X_{K-m}) + i e^{2 pi i m / N} (X_m - conj X_{K-m}),  m < K,
     // with X_m = F_m for m <= lmax (X_0 real) and 0 otherwise.  Element e = (m, rp), both
     // loads unconditional (index clamped, value selected after).
-    for (int e0 = 0; e0 < 2 * K; e0 += ZE * 64 * RG_RINGS) {
+    for (int e0 = 0; e0 < 2 * K; e0 += ZE * NTH) {
       load_spectra(unit, e0);
 #pragma unroll
       for (int i = 0; i < ZE; ++i) {
-        const int e = e0 + tid + i * 64 * RG_RINGS;
+        const int e = e0 + tid + i * NTH;
         if (e < 2 * K) {
           const int m = e >> 1, rp = e & 1;
           const bool ha = m <= lmax, hb = m > 0 && K - m <= lmax;
@@ -592,6 +616,8 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
     lds_barrier();   // (the previous unit's map stores stay in flight here too)
 
     float2* bw = rbuf + w * KP;
+    int lane = tid & (64 * WPR - 1);
+    if (WPR > 1) asm volatile("" : "+v"(lane));   // LDS addresses formed anew: kept over the loop they spill
     // z = sum_m Z_m e^{+2 pi i m n / K}; the last pass writes the map row directly:
     // M_{2n} = Re z_n, M_{2n+1} = Im z_n
     const int j = rb * 8 + RG_RINGS * half + w;
@@ -609,9 +635,9 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
       rg_pass<3, PTS, true, KC, 256>(bw, K, 256, lane, twp + 255, dst);
     } else if constexpr (KC == 3008) {
       // passes 47, 8, 8 (strides 1, 47, 376; twiddle tables at 46, 46 + 7 * 47)
-      rg_pass47_first(bw, lane);
-      rg_pass<8, PTS, false, KC, 47>(bw, K, 47, lane, twp + 46);
-      rg_pass<8, PTS, true, KC, 376>(bw, K, 376, lane, twp + 46 + 7 * 47, dst);
+      rg_pass47_first<WPR>(bw, lane & 63, wv % WPR);
+      rg_pass<8, PTS, false, KC, 47, WPR>(bw, K, 47, lane, twp + 46);
+      rg_pass<8, PTS, true, KC, 376, WPR>(bw, K, 376, lane, twp + 46 + 7 * 47, dst);
     } else {
       int Ns = 1;
       const float2* tf = twp;
@@ -664,11 +690,15 @@ __global__ __launch_bounds__(64 * RG_RINGS) __attribute__((amdgpu_waves_per_eu(4
 }
 
 // the plan 47 x 8 x 8 of K = 3008 (the rings of nphi 6016, the l_max 2000 grid): its
-// LDS (about 141 KB) holds one workgroup per CU, so registers are not limited
-__global__ __launch_bounds__(64 * RG_RINGS) void k_fft_c2r_rg_k3008(
+// LDS (about 141 KB) holds one workgroup of four rings per CU.  Two waves share a ring, two
+// waves per SIMD: one wave alone issues a vector instruction every 5 cycles or so, two every 2.5,
+// and the 47-point pass is 2100 of them.  4 skies of 3008 rings, 50 modes: 11.6 ms with a wave per
+// ring, 8.0 now (a copy of its 24 GB takes 5.2).
+constexpr int kW3008 = 2;   // waves per ring
+__global__ __launch_bounds__(64 * RG_RINGS * kW3008) __attribute__((amdgpu_waves_per_eu(2))) void k_fft_c2r_rg_k3008(
     FftPlan plan, int lmax, int ntheta, int nseq, const float2* __restrict__ F, float* __restrict__ maps,
     const float2* __restrict__ twg, const float2* __restrict__ twpg) {
-  c2r_rg_body<48, 3008>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
+  c2r_rg_body<48, 3008, kW3008>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
 }
 
 // r2c, register passes (the adjoint of k_fft_c2r_rg): same persistent ring-group order,
@@ -947,7 +977,7 @@ hipError_t launch_fft_c2r(const modal_ctx* c, const void* F, int S, void* maps, 
                          c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps, (const float2*)c->t.tw32,
                          (const float2*)c->t.twp32);
     else if (plan_is_k3008(c->fft_rg_plan))   // one workgroup per CU: 256 of them
-      hipLaunchKernelGGL(k_fft_c2r_rg_k3008, dim3(std::min(blocks, 256)), dim3(64 * RG_RINGS), fft_rg_lds(c), st,
+      hipLaunchKernelGGL(k_fft_c2r_rg_k3008, dim3(std::min(blocks, 256)), dim3(64 * RG_RINGS * kW3008), fft_rg_lds(c), st,
                          c->fft_rg_plan, c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps,
                          (const float2*)c->t.tw32, (const float2*)c->t.twp32);
     else if (pts <= 16) LAUNCH(16);
