@@ -279,17 +279,23 @@ __global__ __launch_bounds__(256) void k_adj_legendre_mfma(int lmax, int ntheta,
 // (K = 16 rings, N = 32 l of one parity); lane l holds A[l % 32][8 (l / 32) + i] and
 // B[8 (l / 32) + i][l % 32]; accumulator register r is D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 // Both operands are split into bf16 hi + lo and each product is Ah Bh + Ah Bl + Al Bh.
-// Workgroup: 4 waves, one m, 128 consecutive l - m (wave w: the 32 l of parity w / 2 in
-// the half w % 2), 64 complex columns (4 tiles of 32 real columns).  The folded ring values
-// of a 32-ring chunk are split and staged in LDS, double buffered; each lane loads the
+// Workgroup: 8 waves, one m, 256 consecutive l - m (wave w: the 32 l of parity w / 4 in
+// the quarter w % 4), 64 complex columns (4 tiles of 32 real columns).  The folded ring values
+// of a 32-ring chunk are loaded two rings at a time, split and staged in LDS, double buffered; each lane loads the
 // lambda of its l at the 16 rings of its two K steps from the FP32 table one chunk ahead
 // and splits them in registers.  The workgroups of one m (l blocks x column blocks) run
 // back to back on one XCD, so lambda[m] and the ring values of m come from HBM about once.  An output takes
 // 3 nrp / 16 accumulations (144 at 768 rings); the truncation of the matrix core's
 // accumulation stays below the operand split error.
+// Bound by the staging's vector work and the latency of a chunk's loads (two waves per SIMD), so the
+// l block is as wide as the workgroup allows: every block of a column folds and splits the same
+// rings again.  64 planes of l_max 500, 768 rings: 225 us with 128 l and 4 waves, ring values loaded
+// one by one and selected behind branches, 173 now (the bytes take about 97); twice the planes per
+// transform, which reads lambda half as often, is slower (their spectra then miss the last-level cache).
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-constexpr int AS_L = 128;         // l per workgroup (32 of one parity per wave)
+constexpr int AS_L = 256;         // l per workgroup (32 of one parity per wave)
+constexpr int AS_NT = 2 * AS_L;   // threads
 constexpr int AS_NC = 64;         // complex columns per workgroup
 constexpr int AS_RC = 32;         // rings per staged chunk (two K steps)
 constexpr int AS_RS = AS_RC + 8;  // LDS row stride of a staged column (16-bit words): 16-byte reads of 16 lanes on distinct banks
@@ -316,7 +322,7 @@ __device__ inline void as_split2(float v0, float v1, uint32_t& hi, uint32_t& lo)
   lo = as_bf16x2(v0 - __builtin_bit_cast(float, hb << 16), v1 - __builtin_bit_cast(float, hb & 0xffff0000u));
 }
 
-__global__ __launch_bounds__(256) void k_adj_legendre_split(int lmax, int ntheta, int nrp, int ncol, int nalm, int nlb,
+__global__ __launch_bounds__(AS_NT) __attribute__((amdgpu_waves_per_eu(2))) void k_adj_legendre_split(int lmax, int ntheta, int nrp, int ncol, int nalm, int nlb,
                                                             int ncb, const float* __restrict__ lam,
                                                             const float2* __restrict__ Gh, float* __restrict__ Z) {
   typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -326,12 +332,12 @@ __global__ __launch_bounds__(256) void k_adj_legendre_split(int lmax, int ntheta
   const int L = lmax + 1 - m;
   if (m > lmax || lb * AS_L >= L) return;   // whole workgroup, before any barrier
   const int c0 = cb * AS_NC;
-  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
   const size_t off = (size_t)m * (2 * lmax + 3 - m) / 2;
   const float* lrow = lam + off * nrp;
   __shared__ AsLds S;
-  const int par = wv >> 1;                        // the parity of l - m of this wave's rows
-  const int li = lb * AS_L + 64 * (wv & 1) + 2 * n + par;   // this lane's B column (l - m)
+  const int par = wv >> 2;                        // the parity of l - m of this wave's rows
+  const int li = lb * AS_L + 64 * (wv & 3) + 2 * n + par;   // this lane's B column (l - m)
   const int lcl = min(li, L - 1);
   // lambda at rings 32 c + 16 kk + 8 h + i of the lane's l for the two K steps kk of chunk c
   // (valid addresses for every c), loaded one chunk ahead
@@ -343,36 +349,37 @@ __global__ __launch_bounds__(256) void k_adj_legendre_split(int lmax, int ntheta
       for (int i = 0; i < 8; ++i) dst[kk][i] = lrow[(size_t)min(AS_RC * c + 16 * kk + 8 * h + i, nrp - 1) * L + lcl];
   };
   // ring values of a chunk: thread (column q, ring pair jp) for four (q, jp), north and south
-  constexpr int NU = AS_NC * AS_RC / 2 / 256;
-  float2 gn[NU][2], gs[NU][2];
+  constexpr int NU = AS_NC * AS_RC / 2 / AS_NT;
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));   // two rings; rings of odd ntheta: 8-byte aligned
+  f4u gn[NU], gs[NU];   // rings j, j + 1 and their south rings ntheta - 2 - j, ntheta - 1 - j
   auto load_g = [&](int r0) {
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int e = tid + 256 * u, jp = e % (AS_RC / 2), q = e / (AS_RC / 2);
+      const int e = tid + AS_NT * u, jp = e % (AS_RC / 2), q = e / (AS_RC / 2);
       const float2* g = Gh + ((size_t)min(c0 + q, ncol - 1) * (lmax + 1) + m) * ntheta;   // Gh[col][m][ring]
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int j = min(r0 + 2 * jp + k, nrp - 1);
-        gn[u][k] = g[j];
-        gs[u][k] = g[ntheta - 1 - j];
-      }
+      const int j = min(r0 + 2 * jp, ntheta - 2);
+      gn[u] = *reinterpret_cast<const f4u*>(g + j);
+      gs[u] = *reinterpret_cast<const f4u*>(g + ntheta - 2 - j);
     }
   };
   auto store_g = [&](int r0, int buf) {
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int e = tid + 256 * u, jp = e % (AS_RC / 2), q = e / (AS_RC / 2);
+      const int e = tid + AS_NT * u, jp = e % (AS_RC / 2), q = e / (AS_RC / 2);
       float hp[2][2], hm[2][2];   // [part][ring of the pair]
+      const f4u vn4 = gn[u], vs4 = gs[u];
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const int j = r0 + 2 * jp + k;
-        const bool in = j < nrp && c0 + q < ncol;
-        const float2 vn = in ? gn[u][k] : make_float2(0.f, 0.f);
-        const float2 vs = (in && ntheta - 1 - j != j) ? gs[u][k] : make_float2(0.f, 0.f);   // the equator ring once
-        hp[0][k] = vn.x + vs.x;
-        hp[1][k] = vn.y + vs.y;
-        hm[0][k] = vn.x - vs.x;
-        hm[1][k] = vn.y - vs.y;
+        const uint32_t in = (j < nrp && c0 + q < ncol) ? ~0u : 0u;         // masks: a select would branch
+        const uint32_t is = ntheta - 1 - j != j ? in : 0u;                 // the equator ring once
+        auto masked = [](float v, uint32_t m) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) & m); };
+        const float nx = masked(vn4[2 * k], in), ny = masked(vn4[2 * k + 1], in);
+        const float sx = masked(vs4[2 - 2 * k], is), sy = masked(vs4[3 - 2 * k], is);
+        hp[0][k] = nx + sx;
+        hp[1][k] = ny + sy;
+        hm[0][k] = nx - sx;
+        hm[1][k] = ny - sy;
       }
 #pragma unroll
       for (int part = 0; part < 2; ++part) {
@@ -408,7 +415,7 @@ __global__ __launch_bounds__(256) void k_adj_legendre_split(int lmax, int ntheta
     load_lam(ch + 1, lvn);   // the next chunk's lambda (clamped past the last ring: unused)
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
-      bf16x8 bh, bl;
+      bf16x8 bh, bl, ah[4], al[4];
       {
         u32x4 hv, lo4;
 #pragma unroll
@@ -423,12 +430,16 @@ __global__ __launch_bounds__(256) void k_adj_legendre_split(int lmax, int ntheta
       }
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct) {
-        const bf16x8 ah = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&S.h[buf][par][32 * ct + n][16 * kk + 8 * h]));
-        const bf16x8 al = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&S.l[buf][par][32 * ct + n][16 * kk + 8 * h]));
-        acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc[ct], 0, 0, 0);
-        acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc[ct], 0, 0, 0);
-        acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc[ct], 0, 0, 0);
+        ah[ct] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&S.h[buf][par][32 * ct + n][16 * kk + 8 * h]));
+        al[ct] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&S.l[buf][par][32 * ct + n][16 * kk + 8 * h]));
       }
+      // product by product over the column tiles, so that consecutive MFMAs feed different sums
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[ct], bh, acc[ct], 0, 0, 0);
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[ct], bl, acc[ct], 0, 0, 0);
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[ct], bh, acc[ct], 0, 0, 0);
     }
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
@@ -576,10 +587,10 @@ hipError_t launch_adj_legendre_cols(const modal_ctx* c, const void* lam, const v
   } else if (c->prec == MODAL_F32) {
     hipLaunchKernelGGL(k_adj_legendre_f64<float>, gridf, dim3(256), 0, st, c->lmax, c->ntheta, c->nrp, ncol, c->nalm,
                        nlf, ncf, (const float*)lam, (const float2*)Gh, (float2*)Z);
-  } else if (c->prec == MODAL_BF16X3) {
+  } else if (c->prec == MODAL_BF16X3 && c->ntheta > 1) {   // (it loads two rings at a time)
     const int nlb = (c->lmax + AS_L) / AS_L, ncb = (ncol + AS_NC - 1) / AS_NC;
     const dim3 grid(8 * ((c->lmax + 8) / 8) * nlb * ncb);
-    hipLaunchKernelGGL(k_adj_legendre_split, grid, dim3(256), 0, st, c->lmax, c->ntheta, c->nrp, ncol, c->nalm, nlb,
+    hipLaunchKernelGGL(k_adj_legendre_split, grid, dim3(AS_NT), 0, st, c->lmax, c->ntheta, c->nrp, ncol, c->nalm, nlb,
                        ncb, (const float*)lam, (const float2*)Gh, (float*)Z);
   } else {
     dim3 grid((c->lmax + 1 + 63) / 64, c->lmax + 1, (ncol + AL_NC - 1) / AL_NC);

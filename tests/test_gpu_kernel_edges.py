@@ -247,3 +247,19 @@ def test_trispectrum_edges(lmax, ntheta, nphi, P, S):
             ref = sum(K[x, y] for x, y in parts) / 3
             bound = 4e-5 * sum(Kabs[x, y] for x, y in parts) / 3
             assert np.all(np.abs(got[s] - ref) <= bound), (s, state is None, np.max(np.abs(got[s] - ref) / bound))
+
+
+# Adjoint of the bf16 contexts: l_max on both sides of a block of 256 l, ring counts with 16-byte
+# (even) and 8-byte (odd) aligned pairs, an equator ring alone in its pair, ring counts off a chunk of 32,
+# the smallest grids, columns past a block of 64.
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", [(2, 3, 6, 1, 1), (2, 4, 6, 2, 1), (30, 33, 64, 7, 10),
+                                                  (255, 259, 512, 2, 2), (256, 258, 514, 3, 1)])
+def test_bf16_adjoint_edges(lmax, ntheta, nphi, P, S):
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 76)
+    print(f"[case] bf16 adjoint lmax={lmax} {ntheta}x{nphi} P={P} S={S}", flush=True)
+    a = case.alms(0, S)
+    cot = np.random.default_rng(lmax).standard_normal((S, P * (P + 1) * (P + 2) // 6))
+    got = _ctx(case, "bf16x3").beta_vjp(a, cot).cpu().numpy()
+    for i in range(S):
+        ref = om.vjp(a[i], case.cl, case.q, case.grid, None, cot[i])[0]
+        assert np.linalg.norm(got[i] - ref) <= 1e-4 * np.linalg.norm(ref)   # the map bound of these contexts
