@@ -215,9 +215,9 @@ __global__ __launch_bounds__(256) void k_pair_adjoint_f32(int P, int npairs, int
 //   G[u][x] = w(x) 2^E sum_k A[u][k] B[k][x],  A = 2^-E K[u][(ab)] / (s_a s_b),  B = (s_a M_a)(s_b M_b),
 // with s_p the context's power-of-two map scales (~ 1/sigma_p) and 2^-E a power of two per sky
 // that puts max |A| near 2^14, so both operands sit well inside the fp16 range and every
-// scaling is exact.  On v_mfma_f32_32x32x16_f16 (lane l holds A[l % 32][8 (l / 32) + i],
-// B[8 (l / 32) + i][l % 32]; accumulator register j is D[8 (j / 4) + 4 (l / 32) + j % 4][l % 32]):
-// rows = modes (one or two 32-row tiles), columns = pixels, inner index = pairs.
+// scaling is exact.  On v_mfma_f32_16x16x32_f16 (lane l holds A[l % 16][8 (l / 16) + i],
+// B[8 (l / 16) + i][l % 16]; accumulator register j is D[4 (l / 16) + j][l % 16]):
+// rows = modes (one to three 16-row tiles), columns = pixels, inner index = pairs.
 //   A = Ah + Al: fp16 hi and lo of the FP32 value, split once per sky;
 //   the scaled maps are held as fp16 pairs m = h + l (h = f16(m), l = f16(m - h)), and a pair
 //   product is formed with packed fp16 arithmetic, two pairs per instruction:
@@ -228,12 +228,17 @@ __global__ __launch_bounds__(256) void k_pair_adjoint_f32(int P, int npairs, int
 // The inner index runs over 8-pair groups (a, b = B0 .. B0 + 7), B0 a multiple of 8 with
 // B0 >= 8 floor(a / 8): a lane reads h_a, l_a and the eight h_b, l_b of its pixel from the map
 // row in LDS (two 2-byte and two 16-byte reads), and the slots with b < a or b >= P carry A = 0
-// (for P = 40: 960 slots for 820 pairs).  An MFMA K step of 16 takes groups 2t (lanes 0-31)
-// and 2t + 1 (lanes 32-63); the map reads and products of step t + 1 are issued among the
-// MFMAs of step t (software pipeline).  The A operands of SG_KC steps are staged in LDS, double
-// buffered; the MFMAs of SG_CH staged chunks accumulate from zero into a chain that is then
-// added to the running FP32 sums (the matrix core truncates the addend of a long accumulation).
+// (for P = 40: 960 slots for 820 pairs).  An MFMA K step of 32 takes groups 4t .. 4t + 3, one per
+// 16 lanes; the map reads and products of step t + 1 are issued among the MFMAs of step t
+// (software pipeline).  The A operands of a step are staged in LDS, double buffered; the MFMAs of
+// SG_CH steps accumulate from zero into a chain that is then added to the running FP32 sums (the
+// matrix core truncates the addend of a long accumulation).
 // A workgroup is 4 waves and 256 pixels of one sky (70 KB of LDS: two workgroups per CU).
+// Bound by the matrix cores and the packed products together (they overlap in part: 12 products of
+// 32 x 32 x 16 and 144 vector instructions take 646 cycles of a SIMD with two waves, 460 and 406
+// alone), so the row tiles follow P: 8 skies of 1536 x 3072 pixels, P 40: 6.8 ms with rows in tiles
+// of 32 and three dependent products in turn, 6.1 now; P 30, 4 skies of 768 x 1536: the whole
+// gradient 2.46 -> 2.15 ms, P 16 1.64 -> 1.43.
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16 f16x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -242,9 +247,8 @@ constexpr int SG_NW = 4;               // waves per workgroup (two workgroups pe
 constexpr int SG_PX = 64 * SG_NW;      // pixels per workgroup: two 32-column tiles per wave
 constexpr int SG_PP = 48;              // modes held per map row (P <= 48; rows zero past P)
 constexpr int SG_MS = 2 * SG_PP + 8;   // map row stride in halves: hi words, lo words, pad (208 B)
-constexpr int SG_KC = 2;               // K steps per staged chunk
-constexpr int SG_CH = 4;               // staged chunks per accumulation chain
-constexpr int SG_GC = 2 * SG_KC;       // 8-pair groups per chunk
+constexpr int SG_GC = 4;               // 8-pair groups per K step (and staged chunk)
+constexpr int SG_CH = 4;               // K steps per accumulation chain
 constexpr int SG_MAXG = 176;           // groups for P = 48 (168), padded to a whole chunk
 constexpr int SG_EMAX = 14;            // max |A| is scaled to about 2^SG_EMAX
 
@@ -336,8 +340,8 @@ struct SgLds {
   float msc[SG_PP];            // map scales, zero past P
 };
 
-template <int MT>
-__global__ __launch_bounds__(64 * SG_NW) void k_pair_adjoint_split(int P, int npix, int ngp,
+template <int NT>
+__global__ __launch_bounds__(64 * SG_NW) __attribute__((amdgpu_waves_per_eu(2))) void k_pair_adjoint_split(int P, int npix, int ngp,
                                                                      const int* __restrict__ grp,
                                                                      const float* __restrict__ maps,
                                                                      const float* __restrict__ w,
@@ -348,7 +352,7 @@ __global__ __launch_bounds__(64 * SG_NW) void k_pair_adjoint_split(int P, int np
   __shared__ SgLds L;
   const int s = blockIdx.y, x0 = blockIdx.x * SG_PX;
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-  const int c = lane & 31, h = lane >> 5;
+  const int c = lane & 15, h = lane >> 4;
   const float* Ms = maps + (size_t)s * P * npix;
   // the scaled maps as fp16 pairs: thread (xx = tid, modes 2i, 2i + 1), coalesced along pixels.
   // All loads are issued before the first is used: one round trip instead of 24.
@@ -391,41 +395,36 @@ __global__ __launch_bounds__(64 * SG_NW) void k_pair_adjoint_split(int P, int np
       L.a[buf][e >> 7][(e >> 6) & 1][e & 63] = pre[i];
     }
   };
-  f32x16 acc[MT][2], cc[MT][2];
+  f32x4 acc[NT][4], cc[NT][4];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) acc[mt][ct][j] = cc[mt][ct][j] = 0.f;
-  const uint16_t* row[2] = {L.ms[wv * 64 + c], L.ms[wv * 64 + 32 + c]};   // this lane's pixel of each tile
-  // The lane's map words of K step t (group 2t + h: a, B0) for both pixel tiles, and the
-  // fp16 hi/lo pair products formed from them.
+    for (int ct = 0; ct < 4; ++ct) acc[mt][ct] = cc[mt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint16_t* row = L.ms[wv * 64 + c];   // this lane's pixel of tile 0 (tile ct: 16 ct rows on)
+  // The lane's map words of K step t (group 4t + h: a, B0) for a pixel tile, and the fp16
+  // hi/lo pair products formed from them.
   struct Maps {
-    uint32_t ha[2], la[2];
-    u32x4 hb[2], lb[2];
+    uint32_t ha, la;
+    u32x4 hb, lb;
   };
-  const int nk = ngp / 2;
-  auto read_maps = [&](int t, Maps& R) {
-    const int gv = L.grp[2 * t + h];
+  auto group = [&](int t) { return L.grp[SG_GC * t + h]; };
+  auto read_maps = [&](int gv, int ct, Maps& R) {
     const int a = gv & 0xff, B0 = gv >> 8;
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-      R.ha[ct] = row[ct][a];
-      R.la[ct] = row[ct][SG_PP + a];
-      R.hb[ct] = *reinterpret_cast<const u32x4*>(row[ct] + B0);
-      R.lb[ct] = *reinterpret_cast<const u32x4*>(row[ct] + SG_PP + B0);
-    }
+    const uint16_t* r = row + 16 * ct * SG_MS;
+    R.ha = r[a];
+    R.la = r[SG_PP + a];
+    R.hb = *reinterpret_cast<const u32x4*>(r + B0);
+    R.lb = *reinterpret_cast<const u32x4*>(r + SG_PP + B0);
   };
-  auto make_b = [&](const Maps& R, int ct, f16x8& bh, f16x8& bl) {
-    const uint32_t ha = R.ha[ct], la = R.la[ct];
+  auto make_b = [&](const Maps& R, f16x8& bh, f16x8& bl) {
+    const uint32_t ha = R.ha, la = R.la;
     const f16x2 xa = __builtin_bit_cast(f16x2, ha | (ha << 16)), ya = __builtin_bit_cast(f16x2, la | (la << 16));
     u32x4 H4, L4;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       // vector elements go through scalars first: a bit_cast of the element itself is
       // dropped by the compiler
-      const uint32_t wb = R.hb[ct][k], vb = R.lb[ct][k];
+      const uint32_t wb = R.hb[k], vb = R.lb[k];
       const f16x2 xb = __builtin_bit_cast(f16x2, wb), yb = __builtin_bit_cast(f16x2, vb);
       f16x2 Hh = xa * xb;
       uint32_t Hb = __builtin_bit_cast(uint32_t, Hh);
@@ -441,88 +440,81 @@ __global__ __launch_bounds__(64 * SG_NW) void k_pair_adjoint_split(int P, int np
     bl = __builtin_bit_cast(f16x8, L4);
   };
   auto read_a = [&](int t, f16x8* ah, f16x8* al) {
-    const int buf = (t / SG_KC) & 1, gl = 2 * (t % SG_KC) + h;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      ah[mt] = __builtin_bit_cast(f16x8, L.a[buf][gl][0][32 * mt + c]);
-      al[mt] = __builtin_bit_cast(f16x8, L.a[buf][gl][1][32 * mt + c]);
+    for (int mt = 0; mt < NT; ++mt) {
+      ah[mt] = __builtin_bit_cast(f16x8, L.a[t & 1][h][0][16 * mt + c]);
+      al[mt] = __builtin_bit_cast(f16x8, L.a[t & 1][h][1][16 * mt + c]);
     }
   };
   // Software pipeline: the A operands, map words and pair products of step t + 1 are read
   // and formed among the MFMAs of step t (for the last step, those of the last step again,
-  // unused).  A chunks: chunks 0 and 1 are staged before the loop; in chunk ch, a barrier
-  // before its last step (all waves are then past their reads of chunk ch's operands, and
-  // chunk ch + 1 is visible) is followed by the store of chunk ch + 2 into chunk ch's buffer.
+  // unused).  A chunks: chunks 0 and 1 are staged before the loop; in step t a barrier
+  // (all waves are then past their reads of chunk t's operands, and chunk t + 1 is visible)
+  // is followed by the store of chunk t + 2 into chunk t's buffer.
   load_chunk(0);
   store_chunk(0);
   load_chunk(1);
   store_chunk(1);
   load_chunk(2);
   __syncthreads();   // maps, group table, chunks 0 and 1
-  f16x8 bh[2], bl[2], ah[MT], al[MT];
-  {
-    Maps R0;
-    read_maps(0, R0);
+  f16x8 bh[4], bl[4], ah[NT], al[NT];
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) make_b(R0, ct, bh[ct], bl[ct]);
-    read_a(0, ah, al);
+  for (int ct = 0; ct < 4; ++ct) {
+    Maps R;
+    read_maps(group(0), ct, R);
+    make_b(R, bh[ct], bl[ct]);
   }
-  auto chunk = [&](int ch) {
+  read_a(0, ah, al);
+  int link = 0;
+  for (int t = 0; t < nch; ++t) {
+    const int tn = min(t + 1, nch - 1);
+    __syncthreads();
+    if (t + 2 < nch) store_chunk(t & 1);
+    load_chunk(t + 3);
+    const int gv = group(tn);
+    f16x8 ahn[NT], aln[NT];
+    read_a(tn, ahn, aln);
+    Maps Rn[2];
+    read_maps(gv, 0, Rn[0]);
 #pragma unroll
-    for (int kk = 0; kk < SG_KC; ++kk) {
-      const int t = ch * SG_KC + kk;
-      const int tn = min(t + 1, nk - 1);
-      if (kk == SG_KC - 1) {
-        __syncthreads();
-        if (ch + 2 < nch) store_chunk(ch & 1);
-        load_chunk(ch + 3);
-      }
-      Maps Rn;
-      read_maps(tn, Rn);
-      f16x8 ahn[MT], aln[MT];
-      read_a(tn, ahn, aln);
+    for (int ct = 0; ct < 4; ++ct) {
+      if (ct < 3) read_maps(gv, ct + 1, Rn[(ct + 1) & 1]);
+      // product by product over the row tiles, so that consecutive MFMAs feed different sums
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
+      for (int mt = 0; mt < NT; ++mt) cc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[mt], bh[ct], cc[mt][ct], 0, 0, 0);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          cc[mt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[mt], bh[ct], cc[mt][ct], 0, 0, 0);
-          cc[mt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[mt], bl[ct], cc[mt][ct], 0, 0, 0);
-          cc[mt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[mt], bh[ct], cc[mt][ct], 0, 0, 0);
-        }
-        make_b(Rn, ct, bh[ct], bl[ct]);
-      }
+      for (int mt = 0; mt < NT; ++mt) cc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[mt], bl[ct], cc[mt][ct], 0, 0, 0);
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        ah[mt] = ahn[mt];
-        al[mt] = aln[mt];
-      }
+      for (int mt = 0; mt < NT; ++mt) cc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[mt], bh[ct], cc[mt][ct], 0, 0, 0);
+      make_b(Rn[ct & 1], bh[ct], bl[ct]);
     }
-  };
-  // chains of SG_CH staged chunks join the running sums
-  for (int ch0 = 0; ch0 < nch; ch0 += SG_CH) {
 #pragma unroll
-    for (int j = 0; j < SG_CH; ++j)
-      if (ch0 + j < nch) chunk(ch0 + j);
+    for (int mt = 0; mt < NT; ++mt) {
+      ah[mt] = ahn[mt];
+      al[mt] = aln[mt];
+    }
+    if (++link == SG_CH || t + 1 == nch) {   // chains of SG_CH steps join the running sums
+      link = 0;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+      for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
-        acc[mt][ct] += cc[mt][ct];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) cc[mt][ct][j] = 0.f;
-      }
+        for (int ct = 0; ct < 4; ++ct) {
+          acc[mt][ct] += cc[mt][ct];
+          cc[mt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
   }
   const float up = sc[s].y;   // 2^E
 #pragma unroll
-  for (int ct = 0; ct < 2; ++ct) {
-    const int x = x0 + wv * 64 + 32 * ct + c;
+  for (int ct = 0; ct < 4; ++ct) {
+    const int x = x0 + wv * 64 + 16 * ct + c;
     if (x >= npix) continue;
     const float wx = w[x];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int u = 32 * mt + 8 * (j / 4) + 4 * h + j % 4;
+      for (int j = 0; j < 4; ++j) {
+        const int u = 16 * mt + 4 * h + j;
         if (u < P) G[((size_t)s * P + u) * npix + x] = (wx * acc[mt][ct][j]) * up;
       }
   }
@@ -557,12 +549,13 @@ hipError_t launch_pair_adjoint(const modal_ctx* c, const void* maps, const void*
     hipLaunchKernelGGL(k_adj_ksplit, dim3(ngp, S), dim3(64), 0, st, c->P, c->npairs, ng, c->t.pair_of, c->t.mscale,
                        sc, (const double*)K, Ks, grp);
     const dim3 grid((c->npix + SG_PX - 1) / SG_PX, S);
-    if (c->P <= 32)
-      hipLaunchKernelGGL(k_pair_adjoint_split<1>, grid, dim3(64 * SG_NW), 0, st, c->P, c->npix, ngp, grp,
-                         (const float*)maps, c->t.w32, c->t.mscale, sc, Ks, (float*)G);
-    else
-      hipLaunchKernelGGL(k_pair_adjoint_split<2>, grid, dim3(64 * SG_NW), 0, st, c->P, c->npix, ngp, grp,
-                         (const float*)maps, c->t.w32, c->t.mscale, sc, Ks, (float*)G);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(64 * SG_NW), 0, st, c->P, c->npix, ngp, grp, (const float*)maps, c->t.w32,
+                         c->t.mscale, sc, Ks, (float*)G);
+    };
+    if (c->P <= 16) launch(k_pair_adjoint_split<1>);
+    else if (c->P <= 32) launch(k_pair_adjoint_split<2>);
+    else launch(k_pair_adjoint_split<3>);
     return hipGetLastError();
   }
   if (is_f64(c)) {
