@@ -40,13 +40,16 @@ __global__ __launch_bounds__(256) void k_weight_planes(int npix, int nk, const T
 // group, y: the l tile), so that every Z and a_lm element it loads feeds PT or ST products; its MW waves take the m of the
 // sum in turn (m = w, w + MW, ...) and their partial sums are added through LDS.  The
 // lanes of a wave read consecutive l of one m row of the m-major packing: coalesced.
-constexpr int PT = 8;
+// Large problems: 8 pairs and four waves.  With fewer workgroups than half the CUs the chain of a
+// wave's m bounds it (a load's latency each): 2 pairs and 16 waves, a quarter of the chain and four
+// times the workgroups.  With k_lin_l, 8 and 4 against 2 and 16: l_max 150, 91 pairs, 3 maps (36
+// workgroups) 41.6 and 27.0 us; 300, 136, 4 (85) 74.2 and 57.8; 300, 210, 8 (135) 88.5 and 91.7; 500,
+// 465, 8 (472) 218 and 320; 1000, 820, 8 (1648) 1.19 and 1.88 ms.
 constexpr int ST = 8;
 constexpr int LT = 64;
-constexpr int MW = 4;
-constexpr int RED = 16;   // accumulators per LDS reduction round
 
-template <typename T>
+// RED: accumulators per LDS reduction round
+template <typename T, int PT, int MW, int RED>
 __global__ __launch_bounds__(LT * MW) void k_lin_x(int lmax, int nalm, int npairs, int S,
                                                    const typename vec2<T>::type* __restrict__ Z,
                                                    const typename vec2<T>::type* __restrict__ alm,
@@ -259,13 +262,19 @@ hipError_t launch_lin_harmonic(const modal_ctx* c, const void* Z, const void* al
                                hipStream_t st) {
   if (c->P > 64) return hipErrorInvalidValue;
   // pair groups fastest: the workgroups running together share one l tile of a_lm in L2
-  dim3 gx((c->npairs + PT - 1) / PT, (c->lmax + LT) / LT, (S + ST - 1) / ST);
-  if (is_f64(c))
-    hipLaunchKernelGGL(k_lin_x<double>, gx, dim3(LT * MW), 0, st, c->lmax, c->nalm, c->npairs, S, (const double2*)Z,
-                       (const double2*)alm, X);
-  else
-    hipLaunchKernelGGL(k_lin_x<float>, gx, dim3(LT * MW), 0, st, c->lmax, c->nalm, c->npairs, S, (const float2*)Z,
-                       (const float2*)alm, X);
+  auto grid = [&](int pt) { return dim3((c->npairs + pt - 1) / pt, (c->lmax + LT) / LT, (S + ST - 1) / ST); };
+  const dim3 wide = grid(8), narrow = grid(2);
+  const bool few = (size_t)wide.x * wide.y * wide.z < 128;
+  auto launch = [&](auto kernel, dim3 g, int mw, auto* z) {
+    hipLaunchKernelGGL(kernel, g, dim3(LT * mw), 0, st, c->lmax, c->nalm, c->npairs, S, z, (decltype(z))alm, X);
+  };
+  if (is_f64(c)) {
+    if (few) launch(k_lin_x<double, 2, 16, 4>, narrow, 16, (const double2*)Z);
+    else launch(k_lin_x<double, 8, 4, 16>, wide, 4, (const double2*)Z);
+  } else {
+    if (few) launch(k_lin_x<float, 2, 16, 4>, narrow, 16, (const float2*)Z);
+    else launch(k_lin_x<float, 8, 4, 16>, wide, 4, (const float2*)Z);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_lin_l, dim3(c->npairs, S), dim3(64), 0, st, c->lmax, c->npairs, c->P, c->t.qw64, X, L);

@@ -263,3 +263,26 @@ def test_bf16_adjoint_edges(lmax, ntheta, nphi, P, S):
     for i in range(S):
         ref = om.vjp(a[i], case.cl, case.q, case.grid, None, cot[i])[0]
         assert np.linalg.norm(got[i] - ref) <= 1e-4 * np.linalg.norm(ref)   # the map bound of these contexts
+
+
+# Linear term in harmonic space: workgroup counts on both sides of 128 (2 pairs and 16 waves below, 8
+# and 4 from there), pair counts off a multiple of 2 and of 8, l_max on both sides of an l tile
+# of 64 and below the 16 waves, more maps than a workgroup takes.
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", [(2, 3, 6, 1, 1), (9, 14, 30, 2, 9), (63, 66, 130, 5, 3),
+                                                  (64, 66, 130, 10, 12), (64, 66, 130, 10, 80)])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_linear_apply_edges(lmax, ntheta, nphi, P, S, prec):
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 77)
+    print(f"[case] linear apply {prec} lmax={lmax} P={P} S={S}", flush=True)
+    a, mc = case.alms(0, S), case.alms(200, 2)
+    c = _ctx(case, prec)
+    st = c.linear_state()
+    c.linear_reset(st)
+    c.linear_accumulate(st, mc)
+    c.linear_finalize(st)
+    got = c.linear_apply(st, a).cpu().numpy()
+    V = om.pair_means(case.maps(mc))
+    tol = 1e-5 if prec == "f32" else 1e-10   # the bounds of the linear-term tests
+    for i in {0, S // 2, S - 1}:
+        ref = om.linear_term(case.maps(a[i:i + 1])[0], case.grid.w, V)
+        assert np.abs(got[i] - ref).max() <= tol * np.abs(ref).max()
