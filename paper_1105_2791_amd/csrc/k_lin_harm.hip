@@ -42,9 +42,9 @@ __global__ __launch_bounds__(256) void k_weight_planes(int npix, int nk, const T
 // lanes of a wave read consecutive l of one m row of the m-major packing: coalesced.
 // Large problems: 8 pairs and four waves.  With fewer workgroups than half the CUs the chain of a
 // wave's m bounds it (a load's latency each): 2 pairs and 16 waves, a quarter of the chain and four
-// times the workgroups.  With k_lin_l, 8 and 4 against 2 and 16: l_max 150, 91 pairs, 3 maps (36
-// workgroups) 41.6 and 27.0 us; 300, 136, 4 (85) 74.2 and 57.8; 300, 210, 8 (135) 88.5 and 91.7; 500,
-// 465, 8 (472) 218 and 320; 1000, 820, 8 (1648) 1.19 and 1.88 ms.
+// times the workgroups.  8 and 4 against 2 and 16: l_max 150, 91 pairs, 3 maps (36 workgroups) 31 and
+// 16 us; 300, 136, 4 (85) 16 us less; 300, 210, 8 (135) 3 us more; 500, 465, 8 (472) 163 and 265; 1000,
+// 820, 8 (1648) 0.96 and 1.66 ms.
 constexpr int ST = 8;
 constexpr int LT = 64;
 
@@ -118,26 +118,72 @@ __global__ __launch_bounds__(LT * MW) void k_lin_x(int lmax, int nalm, int npair
   }
 }
 
-// L[s][pair][t] = sum_l qw_t(l) X[s][pair][l]; one workgroup per (map, pair), one
-// thread per mode, the X row staged in LDS.
-__global__ __launch_bounds__(64) void k_lin_l(int lmax, int npairs, int P, const double* __restrict__ qw,
-                                              const double* __restrict__ X, double* __restrict__ L) {
-  const int pair = blockIdx.x, s = blockIdx.y;
-  const int t = threadIdx.x;
-  __shared__ double xs[256];
-  const double* xrow = X + ((size_t)s * npairs + pair) * (lmax + 1);
-  double acc = 0.0;
-  for (int l0 = 0; l0 <= lmax; l0 += 256) {
-    const int n = min(256, lmax + 1 - l0);
-    __syncthreads();
-    for (int i = t; i < n; i += 64) xs[i] = xrow[l0 + i];
-    __syncthreads();
-    if (t < P) {
-      const double* q = qw + (size_t)t * (lmax + 1) + l0;
-      for (int i = 0; i < n; ++i) acc = fma(q[i], xs[i], acc);
-    }
+// L[row][t] = sum_l qw_t(l) X[row][l], row = (map, pair): a product with K = l on the FP64 matrix
+// cores (v_mfma_f64_16x16x4_f64: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16], accumulator
+// register r is D[4 r + l / 16][l % 16]).  A workgroup covers 16 rows and all modes (NT tiles of
+// 16); its four waves take blocks of 32 l in turn and their sums are added through LDS.  In a
+// block the inner index is dealt so that a lane reads 8 consecutive l of its row and its mode.
+// Bound by reading X.  6560 rows, 40 modes, l_max 1000: 216 us with a wave per row, a mode per lane
+// and one chain over l, 53 now; 3720 rows, 30 modes, l_max 500: 52 and 11.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <int NT>
+__global__ __launch_bounds__(256) void k_lin_l(int lmax, int rows, int P, const double* __restrict__ qw,
+                                               const double* __restrict__ X, double* __restrict__ L) {
+  __shared__ double red[3][4 * NT][64];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l16 = lane & 15, kq = lane >> 4, r0 = blockIdx.x * 16;
+  const size_t n = lmax + 1;
+  const double* xr = X + min(r0 + l16, rows - 1) * n;
+  const double* qr[NT];
+  f64x4 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    qr[t] = qw + min(16 * t + l16, P - 1) * n;
+    acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
   }
-  if (t < P) L[((size_t)s * npairs + pair) * P + t] = acc;
+  for (int k0 = 32 * wv; k0 <= lmax; k0 += 128) {
+    const int k = k0 + 8 * kq;
+    double a[8], b[NT][8];
+    if (k0 + 31 <= lmax) {   // uniform
+#pragma unroll
+      for (int i = 0; i < 8; ++i) a[i] = xr[k + i];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[t][i] = qr[t][k + i];
+    } else {                 // indices clamped, values past l_max zero
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const double v = xr[min(k + i, lmax)];
+        a[i] = k + i <= lmax ? v : 0.0;
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[t][i] = qr[t][min(k + i, lmax)];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[t][i], acc[t], 0, 0, 0);
+  }
+  if (wv > 0) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wv - 1][4 * t + r][lane] = acc[t][r];
+  }
+  __syncthreads();
+  if (wv > 0) return;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double v = acc[t][r] + red[0][4 * t + r][lane] + red[1][4 * t + r][lane] + red[2][4 * t + r][lane];
+      const int row = r0 + 4 * r + kq, mode = 16 * t + l16;
+      if (row < rows && mode < P) L[(size_t)row * P + mode] = v;
+    }
 }
 
 // The adjoint of the linear term with respect to a_lm.  With the slot matrix K of the
@@ -277,7 +323,14 @@ hipError_t launch_lin_harmonic(const modal_ctx* c, const void* Z, const void* al
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_lin_l, dim3(c->npairs, S), dim3(64), 0, st, c->lmax, c->npairs, c->P, c->t.qw64, X, L);
+  const int rows = S * c->npairs;
+  auto modes = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((rows + 15) / 16), dim3(256), 0, st, c->lmax, rows, c->P, c->t.qw64, X, L);
+  };
+  if (c->P <= 16) modes(k_lin_l<1>);
+  else if (c->P <= 32) modes(k_lin_l<2>);
+  else if (c->P <= 48) modes(k_lin_l<3>);
+  else modes(k_lin_l<4>);
   return hipGetLastError();
 }
 

@@ -286,3 +286,23 @@ def test_linear_apply_edges(lmax, ntheta, nphi, P, S, prec):
     for i in {0, S // 2, S - 1}:
         ref = om.linear_term(case.maps(a[i:i + 1])[0], case.grid.w, V)
         assert np.abs(got[i] - ref).max() <= tol * np.abs(ref).max()
+
+
+# The modes of the linear term: one to four tiles of 16 modes (P 16 | 17, 33, 49), l in a single
+# block of 32, at its edge and in blocks for every wave and more, rows off a multiple of 16.
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", [(30, 33, 64, 16, 1), (31, 33, 64, 17, 2), (32, 34, 66, 33, 1),
+                                                  (9, 14, 30, 49, 1), (129, 131, 260, 4, 2), (160, 162, 322, 3, 1)])
+def test_linear_modes_edges(lmax, ntheta, nphi, P, S):
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 78)
+    print(f"[case] linear modes lmax={lmax} P={P} S={S}", flush=True)
+    a, mc = case.alms(0, S), case.alms(200, 2)
+    c = _ctx(case, "f64")
+    st = c.linear_state()
+    c.linear_reset(st)
+    c.linear_accumulate(st, mc)
+    c.linear_finalize(st)
+    got = c.linear_apply(st, a).cpu().numpy()
+    V = om.pair_means(case.maps(mc))
+    for i in range(S):
+        ref = om.linear_term(case.maps(a[i:i + 1])[0], case.grid.w, V)
+        assert np.abs(got[i] - ref).max() <= 1e-10 * np.abs(ref).max()   # the bound of the linear-term tests
