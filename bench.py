@@ -460,9 +460,9 @@ def run_shapes(args):
         times[name] = 1e3 * (time.perf_counter() - t0) / args.steps
     nmu = (3 * lmax + 2) // 2
     n = ctx.nmax
-    # the 3 x 3 permanent expanded along its third row, its 2 x 2 permanents shared
-    # across the rows of a group: 1 mul + 2 fma, then the weighted fma, per (pair of modes, node)
-    flop = n * (n + 1) / 2 * nmu * 7.0
+    # the sums over the nodes of the products of every three pair functions, each formed once
+    npairs = P * (P + 1) // 2
+    flop = 2.0 * nmu * (npairs * (npairs + 1) * (npairs + 2) // 6)
     t = times["ideal_covariance"] * 1e-3
     line = {
         "metric": "theory side: alpha_n (3 separable terms) and ideal covariance, ms per call", "unit": "ms",
@@ -470,7 +470,7 @@ def run_shapes(args):
         "warmup": args.warmup, "dtype": "f64", "data": "synthetic",
         "config": {"workload": f"lmax={lmax} P={P} nmax={n}, {nmu} Gauss-Legendre nodes in mu"},
         "ms": times,
-        "roofline": {"bound": "alu", "kernel": "ideal_covariance (k_ideal_cov dominant)", "per_launch": flop,
+        "roofline": {"bound": "alu", "kernel": "ideal_covariance (k_node_triples dominant)", "per_launch": flop,
                      "per_launch_unit": "flop", "achieved": flop / t / 1e12, "peak": PEAK["f64_vec"] / 1e12,
                      "unit": "TFLOP/s", "frac": flop / t / PEAK["f64_vec"], "traffic": None},
         # the ideal covariance only: the oracle's alpha is a triple sum over an l_max^3 table

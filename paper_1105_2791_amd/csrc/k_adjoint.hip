@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256) void k_pair_adjoint_f32(int P, int npairs, int
 // A workgroup is 4 waves and 256 pixels of one sky (70 KB of LDS: two workgroups per CU).
 // Bound by the matrix cores and the packed products together (they overlap in part: 12 products of
 // 32 x 32 x 16 and 144 vector instructions take 646 cycles of a SIMD with two waves, 460 and 406
-// alone), so the row tiles follow P: 8 skies of 1536 x 3072 pixels, P 40: 6.8 ms with rows in tiles
+// alone), so the row tiles follow P: 4 skies of 1536 x 3072 pixels, P 40: 6.8 ms with rows in tiles
 // of 32 and three dependent products in turn, 6.1 now; P 30, 4 skies of 768 x 1536: the whole
 // gradient 2.46 -> 2.15 ms, P 16 1.64 -> 1.43.
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
