@@ -63,13 +63,28 @@ __device__ inline d4 block_product(d4 acc, const double (*X)[DS], int x0, int xc
   return acc;   // register r of lane l: row 4 r + l / 16, column l % 16
 }
 
-__global__ __launch_bounds__(256) void k_potrf_diag(int n, double* __restrict__ A, int k0, int kb, int* flag) {
+// copy: the block below, A[k0 + NB ..][k0 ..], is left transposed in the upper triangle for
+// k_panel_update, whose workgroups all need it while one of them overwrites it.
+__global__ __launch_bounds__(256) void k_potrf_diag(int n, double* __restrict__ A, int k0, int kb, int* flag,
+                                                    bool copy) {
   __shared__ double a[NB][DS];
   __shared__ double Wf[NB][DS];   // W = L^-1 (diagonal blocks first, then the rest)
   __shared__ double T[NB][DS];    // block products of the inverse
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int l16 = lane & 15, kq = lane >> 4;
-  double av[NB * NB / 256];
+  double av[NB * NB / 256], bv[NB * NB / 256];
+  if (copy) {   // uniform
+#pragma unroll
+    for (int u = 0; u < NB * NB / 256; ++u) {
+      const int e = t + 256 * u, r = e / NB, c = e - r * NB;
+      bv[u] = A[(size_t)min(k0 + NB + r, n - 1) * n + k0 + c];
+    }
+#pragma unroll
+    for (int u = 0; u < NB * NB / 256; ++u) {
+      const int e = t + 256 * u, r = e / NB, c = e - r * NB;
+      if (k0 + NB + r < n) A[(size_t)(k0 + c) * n + k0 + NB + r] = bv[u];
+    }
+  }
 #pragma unroll
   for (int u = 0; u < NB * NB / 256; ++u) {
     const int e = t + 256 * u, r = e / NB, c = e - r * NB;
@@ -490,6 +505,104 @@ __global__ __launch_bounds__(256) void k_panel_mfma(int n, double* __restrict__ 
       }
 }
 
+// The panel of block column k0 (as k_panel_mfma) and its update of the next block column,
+//   P = A[rows, k0 ..] W^T,   A[rows, k2 ..] -= P P_0^T,   k2 = k0 + NB,
+// in one launch: every workgroup forms P_0, the panel of the rows k2 .., for itself from the copy
+// that k_potrf_diag left (a product of 64^3 against a launch and the wait for the panel).
+// Bound by latency, on the chain of the factorization.  The estimator at 4960 modes: 8.95 ms with the
+// panel and the update as two launches, 8.76 now.
+__global__ __launch_bounds__(256) void k_panel_update(int n, double* __restrict__ A, int k0) {
+  __shared__ double X[NB][DS], Y[NB][DS], Wt[NB][DS];   // the workgroup's rows (then P), rows k2 .. (then P_0), W^T
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  const int l16 = lane & 15, kq = lane >> 4, wr = wv >> 1, wc = wv & 1;
+  const int k2 = k0 + NB, rbase = k2 + blockIdx.x * NB;
+  double xv[NB * NB / 256], yv[NB * NB / 256], wv_[NB * NB / 256];
+#pragma unroll
+  for (int u = 0; u < NB * NB / 256; ++u) {
+    const int e = tid + 256 * u, r = e / NB, c = e - r * NB;
+    xv[u] = A[(size_t)min(rbase + r, n - 1) * n + k0 + c];
+    yv[u] = A[(size_t)(k0 + r) * n + min(k2 + c, n - 1)];
+    wv_[u] = A[(size_t)(k0 + min(r, c)) * n + k0 + c];
+  }
+  d4 cv[2][2];
+#pragma unroll
+  for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = min(rbase + 32 * wr + 16 * ta + 4 * r + kq, n - 1), j = min(k2 + 32 * wc + 16 * tb + l16, n - 1);
+        cv[ta][tb][r] = -A[(size_t)i * n + j];
+      }
+#pragma unroll
+  for (int u = 0; u < NB * NB / 256; ++u) {
+    const int e = tid + 256 * u, r = e / NB, c = e - r * NB;
+    X[r][c] = rbase + r < n ? xv[u] : 0.0;
+    Y[c][r] = k2 + c < n ? yv[u] : 0.0;
+    Wt[r][c] = r == c ? 1.0 / wv_[u] : (r < c ? wv_[u] : 0.0);
+  }
+  __syncthreads();
+  d4 p[2][2], q[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) p[a][b] = q[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int ks = 0; ks < NB / 4; ++ks) {
+    const int kk = 4 * ks + kq;
+    double a[2], c[2], b[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      a[t] = X[32 * wr + 16 * t + l16][kk];
+      c[t] = Y[32 * wr + 16 * t + l16][kk];
+      b[t] = Wt[kk][32 * wc + 16 * t + l16];
+    }
+#pragma unroll
+    for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb) {
+        p[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], p[ta][tb], 0, 0, 0);
+        q[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[ta], b[tb], q[ta][tb], 0, 0, 0);
+      }
+  }
+  __syncthreads();   // every read of the rows is done
+#pragma unroll
+  for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int ri = 32 * wr + 16 * ta + 4 * r + kq, c = 32 * wc + 16 * tb + l16;
+        X[ri][c] = p[ta][tb][r];
+        Y[ri][c] = q[ta][tb][r];
+        if (rbase + ri < n) A[(size_t)(rbase + ri) * n + k0 + c] = p[ta][tb][r];
+      }
+  __syncthreads();
+#pragma unroll 4
+  for (int ks = 0; ks < NB / 4; ++ks) {
+    const int kk = 4 * ks + kq;
+    double a[2], b[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      a[t] = X[32 * wr + 16 * t + l16][kk];
+      b[t] = Y[32 * wc + 16 * t + l16][kk];
+    }
+#pragma unroll
+    for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb) cv[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], cv[ta][tb], 0, 0, 0);
+  }
+#pragma unroll
+  for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = rbase + 32 * wr + 16 * ta + 4 * r + kq, j = k2 + 32 * wc + 16 * tb + l16;
+        if (i < n && j <= i) A[(size_t)i * n + j] = -cv[ta][tb][r];
+      }
+}
+
 __global__ void k_copy_lower(int n, const double* __restrict__ src, double* __restrict__ dst) {
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (size_t)n * n) return;
@@ -541,13 +654,12 @@ hipError_t launch_cholesky_lookahead(int n, double* A, int* flag, hipStream_t st
   // second half's columns, then the second half's diagonal block and panel.
   auto factor2 = [&](int k, hipStream_t s) {
     const int kb = n - k < NB ? n - k : NB;
-    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, n, A, k, kb, flag);
-    if (n - k - kb > 0) hipLaunchKernelGGL(k_panel_mfma, dim3((n - k - kb + NB - 1) / NB), dim3(256), 0, s, n, A, k, kb);
     const int k2 = k + NB;
+    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, n, A, k, kb, flag, k2 < n);
     if (k2 < n) {
-      update(k, NB, k2, 1, s);
+      hipLaunchKernelGGL(k_panel_update, dim3((n - k2 + NB - 1) / NB), dim3(256), 0, s, n, A, k);
       const int kb2 = n - k2 < NB ? n - k2 : NB;
-      hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, n, A, k2, kb2, flag);
+      hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, n, A, k2, kb2, flag, false);
       if (n - k2 - kb2 > 0)
         hipLaunchKernelGGL(k_panel_mfma, dim3((n - k2 - kb2 + NB - 1) / NB), dim3(256), 0, s, n, A, k2, kb2);
     }
