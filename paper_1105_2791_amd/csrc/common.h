@@ -228,9 +228,9 @@ hipError_t launch_copy_lower(int n, const double* src, double* dst, hipStream_t 
 // blocked right-looking Cholesky with look-ahead: the next diagonal block and panel run on
 // side while the rest of the trailing update runs on st (ev_a, ev_p order them); st is
 // joined with side when it returns.  With nrhs > 0 the solves L Y = B of nrhs right-hand
-// sides stored as rows of B [nrhs][n] run too, each block's step right after the block is
-// factored (the inverted diagonal block and its panel); Y gets the solution, B is
-// overwritten below the blocks
+// sides stored as rows of B [nrhs][n] run too, a block column's steps on st during the
+// factorization of the next (the inverted diagonal blocks and their panels); Y gets the
+// solution, B is overwritten below the blocks.  A's strict upper triangle is scratch
 hipError_t launch_cholesky_lookahead(int n, double* A, int* flag, hipStream_t st, hipStream_t side, hipEvent_t ev_a,
                                      hipEvent_t ev_p, int nrhs = 0, double* B = nullptr, double* Y = nullptr);
 // solve L Y = B in place for nrhs right-hand sides stored as rows of B [nrhs][n]
