@@ -104,14 +104,26 @@ __device__ inline void store_rings(const f32x4 (&acc)[2][NRT][4], float* stg, in
   }
 }
 
+// The largest byte offset of a coefficient from its block's first sky fits in 32 bits: a block's
+// 32 sequences (s, p) reach at most 1 + 30 / P skies past the one it starts in.
+constexpr bool offsets_fit(int lmax, int P, int S) {
+  const uint64_t nalm = (uint64_t)(lmax + 1) * (lmax + 2) / 2;
+  const uint64_t past = S - 1 < 1 + 30 / P ? S - 1 : 1 + 30 / P;
+  return 8 * (past * nalm + lmax) + 4 <= UINT32_MAX;
+}
+static_assert(offsets_fit(5883, 1, 1000) && !offsets_fit(5884, 1, 32) && offsets_fit(5884, 1, 31), "32 skies of P 1");
+static_assert(offsets_fit(8190, 2, 1000) && !offsets_fit(8191, 2, 1000) && offsets_fit(8191, 2, 16), "17 skies of P 2");
+
 // A thread's part of the coefficient tile: index ci of both parities, columns cc + 8 u (eight
 // columns x four l groups x two k over a wave: two lanes per bank, 64-byte runs of l).  The
-// offsets are 32-bit byte offsets from uniform bases (the block's first sky, the mode
-// functions), so that a load costs one add; 64-bit addresses formed per load were most of the
-// kernel's vector instructions.  Columns past the last repeat it and are not stored.
+// offsets are byte offsets from uniform bases (the block's first sky, the mode functions), in 32
+// bits (Off) where they fit, so that a load costs one add; 64-bit addresses formed per load were
+// most of the kernel's vector instructions.  Columns past the last repeat it and are not stored.
+template <typename Off>
 struct CoefLoader {
   int ci, ck, cc, kg;
-  uint32_t ao[CPT], qo[CPT];
+  Off ao[CPT];
+  uint32_t qo[CPT];
   const char *ab, *qb;
   float a[CPT][2], q[CPT][2];
   __device__ inline void init(int wv, int lane, int c0, int ncols, int P, int nalm, int lmax, const float* alm,
@@ -126,7 +138,7 @@ struct CoefLoader {
 #pragma unroll
     for (int u = 0; u < CPT; ++u) {   // column parity (re, im) is cc's: 8 u is even
       const int sq = min(c0 + cc + 8 * u, ncols - 1) >> 1, s = sq / P;
-      ao[u] = (uint32_t)(s - s0) * (uint32_t)nalm * 8u + 4u * (cc & 1);   // at most 32 skies: below 2^32
+      ao[u] = (Off)(s - s0) * (Off)nalm * 8u + 4u * (cc & 1);
       qo[u] = (uint32_t)(sq - s * P) * (uint32_t)(lmax + 1) * 4u;
     }
   }
@@ -153,7 +165,7 @@ struct CoefLoader {
 
 // NRT: ring tiles of 16 per wave.  The host spreads the rings evenly over the workgroups and
 // waves: 384 north rings are two workgroups of four waves of 48 rings, not one and a half of 64.
-template <int NRT>
+template <int NRT, typename Off>
 __global__ __launch_bounds__(256, 2) void k_legendre_f32(int lmax, int ntheta, int nrp, int P, int ncols, int nalm,
                                                          const double* __restrict__ x, const double* __restrict__ rec,
                                                          const double* __restrict__ seed,
@@ -196,7 +208,7 @@ __global__ __launch_bounds__(256, 2) void k_legendre_f32(int lmax, int ntheta, i
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[a][b][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  CoefLoader cl;
+  CoefLoader<Off> cl;
   cl.init(wv, lane, c0, ncols, P, nalm, lmax, alm, qw, off, m);
 
   // chunks start at l = m + 64 k so that parity(l - m) = parity(l - l0)
@@ -386,7 +398,7 @@ __global__ __launch_bounds__(256, 2) void k_legendre_f32_tab(int lmax, int nthet
     for (int b = 0; b < NRT; ++b)
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[a][b][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  CoefLoader cl;
+  CoefLoader<uint32_t> cl;
   cl.init(wv, lane, c0, ncols, P, nalm, lmax, alm, qw, off, m);
   const int kfirst = (lmin > m) ? (lmin - m) / LCH : 0, nch = m_chunks(lmax, m);
   const f32x4* rec = reinterpret_cast<const f32x4*>(tab + chunks_before(lmax, m) * ntile * TREC) + 4 * lane;
@@ -450,8 +462,10 @@ __global__ __launch_bounds__(256, 2) void k_legendre_f32_tab(int lmax, int nthet
 size_t legendre_mfma_lds() { return kLds; }
 
 hipError_t legendre_mfma_set_lds(size_t bytes) {
-  const void* f[] = {(const void*)k_legendre_f32<1>,     (const void*)k_legendre_f32<2>,
-                     (const void*)k_legendre_f32<3>,     (const void*)k_legendre_f32<4>,
+  const void* f[] = {(const void*)k_legendre_f32<1, uint32_t>, (const void*)k_legendre_f32<2, uint32_t>,
+                     (const void*)k_legendre_f32<3, uint32_t>, (const void*)k_legendre_f32<4, uint32_t>,
+                     (const void*)k_legendre_f32<1, uint64_t>, (const void*)k_legendre_f32<2, uint64_t>,
+                     (const void*)k_legendre_f32<3, uint64_t>, (const void*)k_legendre_f32<4, uint64_t>,
                      (const void*)k_legendre_f32_tab<1>, (const void*)k_legendre_f32_tab<2>,
                      (const void*)k_legendre_f32_tab<3>, (const void*)k_legendre_f32_tab<4>};
   for (const void* k : f) {
@@ -468,7 +482,8 @@ size_t legendre_mfma_tab_bytes(const modal_ctx* c) {
 // scratch: device memory that the call may overwrite (the maps that are formed next).  Lambda
 // comes from a table there when at least three column blocks share it (below that, building it
 // costs what running the recurrence in each block does: 72 us against 24 us a block at l_max
-// 500, 768 rings) and it fits, 16-byte aligned.
+// 500, 768 rings) and it fits, 16-byte aligned.  Skies too large for 32-bit offsets (32 of them in
+// a block from l_max 5884 on) take the recurrence with 64-bit ones.
 hipError_t launch_legendre_mfma(const modal_ctx* c, const void* alm, int S, void* F, void* scratch,
                                 size_t scratch_bytes, hipStream_t st) {
   if (c->prec != MODAL_F32) return hipErrorInvalidValue;
@@ -476,7 +491,8 @@ hipError_t launch_legendre_mfma(const modal_ctx* c, const void* alm, int S, void
   const int blocks = (c->nrp + NWAVE * RW - 1) / (NWAVE * RW);          // workgroups of at most 256 rings
   const int nrt = (c->nrp + blocks * NWAVE * 16 - 1) / (blocks * NWAVE * 16);   // 16-ring tiles per wave, <= 4
   const dim3 grid((ncols + NCOL - 1) / NCOL, blocks, c->lmax + 1);
-  const bool table = grid.x >= 3 && scratch && scratch_bytes >= legendre_mfma_tab_bytes(c) &&
+  const bool fit = offsets_fit(c->lmax, c->P, S);
+  const bool table = fit && grid.x >= 3 && scratch && scratch_bytes >= legendre_mfma_tab_bytes(c) &&
                      reinterpret_cast<uintptr_t>(scratch) % 16 == 0;
   if (table) {
     hipLaunchKernelGGL(k_lambda_records, dim3((c->nrp + 63) / 64, c->lmax + 1), dim3(64), 0, st, c->lmax, c->nrp, c->t.x,
@@ -498,10 +514,15 @@ hipError_t launch_legendre_mfma(const modal_ctx* c, const void* alm, int S, void
     hipLaunchKernelGGL(kernel, grid, dim3(256), kLds, st, c->lmax, c->ntheta, c->nrp, c->P, ncols, c->nalm, c->t.x,
                        c->t.rec, c->t.seed, c->t.lstart, c->t.qw32, (const float*)alm, (float2*)F);
   };
-  if (nrt == 1) launch(k_legendre_f32<1>);
-  else if (nrt == 2) launch(k_legendre_f32<2>);
-  else if (nrt == 3) launch(k_legendre_f32<3>);
-  else launch(k_legendre_f32<4>);
+  auto tiles = [&](auto o) {
+    using Off = decltype(o);
+    if (nrt == 1) launch(k_legendre_f32<1, Off>);
+    else if (nrt == 2) launch(k_legendre_f32<2, Off>);
+    else if (nrt == 3) launch(k_legendre_f32<3, Off>);
+    else launch(k_legendre_f32<4, Off>);
+  };
+  if (fit) tiles(uint32_t{});
+  else tiles(uint64_t{});
   return hipGetLastError();
 }
 

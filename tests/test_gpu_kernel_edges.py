@@ -306,3 +306,18 @@ def test_linear_modes_edges(lmax, ntheta, nphi, P, S):
     for i in range(S):
         ref = om.linear_term(case.maps(a[i:i + 1])[0], case.grid.w, V)
         assert np.abs(got[i] - ref).max() <= 1e-10 * np.abs(ref).max()   # the bound of the linear-term tests
+
+
+# FP32 synthesis of skies so large that the last of a block's 32 skies (P 1) lies past 32-bit byte
+# offsets from the first: each sky of a batch equals the sky alone (columns do not mix), bit for bit.
+def test_f32_synthesis_offsets_past_32_bits():
+    from paper_1105_2791_amd import ModalContext
+    lmax, ntheta, nphi, S = 5884, 5885, 12288, 32
+    assert 8 * (S - 1) * (lmax + 1) * (lmax + 2) // 2 > 2**32
+    print(f"[case] f32 synthesis lmax={lmax} {ntheta}x{nphi} P=1 S={S}", flush=True)
+    c = ModalContext(lmax, ntheta, nphi, 1, "f32", np.ones((1, lmax + 1)), np.ones(lmax + 1))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    a = torch.view_as_complex(torch.randn((S, c.nalm, 2), generator=g, device="cuda"))
+    got = c.filter_maps(a)
+    for s in (0, 30, 31):
+        assert torch.equal(got[s:s + 1], c.filter_maps(a[s:s + 1]))
