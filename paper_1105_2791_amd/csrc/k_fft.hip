@@ -423,8 +423,11 @@ __device__ inline void rg_order() {
 // the arguments), so that the index arithmetic of a specialised plan folds to constants
 // WPR: the waves that share a ring (lane counts through them); with two, every wave of the
 // workgroup runs the pass and barriers keep its order
+// Always inlined where the plan is compiled in: called, a pass of 47 x 8 x 8 keeps 296 bytes per lane
+// in memory.  A plan run from its arguments leaves it to the compiler (rg_pass_args): with every
+// radix inlined its kernels of 32 and 48 points hold one wave per SIMD instead of two.
 template <int R, int PTS, bool OUT = false, int KC = 0, int NSC = 0, int WPR = 1>
-__device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float2* twp, float2* out = nullptr) {
+__device__ __forceinline__ void rg_pass(float2* b, int K_, int Ns_, int lane, const float2* twp, float2* out = nullptr) {
   static_assert(WPR == 1 || KC, "shared rings: compiled-in plans only");
   constexpr int NB = KC ? (KC / R + 64 * WPR - 1) / (64 * WPR) : (PTS + R - 1) / R;
   const int K = KC ? KC : K_;
@@ -465,6 +468,11 @@ __device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float
   if (WPR == 1 || !OUT) rg_order<WPR>();
 }
 
+template <int R, int PTS, bool OUT = false>
+__device__ inline void rg_pass_args(float2* b, int K, int Ns, int lane, const float2* twp, float2* out = nullptr) {
+  rg_pass<R, PTS, OUT>(b, K, Ns, lane, twp, out);
+}
+
 // cos and sin of 2 pi j / 47, j < 47, rounded to float
 __device__ constexpr float kC47[47] = {
     1.0f, 0.991077488f, 0.964469175f, 0.920649887f, 0.860401579f, 0.784799385f, 0.695192428f,
@@ -494,7 +502,7 @@ __device__ constexpr float kS47[47] = {
 // program order, of two by a barrier), so the pass is in place.  Of two waves both form all
 // sums s, d and half the outputs each.
 template <int WPR = 1>
-__device__ inline void rg_pass47_first(float2* b, int lane, int half = 0) {
+__device__ __forceinline__ void rg_pass47_first(float2* b, int lane, int half = 0) {
   float2 x[47];
 #pragma unroll
   for (int r = 0; r < 47; ++r) x[r] = b[padr(lane + 64 * r)];
@@ -646,13 +654,13 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
       const bool direct = plan.radix[plan.nf - 1] == 8;
       for (int f = 0; f < plan.nf; ++f) {
         const int R = plan.radix[f];
-        if (direct && f == plan.nf - 1) rg_pass<8, PTS, true>(bw, K, Ns, lane, tf, dst);
-        else if (R == 8) rg_pass<8, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 4) rg_pass<4, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 2) rg_pass<2, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 3) rg_pass<3, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 5) rg_pass<5, PTS>(bw, K, Ns, lane, tf);
-        else if constexpr (PTS >= 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
+        if (direct && f == plan.nf - 1) rg_pass_args<8, PTS, true>(bw, K, Ns, lane, tf, dst);
+        else if (R == 8) rg_pass_args<8, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 4) rg_pass_args<4, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 2) rg_pass_args<2, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 3) rg_pass_args<3, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 5) rg_pass_args<5, PTS>(bw, K, Ns, lane, tf);
+        else if constexpr (PTS >= 24) rg_pass_args<24, PTS>(bw, K, Ns, lane, tf);
         tf += (R - 1) * Ns;
         Ns *= R;
       }
@@ -798,12 +806,12 @@ __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_r2c_rg(FftPlan plan, int 
         const float2* tf = twp;
         for (int f = 0; f < plan.nf; ++f) {
           const int R = plan.radix[f];
-          if (R == 8) rg_pass<8, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 4) rg_pass<4, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 2) rg_pass<2, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 3) rg_pass<3, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 5) rg_pass<5, PTS>(bw, K, Ns, lane, tf);
-          else if constexpr (PTS >= 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
+          if (R == 8) rg_pass_args<8, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 4) rg_pass_args<4, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 2) rg_pass_args<2, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 3) rg_pass_args<3, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 5) rg_pass_args<5, PTS>(bw, K, Ns, lane, tf);
+          else if constexpr (PTS >= 24) rg_pass_args<24, PTS>(bw, K, Ns, lane, tf);
           tf += (R - 1) * Ns;
           Ns *= R;
         }

@@ -321,3 +321,31 @@ def test_f32_synthesis_offsets_past_32_bits():
     got = c.filter_maps(a)
     for s in (0, 30, 31):
         assert torch.equal(got[s:s + 1], c.filter_maps(a[s:s + 1]))
+
+
+# A state finalised over each form of the ring transform that scales and weights its rows as they are
+# loaded: plans of at most 16, 24, 32 and 48 points per lane run from their arguments (nphi 1440, 2560,
+# 4096, 3840) and the compiled ones (1536, 3072, 6016).  Both what it writes: the pair means in place
+# and, through the linear term, their harmonic transform.
+@pytest.mark.parametrize("nphi", [1440, 1536, 2560, 3072, 3840, 4096, 6016])
+@pytest.mark.parametrize("prec", ["f32", "bf16x3"])
+def test_finalized_state_of_each_ring_transform(nphi, prec):
+    lmax, ntheta, P, S = 20, 27, 3, 2
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 79)
+    print(f"[case] finalised state {prec} {ntheta}x{nphi}", flush=True)
+    a, mc = case.alms(0, S), case.alms(60, 3)
+    c = _ctx(case, prec)
+    st = c.linear_state()
+    c.linear_reset(st)
+    c.linear_accumulate(st, mc)
+    c.linear_finalize(st)
+    Mmc = case.maps(mc)
+    V, rms = om.pair_means(Mmc), np.sqrt(np.mean(Mmc**2, axis=(0, 2, 3)))
+    pa, pb = np.triu_indices(P)
+    tol = 1e-5 if prec == "f32" else 1e-4   # the map bounds: twice them for a product of two maps
+    err = np.abs(c.pair_means(st).cpu().numpy() - V).reshape(len(pa), -1).max(1)
+    assert np.all(err <= 2 * tol * rms[pa] * rms[pb])
+    got = c.linear_apply(st, a).cpu().numpy()
+    for i in range(S):
+        ref = om.linear_term(case.maps(a[i:i + 1])[0], case.grid.w, V)
+        assert np.abs(got[i] - ref).max() <= tol * np.sqrt(np.mean(ref**2))
