@@ -137,7 +137,7 @@ hipError_t launch_seeds(const modal_ctx* c, const double* logpref, hipStream_t s
 
 // Legendre synthesis: F (f_index layout) complex, double2 for F64, float2 otherwise
 hipError_t launch_legendre(const modal_ctx* c, const void* alm, int S, void* F, hipStream_t st);
-// FP32 contexts; scratch (may be null) is overwritten
+// FP32 contexts; scratch (may be null, may hold alm) is overwritten, alm in it only by what follows
 hipError_t launch_legendre_mfma(const modal_ctx* c, const void* alm, int S, void* F, void* scratch,
                                 size_t scratch_bytes, hipStream_t st);
 // split bf16/fp16 synthesis on 32x32 tiles, lambda in registers (k_legendre_split.hip)

@@ -482,7 +482,8 @@ size_t legendre_mfma_tab_bytes(const modal_ctx* c) {
 // scratch: device memory that the call may overwrite (the maps that are formed next).  Lambda
 // comes from a table there when at least three column blocks share it (below that, building it
 // costs what running the recurrence in each block does: 72 us against 24 us a block at l_max
-// 500, 768 rings) and it fits, 16-byte aligned.  Skies too large for 32-bit offsets (32 of them in
+// 500, 768 rings) and it fits, 16-byte aligned, beside a_lm that may lie in the same memory (a
+// caller's maps may replace the a_lm they are formed from).  Skies too large for 32-bit offsets (32 of them in
 // a block from l_max 5884 on) take the recurrence with 64-bit ones.
 hipError_t launch_legendre_mfma(const modal_ctx* c, const void* alm, int S, void* F, void* scratch,
                                 size_t scratch_bytes, hipStream_t st) {
@@ -492,8 +493,10 @@ hipError_t launch_legendre_mfma(const modal_ctx* c, const void* alm, int S, void
   const int nrt = (c->nrp + blocks * NWAVE * 16 - 1) / (blocks * NWAVE * 16);   // 16-ring tiles per wave, <= 4
   const dim3 grid((ncols + NCOL - 1) / NCOL, blocks, c->lmax + 1);
   const bool fit = offsets_fit(c->lmax, c->P, S);
-  const bool table = fit && grid.x >= 3 && scratch && scratch_bytes >= legendre_mfma_tab_bytes(c) &&
-                     reinterpret_cast<uintptr_t>(scratch) % 16 == 0;
+  const uintptr_t t0 = reinterpret_cast<uintptr_t>(scratch), a0 = reinterpret_cast<uintptr_t>(alm);
+  const size_t tab = legendre_mfma_tab_bytes(c), na = (size_t)S * c->nalm * sizeof(float2);
+  const bool apart = a0 + na <= t0 || t0 + tab <= a0;
+  const bool table = fit && apart && grid.x >= 3 && scratch && scratch_bytes >= tab && t0 % 16 == 0;
   if (table) {
     hipLaunchKernelGGL(k_lambda_records, dim3((c->nrp + 63) / 64, c->lmax + 1), dim3(64), 0, st, c->lmax, c->nrp, c->t.x,
                        c->t.rec, c->t.seed, c->t.lstart, (float*)scratch);

@@ -349,3 +349,22 @@ def test_finalized_state_of_each_ring_transform(nphi, prec):
     for i in range(S):
         ref = om.linear_term(case.maps(a[i:i + 1])[0], case.grid.w, V)
         assert np.abs(got[i] - ref).max() <= tol * np.sqrt(np.mean(ref**2))
+
+
+# Maps written over the a_lm they are formed from, which lie at the start, in the middle or at the end
+# of their memory: what separate memory gives, bit for bit.
+@pytest.mark.parametrize("prec", ["f32", "f64", "bf16x3"])
+@pytest.mark.parametrize("where", [0.0, 0.4, 1.0])
+def test_maps_over_their_own_alm(prec, where):
+    lmax, ntheta, nphi, P, S = 64, 130, 136, 7, 14
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 80)
+    print(f"[case] maps over alm {prec} at {where}", flush=True)
+    c = _ctx(case, prec)
+    a = torch.as_tensor(case.alms(0, S)).to("cuda", c.complex_dtype)
+    ref = c.filter_maps(a)
+    out = torch.zeros_like(ref)
+    room = out.numel() - 2 * a.numel()
+    at = int(where * room) // 64 * 64
+    inside = torch.view_as_complex(out.view(-1)[at:at + 2 * a.numel()].view(-1, 2)).view(S, c.nalm)
+    inside.copy_(a)
+    assert torch.equal(c.filter_maps(inside, out=out), ref)
