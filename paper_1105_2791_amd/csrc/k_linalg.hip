@@ -284,39 +284,40 @@ __global__ __launch_bounds__(256) void k_dots(int n, const double* __restrict__ 
 
 typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));   // rows of odd length: 8-byte aligned
 constexpr int TK = 16;     // k per LDS stage of the matrix-core update kernel
-constexpr int TR = 128;    // rows per tile
-constexpr int TC = 64;     // columns per tile
+constexpr int TRL = 128;   // rows per tile
+constexpr int TC = 64;     // columns per tile, and rows of the small tile
 
-// Lower-triangle tile update on the matrix cores, tile (bi, bj) of 128 x 64, j0 <= i0 + 127:
+// Lower-triangle tile update on the matrix cores, tile (bi, bj) of TR x 64, j0 <= i0 + TR - 1 (TR 128, or 64):
 //   C[i][j] = alpha sum_k P(i, k) P(j, k)                 (COLS: P(i, k) = X[k][i], rows of X
 //                                                          [K][n] are the samples), or
 //   C[i][j] -= sum_k P(i, k) P(j, k)                      (P(i, k) = X[(r0 + i) ld + k], a panel;
 //                                                          the old values start the sums).
 // Rows and columns start at r0 for C.  MIRROR: the upper triangle gets the same values (a
-// symmetric result), transposed through LDS.  Four waves of 64 x 32; a wave wholly above the
-// diagonal only stages.  COLS numbers the lower triangle's tiles alone (row bi has 2 (bi + 1)), so
+// symmetric result), transposed through LDS.  Four waves of TR / 2 x 32; a wave wholly above the
+// diagonal only stages.  COLS numbers the lower triangle's tiles alone (row bi has TR / 64 (bi + 1)), so
 // that the workgroups which leave at once are not dealt unevenly over the chip.  LDS: k-major rows of COLS 16 doubles past a multiple of 64 words, so
 // that two k of 16 rows fill the banks; row-major of 18 doubles for a panel, the same.
 // Bound by the matrix cores and by the staging's L2 reads (10.7 flop per byte; 64 x 64 tiles
 // had 8).  6000 x 4960 samples: 4.93 ms with 64 x 64 tiles and two-way bank conflicts, 3.35 ms
 // (44 TFLOP/s of the triangle's flops) now, 3.64 with the triangle cut out of a square grid.
-template <bool COLS, bool MIRROR>
+template <bool COLS, bool MIRROR, int TR>
 __global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, const double* __restrict__ X, int ld,
                                                         double alpha, double* __restrict__ C) {
+  constexpr int NR = TR / TC, MA = TR / 32;   // column tiles per tile row of the diagonal; a wave's 16-row tiles
   int bi = blockIdx.y, bj = blockIdx.x;
   if (COLS) {
-    const int t = blockIdx.x;
+    const int t = 2 / NR * blockIdx.x;   // rows before bi hold NR bi (bi + 1) / 2 tiles
     bi = (int)((sqrtf(1.0f + 4.0f * t) - 1.0f) * 0.5f);
     while (bi * (bi + 1) > t) --bi;
     while ((bi + 1) * (bi + 2) <= t) ++bi;
-    bj = t - bi * (bi + 1);
+    bj = (t - bi * (bi + 1)) / (2 / NR);
   }
   const int i0 = r0 + bi * TR, j0 = r0 + bj * TC;
   if (j0 > i0 + TR - 1 || i0 >= n || j0 >= n) return;   // whole workgroup, before any barrier
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
   const int wr = wv >> 1, wc = wv & 1, l16 = lane & 15, kq = lane >> 4;
-  const int iw = i0 + 64 * wr, jw = j0 + 32 * wc;         // the wave's first row and column
-  const bool live = jw <= iw + 63 && iw < n && jw < n;    // uniform
+  const int iw = i0 + TR / 2 * wr, jw = j0 + 32 * wc;             // the wave's first row and column
+  const bool live = jw <= iw + TR / 2 - 1 && iw < n && jw < n;    // uniform
   constexpr int SI = COLS ? TR + 16 : TK + 2, SJ = COLS ? TC + 16 : TK + 2;   // row strides
   constexpr int NI = COLS ? TK : TR, NJ = COLS ? TK : TC;                     // LDS rows
   constexpr int TS = 17;                                                      // mirror staging row
@@ -325,9 +326,9 @@ __global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, co
   double(*Pi)[SI] = reinterpret_cast<double(*)[SI]>(raw);
   double(*Pj)[SJ] = reinterpret_cast<double(*)[SJ]>(raw + sizeof(double) * NI * SI);
   // acc starts from -C (panel update) or 0
-  d4 acc[4][2];
+  d4 acc[MA][2];
 #pragma unroll
-  for (int ta = 0; ta < 4; ++ta)
+  for (int ta = 0; ta < MA; ++ta)
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
@@ -401,10 +402,10 @@ __global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, co
 #pragma unroll
       for (int ks = 0; ks < TK / 4; ++ks) {
         const int kk = 4 * ks + kq;
-        double a[4], b[2];
+        double a[MA], b[2];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int r = 64 * wr + 16 * t + l16;
+        for (int t = 0; t < MA; ++t) {
+          const int r = TR / 2 * wr + 16 * t + l16;
           a[t] = COLS ? Pi[kk][r] : Pi[r][kk];
         }
 #pragma unroll
@@ -413,7 +414,7 @@ __global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, co
           b[t] = COLS ? Pj[kk][c] : Pj[c][kk];
         }
 #pragma unroll
-        for (int ta = 0; ta < 4; ++ta)
+        for (int ta = 0; ta < MA; ++ta)
 #pragma unroll
           for (int tb = 0; tb < 2; ++tb) acc[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
       }
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, co
     __syncthreads();
   }
 #pragma unroll
-  for (int ta = 0; ta < 4; ++ta)
+  for (int ta = 0; ta < MA; ++ta)
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
@@ -432,14 +433,12 @@ __global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, co
       }
   if constexpr (MIRROR) {   // 16 rows x 32 columns at a time: row j of the upper triangle, 16 consecutive i
     double(*tr)[TS] = reinterpret_cast<double(*)[TS]>(raw) + 32 * wv;
-    for (int ta = 0; ta < 4; ++ta) {
+#pragma unroll
+    for (int ta = 0; ta < MA; ++ta) {
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) tr[16 * tb + l16][4 * r + kq] = ta == 0   ? acc[0][tb][r]
-                                                                  : ta == 1 ? acc[1][tb][r]
-                                                                  : ta == 2 ? acc[2][tb][r]
-                                                                            : acc[3][tb][r];
+        for (int r = 0; r < 4; ++r) tr[16 * tb + l16][4 * r + kq] = acc[ta][tb][r];
       __syncthreads();
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
@@ -629,8 +628,15 @@ hipError_t launch_center_rows(int n, int N, const double* B, double* C, hipStrea
 }
 
 hipError_t launch_syrk(int n, int N, const double* B, double scale, double* Z, hipStream_t st) {
-  const int nb = (n + TR - 1) / TR;
-  hipLaunchKernelGGL((k_tile_update<true, true>), dim3(nb * (nb + 1)), dim3(256), 0, st, n, N, 0, B, n, scale, Z);
+  // Tiles of 64 x 64 while those of 128 x 64 are fewer than the CUs: each workgroup runs through all
+  // the samples by itself there, and the smaller tile's stage is the shorter one (1000 samples: 120
+  // modes 110 and 74 us, 816 modes 123 and 99, 1540 modes (182 tiles) 119 and 110; 2600 modes (462
+  // tiles) 171 and 178, 11,480 modes with 200 samples 533 and 548).  The sums are the same bit for bit.
+  const int nb = (n + TRL - 1) / TRL, nc = (n + TC - 1) / TC;
+  if (nb * (nb + 1) <= 256)
+    hipLaunchKernelGGL((k_tile_update<true, true, TC>), dim3(nc * (nc + 1) / 2), dim3(256), 0, st, n, N, 0, B, n, scale, Z);
+  else
+    hipLaunchKernelGGL((k_tile_update<true, true, TRL>), dim3(nb * (nb + 1)), dim3(256), 0, st, n, N, 0, B, n, scale, Z);
   return hipGetLastError();
 }
 
@@ -646,7 +652,7 @@ hipError_t launch_cholesky_lookahead(int n, double* A, int* flag, hipStream_t st
   // A[i][j] -= sum_c A[i][k0 + c] A[j][k0 + c], i >= j >= r0, tile columns [bj0, ...) of the
   // (n - r0)-square trailing grid; nbx tile columns
   auto update = [&](int k0, int kb, int r0, int nbx, hipStream_t s) {
-    hipLaunchKernelGGL((k_tile_update<false, false>), dim3(nbx, (n - r0 + TR - 1) / TR), dim3(256), 0, s, n, kb, r0, A + k0,
+    hipLaunchKernelGGL((k_tile_update<false, false, TRL>), dim3(nbx, (n - r0 + TRL - 1) / TRL), dim3(256), 0, s, n, kb, r0, A + k0,
                        n, -1.0, A);
   };
   // Factor the block column [k, k + 2 NB) (its two NB-wide halves), all updates from the

@@ -368,3 +368,20 @@ def test_maps_over_their_own_alm(prec, where):
     inside = torch.view_as_complex(out.view(-1)[at:at + 2 * a.numel()].view(-1, 2)).view(S, c.nalm)
     inside.copy_(a)
     assert torch.equal(c.filter_maps(inside, out=out), ref)
+
+
+# The covariance's two tiles: 64 rows (1771 modes, 210 tiles of 128 rows) and 128 (2024 modes, 272), odd
+# and even row lengths, sample counts off a stage of 16.  Against FP64 within the bound above,
+# and the modes that both hold are the same bit for bit.
+@pytest.mark.parametrize("N", [17, 200])
+def test_covariance_tile_forms(N):
+    print(f"[case] covariance tiles N={N}", flush=True)
+    b = np.random.default_rng(N).standard_normal((N, 2024)) + 0.5
+    Z = {}
+    for P, n in ((21, 1771), (22, 2024)):
+        d = np.ascontiguousarray(b[:, :n])
+        Z[n] = _ctx(Case("edge", 4, 6, 12, P, 1, "wmap", 73), "f64").covariance_sample(d).cpu().numpy()
+        bound = 4 * N * np.finfo(float).eps * (np.abs(d).T @ np.abs(d)) / (6.0 * N)
+        assert np.all(np.abs(Z[n] - d.T @ d / (6.0 * N)) <= bound)
+        assert np.array_equal(Z[n], Z[n].T)
+    assert np.array_equal(Z[2024][:1771, :1771], Z[1771])
