@@ -110,8 +110,10 @@ __global__ __launch_bounds__(256) void k_potrf_diag(int n, double* __restrict__ 
         const double p = lane_value(d[j], j);
         const bool ok = p > 0.0;
         if (lane == 0 && !ok && c0 + j < kb) atomicCAS(flag, 0, k0 + c0 + j + 1);
-        const double rp = ok ? 1.0 / sqrt(p) : __builtin_nan("");   // uniform
-        d[j] *= rp;   // the pivot's own lane: p / sqrt(p)
+        // divided, not multiplied by 1 / sqrt(p): correctly rounded, and an infinite pivot (a mode
+        // without weight) leaves a column of zeros
+        const double sd = ok ? sqrt(p) : __builtin_nan("");   // uniform
+        d[j] = !id && r == j ? sd : d[j] / sd;
 #pragma unroll
         for (int c = j + 1; c < SB; ++c) d[c] -= d[j] * lane_value(d[j], c);   // entries past the diagonal are never read
       }
