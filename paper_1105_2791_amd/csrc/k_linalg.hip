@@ -35,9 +35,8 @@ constexpr int NB = 64;
 // block's upper triangle (A[k0 + c][k0 + q] = W[q][c]).  Rows and columns past kb are an
 // identity block.  A non-positive pivot is recorded in flag and turns into NaN.
 // Bound by the chain of 64 pivots, which the look-ahead cannot hide: with LDS shuffles, a
-// square root and a division per entry in the chain and scalar block products it took 57 us,
-// 22.6 us
-// now, 33 of them with the inverses formed by substitution.
+// square root and a division per entry in the chain and scalar block products it took 57 us; 22.6
+// now (33 with the inverses formed by substitution).
 constexpr int SB = 16;       // sub-block
 constexpr int DS = NB + 2;   // LDS row stride: 16 rows x 2 columns of doubles fill the 64 banks
 typedef double d4 __attribute__((ext_vector_type(4)));
@@ -292,8 +291,10 @@ constexpr int TC = 64;     // columns per tile, and rows of the small tile
 // Lower-triangle tile update on the matrix cores, tile (bi, bj) of TR x 64, j0 <= i0 + TR - 1 (TR 128, or 64):
 //   C[i][j] = alpha sum_k P(i, k) P(j, k)                 (COLS: P(i, k) = X[k][i], rows of X
 //                                                          [K][n] are the samples), or
-//   C[i][j] -= sum_k P(i, k) P(j, k)                      (P(i, k) = X[(r0 + i) ld + k], a panel;
-//                                                          the old values start the sums).
+//   C[i][j] -= sum_k P(i, k) P(j, k)                      (P(i, k) = X[(r0 + i) ld + k], a panel).
+// The panel's sums start from zero and meet the old values once: started from the old values, each
+// of their 128 steps rounds at the old value's size, and the backward error of the factor at
+// 1140 modes was 3.7e-15 instead of 1.0e-15.
 // Rows and columns start at r0 for C.  MIRROR: the upper triangle gets the same values (a
 // symmetric result), transposed through LDS.  Four waves of TR / 2 x 32; a wave wholly above the
 // diagonal only stages.  COLS numbers the lower triangle's tiles alone (row bi has TR / 64 (bi + 1)), so
@@ -327,17 +328,11 @@ __global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, co
   __shared__ __attribute__((aligned(16))) unsigned char raw[kBytes > kMir ? kBytes : kMir];
   double(*Pi)[SI] = reinterpret_cast<double(*)[SI]>(raw);
   double(*Pj)[SJ] = reinterpret_cast<double(*)[SJ]>(raw + sizeof(double) * NI * SI);
-  // acc starts from -C (panel update) or 0
   d4 acc[MA][2];
 #pragma unroll
   for (int ta = 0; ta < MA; ++ta)
 #pragma unroll
-    for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = min(iw + 16 * ta + 4 * r + kq, n - 1), j = min(jw + 16 * tb + l16, n - 1);
-        acc[ta][tb][r] = COLS ? 0.0 : -C[(size_t)i * n + j];
-      }
+    for (int tb = 0; tb < 2; ++tb) acc[ta][tb] = d4{0.0, 0.0, 0.0, 0.0};
   // The next stage's operands are loaded, two doubles at a time, while this stage multiplies.
   // COLS: 16 k x 64 pairs of rows and 16 k x 32 of columns; panel: rows of 8 pairs of k.
   constexpr int LI = TR * TK / 512, LJ = TC * TK / 512;
@@ -424,15 +419,23 @@ __global__ __launch_bounds__(256, 3) void k_tile_update(int n, int K, int r0, co
     __syncthreads();
   }
 #pragma unroll
-  for (int ta = 0; ta < MA; ++ta)
+  for (int ta = 0; ta < MA; ++ta) {
+    d4 cold[2];   // the old values of a row tile, all loaded before the first is used
+    if (!COLS)
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          cold[tb][r] = C[(size_t)min(iw + 16 * ta + 4 * r + kq, n - 1) * n + min(jw + 16 * tb + l16, n - 1)];
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = iw + 16 * ta + 4 * r + kq, j = jw + 16 * tb + l16;
-        acc[ta][tb][r] = COLS ? alpha * acc[ta][tb][r] : -acc[ta][tb][r];
-        if (live && i < n && j <= i) C[(size_t)i * n + j] = acc[ta][tb][r];
+        if (COLS) acc[ta][tb][r] *= alpha;
+        if (live && i < n && j <= i) C[(size_t)i * n + j] = COLS ? acc[ta][tb][r] : cold[tb][r] - acc[ta][tb][r];
       }
+  }
   if constexpr (MIRROR) {   // 16 rows x 32 columns at a time: row j of the upper triangle, 16 consecutive i
     double(*tr)[TS] = reinterpret_cast<double(*)[TS]>(raw) + 32 * wv;
 #pragma unroll
@@ -511,7 +514,7 @@ __global__ __launch_bounds__(256) void k_panel_mfma(int n, double* __restrict__ 
 // in one launch: every workgroup forms P_0, the panel of the rows k2 .., for itself from the copy
 // that k_potrf_diag left (a product of 64^3 against a launch and the wait for the panel).
 // Bound by latency, on the chain of the factorization.  The estimator at 4960 modes: 8.95 ms with the
-// panel and the update as two launches, 8.76 now.
+// panel and the update as two launches, 8.76 in one.
 __global__ __launch_bounds__(256) void k_panel_update(int n, double* __restrict__ A, int k0) {
   __shared__ double X[NB][DS], Y[NB][DS], Wt[NB][DS];   // the workgroup's rows (then P), rows k2 .. (then P_0), W^T
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
@@ -533,7 +536,7 @@ __global__ __launch_bounds__(256) void k_panel_update(int n, double* __restrict_
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = min(rbase + 32 * wr + 16 * ta + 4 * r + kq, n - 1), j = min(k2 + 32 * wc + 16 * tb + l16, n - 1);
-        cv[ta][tb][r] = -A[(size_t)i * n + j];
+        cv[ta][tb][r] = A[(size_t)i * n + j];
       }
 #pragma unroll
   for (int u = 0; u < NB * NB / 256; ++u) {
@@ -579,6 +582,11 @@ __global__ __launch_bounds__(256) void k_panel_update(int n, double* __restrict_
         if (rbase + ri < n) A[(size_t)(rbase + ri) * n + k0 + c] = p[ta][tb][r];
       }
   __syncthreads();
+  d4 u[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) u[a][b] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
   for (int ks = 0; ks < NB / 4; ++ks) {
     const int kk = 4 * ks + kq;
@@ -591,7 +599,7 @@ __global__ __launch_bounds__(256) void k_panel_update(int n, double* __restrict_
 #pragma unroll
     for (int ta = 0; ta < 2; ++ta)
 #pragma unroll
-      for (int tb = 0; tb < 2; ++tb) cv[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], cv[ta][tb], 0, 0, 0);
+      for (int tb = 0; tb < 2; ++tb) u[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], u[ta][tb], 0, 0, 0);
   }
 #pragma unroll
   for (int ta = 0; ta < 2; ++ta)
@@ -600,7 +608,7 @@ __global__ __launch_bounds__(256) void k_panel_update(int n, double* __restrict_
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = rbase + 32 * wr + 16 * ta + 4 * r + kq, j = k2 + 32 * wc + 16 * tb + l16;
-        if (i < n && j <= i) A[(size_t)i * n + j] = -cv[ta][tb][r];
+        if (i < n && j <= i) A[(size_t)i * n + j] = cv[ta][tb][r] - u[ta][tb][r];
       }
 }
 
