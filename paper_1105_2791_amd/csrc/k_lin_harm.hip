@@ -40,11 +40,15 @@ __global__ __launch_bounds__(256) void k_weight_planes(int npix, int nk, const T
 // group, y: the l tile), so that every Z and a_lm element it loads feeds PT or ST products; its MW waves take the m of the
 // sum in turn (m = w, w + MW, ...) and their partial sums are added through LDS.  The
 // lanes of a wave read consecutive l of one m row of the m-major packing: coalesced.
-// Large problems: 8 pairs and four waves.  With fewer workgroups than half the CUs the chain of a
-// wave's m bounds it (a load's latency each): 2 pairs and 16 waves, a quarter of the chain and four
-// times the workgroups.  8 and 4 against 2 and 16: l_max 150, 91 pairs, 3 maps (36 workgroups) 31 and
-// 16 us; 300, 136, 4 (85) 16 us less; 300, 210, 8 (135) 3 us more; 500, 465, 8 (472) 163 and 265; 1000,
-// 820, 8 (1648) 0.96 and 1.66 ms.
+// Large problems: 8 pairs and four waves.  Float contexts with fewer than 128 pair groups x l tiles: the
+// chain of a wave's m bounds it (a load's latency each), so eight waves, half the chain, and 4 pairs until
+// there are workgroups enough.  The line counts no maps, so that a map's sums, which follow the waves, are
+// the same in any batch.  FP64 contexts, whose loads are twice as wide, keep the four waves: with
+// eight 91 pairs at l_max 150 take 36 us for one map and 63 for eight, 31 and 38 with four.
+// Linear term, four waves | eight with 4 pairs | eight with 8 pairs:
+//   l_max 150, 91 pairs, 3 maps (36 groups x tiles) 33 | 23 | 33 us, 200 maps 90 | 101 | 114;
+//   300, 136, 8 (85) 63 | 39 | 54, 200 maps 408 | 452 | 374;  500, 55, 8 (56) 98 | 56 | 80, 64 maps 143 | 199 | 162.
+// Above the line: 500, 465, 8 (472) 163 against 265 with 2 pairs and 16 waves; 1000, 820, 8 (1648) 0.96 and 1.66 ms.
 constexpr int ST = 8;
 constexpr int LT = 64;
 
@@ -309,18 +313,15 @@ hipError_t launch_lin_harmonic(const modal_ctx* c, const void* Z, const void* al
   if (c->P > 64) return hipErrorInvalidValue;
   // pair groups fastest: the workgroups running together share one l tile of a_lm in L2
   auto grid = [&](int pt) { return dim3((c->npairs + pt - 1) / pt, (c->lmax + LT) / LT, (S + ST - 1) / ST); };
-  const dim3 wide = grid(8), narrow = grid(2);
-  const bool few = (size_t)wide.x * wide.y * wide.z < 128;
+  const dim3 wide = grid(8);
+  const bool few = wide.x * wide.y < 128, half = (size_t)wide.x * wide.y * wide.z < 256;
   auto launch = [&](auto kernel, dim3 g, int mw, auto* z) {
     hipLaunchKernelGGL(kernel, g, dim3(LT * mw), 0, st, c->lmax, c->nalm, c->npairs, S, z, (decltype(z))alm, X);
   };
-  if (is_f64(c)) {
-    if (few) launch(k_lin_x<double, 2, 16, 4>, narrow, 16, (const double2*)Z);
-    else launch(k_lin_x<double, 8, 4, 16>, wide, 4, (const double2*)Z);
-  } else {
-    if (few) launch(k_lin_x<float, 2, 16, 4>, narrow, 16, (const float2*)Z);
-    else launch(k_lin_x<float, 8, 4, 16>, wide, 4, (const float2*)Z);
-  }
+  if (is_f64(c)) launch(k_lin_x<double, 8, 4, 16>, wide, 4, (const double2*)Z);
+  else if (few && half) launch(k_lin_x<float, 4, 8, 8>, grid(4), 8, (const float2*)Z);
+  else if (few) launch(k_lin_x<float, 8, 8, 8>, wide, 8, (const float2*)Z);
+  else launch(k_lin_x<float, 8, 4, 16>, wide, 4, (const float2*)Z);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int rows = S * c->npairs;

@@ -420,3 +420,23 @@ def test_cholesky_backward_error(seed):
     L = L.cpu().numpy()
     d = np.sqrt(np.diag(A))
     assert np.abs((A - L @ L.T) / np.outer(d, d)).max() <= (n / 128 + 1) * np.finfo(float).eps
+
+
+# A sky's results do not depend on the batch it comes in, bit for bit: batches on both sides of where
+# the linear term changes its split (8 and 160 skies: 14 and 280 workgroups of 8 pairs), where the
+# FP32 synthesis takes its table and where a second block of skies begins.
+@pytest.mark.parametrize("prec", ["f32", "f64", "bf16x3", "f16x3"])
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", [(64, 66, 130, 10, 160), (150, 152, 304, 13, 31)])
+def test_batch_independence(lmax, ntheta, nphi, P, S, prec):
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 81)
+    print(f"[case] batch independence {prec} lmax={lmax} P={P} S={S}", flush=True)
+    c = _ctx(case, prec)
+    a = torch.as_tensor(case.alms(0, S)).to("cuda", c.complex_dtype)
+    st = c.linear_state()
+    c.linear_reset(st)
+    c.linear_accumulate(st, a[:2])
+    c.linear_finalize(st)
+    lin, hat = c.linear_apply(st, a), c.beta(a, state=st)
+    for lo, hi in ((0, 1), (S // 2, S // 2 + 8), (S - 10, S)):
+        assert torch.equal(c.linear_apply(st, a[lo:hi]), lin[lo:hi])
+        assert torch.equal(c.beta(a[lo:hi], state=st), hat[lo:hi])
