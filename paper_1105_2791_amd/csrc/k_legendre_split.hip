@@ -383,33 +383,50 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   float2* f = F + (size_t)((c0 >> 1) + lrow) * f_ring_blocks(ntheta) * ms + (size_t)m * 8;
   typedef float f4 __attribute__((ext_vector_type(4)));
   const int jb = rbk * (NWAVE * RW) + wv * RW;
+  // ring j = jb + 4 kh + 2 h + 8 k (k = 4 rt + g) and its south ring t - 8 k: the lane's places are k ring
+  // groups from those of k = 0, a uniform step.  Rings past the last and the checks for them are
+  // left out a group or a wave at a time: formed ring by ring, the addresses and branches were 2 us of
+  // the 13.6 that one sky of 8 modes takes at l_max 32 (11.9 now).
+  float2* fn = f + (size_t)(jb >> 3) * ms + 4 * kh;
+  float2 *fs0[2], *fs1[2];   // south of j, and of j + 1
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+  for (int h = 0; h < 2; ++h) {
+    const int t = ntheta - 1 - jb - 4 * kh - 2 * h;
+    fs0[h] = f + (ptrdiff_t)(t >> 3) * (ptrdiff_t)ms + (t & 7);
+    fs1[h] = f + (ptrdiff_t)((t - 1) >> 3) * (ptrdiff_t)ms + ((t - 1) & 7);
+  }
+  auto store = [&](auto all_) {   // all: every ring of the wave exists and its south rings come in pairs
+    constexpr bool all = decltype(all_)::value;
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int k = 0; k < 8; ++k) {
+      if (!all && jb + 8 * k >= nrp) break;   // uniform
+      const int rt = k >> 2, g = k & 3;
+      const size_t o = k * ms;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int j = jb + 32 * rt + 8 * g + 4 * kh + 2 * h, r = 4 * g + 2 * h;
+        const int j = jb + 8 * k + 4 * kh + 2 * h, r = 4 * g + 2 * h;
         const float2 n0 = make_float2(acc[0][rt][0][r] + acc[1][rt][0][r], acc[0][rt][1][r] + acc[1][rt][1][r]);
         const float2 n1 = make_float2(acc[0][rt][0][r + 1] + acc[1][rt][0][r + 1], acc[0][rt][1][r + 1] + acc[1][rt][1][r + 1]);
         const float2 s0 = make_float2(acc[0][rt][0][r] - acc[1][rt][0][r], acc[0][rt][1][r] - acc[1][rt][1][r]);
         const float2 s1 = make_float2(acc[0][rt][0][r + 1] - acc[1][rt][0][r + 1], acc[0][rt][1][r + 1] - acc[1][rt][1][r + 1]);
         const int jw = ntheta - 1 - j;   // j's south ring; j + 1's is jw - 1
-        float2* fn = f + (j >> 3) * ms + (j & 7);
-        float2* fs = f + (jw >> 3) * ms + (jw & 7);
-        if (j + 1 < nrp) {
-          *reinterpret_cast<f4*>(fn) = f4{n0.x, n0.y, n1.x, n1.y};
-          if (!(ntheta & 1)) {
-            *reinterpret_cast<f4*>(fs - 1) = f4{s1.x, s1.y, s0.x, s0.y};
+        if (all || j + 1 < nrp) {
+          *reinterpret_cast<f4*>(fn + o + 2 * h) = f4{n0.x, n0.y, n1.x, n1.y};
+          if (all || !(ntheta & 1)) {
+            *reinterpret_cast<f4*>(fs1[h] - o) = f4{s1.x, s1.y, s0.x, s0.y};
           } else {
-            *fs = s0;
-            if (jw - 1 != j + 1) f[((jw - 1) >> 3) * ms + ((jw - 1) & 7)] = s1;
+            *(fs0[h] - o) = s0;
+            if (jw - 1 != j + 1) *(fs1[h] - o) = s1;
           }
         } else if (j < nrp) {
-          *fn = n0;
-          if (jw != j) *fs = s0;
+          fn[o + 2 * h] = n0;
+          if (jw != j) *(fs0[h] - o) = s0;
         }
       }
+    }
+  };
+  if (jb + RW <= nrp && !(ntheta & 1)) store(std::true_type{});   // uniform
+  else store(std::false_type{});
 }
 
 }  // namespace
