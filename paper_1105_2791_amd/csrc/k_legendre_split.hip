@@ -97,7 +97,8 @@ __device__ inline double lane_double(uint32_t lo, uint32_t hi, int t) {
   return __builtin_bit_cast(double, v);
 }
 
-template <int PREC, bool FAST>
+// Groups [G0, G1) of 8 steps.
+template <int PREC, bool FAST, int G0, int G1>
 __device__ inline void lambda_chunk(int l0, int m, int lmax, const uint32_t (&rr)[4], double xx, int ls,
                                     double s0, double s1, double& l1, double& l2, uint32_t (&Lh)[2][2][2][4],
                                     uint32_t (&Ll)[2][2][2][4]) {
@@ -105,7 +106,7 @@ __device__ inline void lambda_chunk(int l0, int m, int lmax, const uint32_t (&rr
   // issued with the coefficient loads); each step reads its pair back as wave-uniform
   // values, so the recurrence never waits on the scalar cache
 #pragma unroll
-  for (int g = 0; g < 8; ++g) {
+  for (int g = G0; g < G1; ++g) {
     // 8 steps: l-indices 4 g .. 4 g + 3 of each parity, i.e. [ks = g / 4][half = (g / 2) % 2]
     // at k = 2 (g % 2) and 2 (g % 2) + 1
     float lam[2][4];
@@ -223,14 +224,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int la = min(l0n + 4 * ck + cpar, lmax), lb = min(l0n + 4 * ck + 2 + cpar, lmax);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      int sp = csp[i];
-      if (MODE == RECUR) asm volatile("" : "+v"(sp));   // addresses formed anew: kept over the loop they spill
-      const float2* pa = alm_m + (size_t)((uint32_t)sp / kMaxP) * nalm;
-      const float* pq = qw + (uint32_t)sp % kMaxP * (lmax + 1);
+      const float2* pa = alm_m + (size_t)((uint32_t)csp[i] / kMaxP) * nalm;
+      const float* pq = qw + (uint32_t)csp[i] % kMaxP * (lmax + 1);
       va[i][0] = pa[la];
       va[i][1] = pa[lb];
       vq[i][0] = pq[la];
       vq[i][1] = pq[lb];
+    }
+  };
+
+  // Coefficient tile: qw_p(l) Re/Im a_lm, split, stored: words of l-indices 2 ck, + 1 (zero past lmax
+  // and for padding columns).
+  auto stage_coef = [&](int l0, CoefTile& C) {
+    const bool oka = l0 + 4 * ck + cpar <= lmax, okb = l0 + 4 * ck + 2 + cpar <= lmax;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int col = cp0 + i;   // Re; Im 32 rows on
+      const bool ok = c0 + 2 * col < ncols;
+      const float q0 = vq[i][0], q1 = vq[i][1];
+      uint32_t h, lw;
+      split2<PREC>(ok && oka ? q0 * va[i][0].x : 0.f, ok && okb ? q1 * va[i][1].x : 0.f, h, lw);
+      *reinterpret_cast<uint32_t*>(&C.h[cpar].v[col][2 * ck]) = h;
+      *reinterpret_cast<uint32_t*>(&C.l[cpar].v[col][2 * ck]) = lw;
+      split2<PREC>(ok && oka ? q0 * va[i][0].y : 0.f, ok && okb ? q1 * va[i][1].y : 0.f, h, lw);
+      *reinterpret_cast<uint32_t*>(&C.h[cpar].v[col + 32][2 * ck]) = h;
+      *reinterpret_cast<uint32_t*>(&C.l[cpar].v[col + 32][2 * ck]) = lw;
     }
   };
 
@@ -284,11 +302,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     if (MODE != TABLE) {
       // wave-uniform: every lane is past its seeds and the chunk ends inside l <= lmax,
       // so the steps need no selects (the general form handles seeds and the tail)
-      if (l0 > wls + 1 && l0 + LCH - 1 <= lmax) {
-        lambda_chunk<PREC, true>(l0, m, lmax, rr, xx, ls, s0, s1, l1, l2, Lh, Ll);
-      } else {
-        lambda_chunk<PREC, false>(l0, m, lmax, rr, xx, ls, s0, s1, l1, l2, Lh, Ll);
-      }
+      const bool fast = l0 > wls + 1 && l0 + LCH - 1 <= lmax;
+      auto groups = [&](auto g0, auto g1) {
+        if (fast) lambda_chunk<PREC, true, g0, g1>(l0, m, lmax, rr, xx, ls, s0, s1, l1, l2, Lh, Ll);
+        else lambda_chunk<PREC, false, g0, g1>(l0, m, lmax, rr, xx, ls, s0, s1, l1, l2, Lh, Ll);
+      };
+      typedef std::integral_constant<int, 0> first;
+      typedef std::integral_constant<int, MODE == RECUR ? 2 : 0> mid;
+      typedef std::integral_constant<int, 8> last;
+      groups(first{}, mid{});
+      // staged once the first steps have covered their loads: held over the whole recurrence, the
+      // coefficients and its words spill (l_max 1000, 4 skies of 40 modes: 1.71 ms, 1.58 now)
+      if (MODE == RECUR) stage_coef(l0, C);
+      groups(mid{}, last{});
       // hand half 1 of lanes 0-31 and half 0 of lanes 32-63 across: afterwards
       // half 0 is the ring tile 0 operand and half 1 the ring tile 1 operand
 #pragma unroll
@@ -316,22 +342,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       continue;
     }
 
-    // ---- coefficient tile: qw_p(l) Re/Im a_lm, split, stored: words of l-indices 2 ck, + 1
-    //      (zero past lmax and for padding columns)
-    const bool oka = l0 + 4 * ck + cpar <= lmax, okb = l0 + 4 * ck + 2 + cpar <= lmax;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int col = cp0 + i;   // Re; Im 32 rows on
-      const bool ok = c0 + 2 * col < ncols;
-      const float q0 = vq[i][0], q1 = vq[i][1];
-      uint32_t h, lw;
-      split2<PREC>(ok && oka ? q0 * va[i][0].x : 0.f, ok && okb ? q1 * va[i][1].x : 0.f, h, lw);
-      *reinterpret_cast<uint32_t*>(&C.h[cpar].v[col][2 * ck]) = h;
-      *reinterpret_cast<uint32_t*>(&C.l[cpar].v[col][2 * ck]) = lw;
-      split2<PREC>(ok && oka ? q0 * va[i][0].y : 0.f, ok && okb ? q1 * va[i][1].y : 0.f, h, lw);
-      *reinterpret_cast<uint32_t*>(&C.h[cpar].v[col + 32][2 * ck]) = h;
-      *reinterpret_cast<uint32_t*>(&C.l[cpar].v[col + 32][2 * ck]) = lw;
-    }
+    if (MODE == TABLE) stage_coef(l0, C);
     __syncthreads();
 
     // ---- MFMA: per (parity, ring tile, column tile) a chain over the 2 K steps

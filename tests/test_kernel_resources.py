@@ -51,3 +51,11 @@ def test_ring_transforms_use_no_scratch_memory(built):
     rg = {k: v for k, v in built.items() if "_rg" in k}
     assert len(rg) >= 20 and any("3008" in k for k in rg)
     assert {k: v[".private_segment_fixed_size"] for k, v in rg.items() if v[".private_segment_fixed_size"]} == {}
+
+
+def test_split_synthesis_recurrence_does_not_spill(built):
+    """The split synthesis that runs the recurrence itself: accumulators, lambda's words and the
+    coefficients of a chunk fit its registers."""
+    recur = {k: v for k, v in built.items() if "k_legendre_splitILi2ELi0E" in k or "k_legendre_splitILi3ELi0E" in k}
+    assert len(recur) == 2
+    assert {v[".private_segment_fixed_size"] for v in recur.values()} == {0}
