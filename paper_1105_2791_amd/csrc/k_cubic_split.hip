@@ -409,7 +409,9 @@ __global__ __launch_bounds__(NT) void k_cubic_split(int P, int npairs, int npix,
         // so that consecutive MFMAs feed different accumulators (measured faster than the
         // pipelined order for bf16, whose split is twice the vector work of the fp16 one).  Kept
         // apart: with the compiler's mixture of the two, 4.94 instead of 4.85 ms (l_max 1000, P 40, 8
-        // skies, bf16) and 122 instead of 115 us (two modes' items on eight waves, fp16)
+        // skies, bf16) and 122 instead of 115 us (P 13 on eight waves, fp16); but not in bf16 with eight
+        // waves on one item (P up to 20), where the mixture is the faster (P 13 117 against 121 us, P 16
+        // 202 against 208 for two skies of 768 x 1536)
 #pragma unroll
         for (int i = 0; i < NSUB; ++i) {
           const int ks = sub * NSUB + i;
@@ -421,7 +423,7 @@ __global__ __launch_bounds__(NT) void k_cubic_split(int P, int npairs, int npix,
           vec8 ah[4], al[4];
 #pragma unroll
           for (int j = 0; j < 4; ++j) split_tile(R, j, ah[j], al[j]);
-          __builtin_amdgcn_sched_barrier(0);
+          if (F16 || MULT < 8) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int j = 0; j < 4; ++j) cha[j] = mfma32<PREC>(al[j], bh, cha[j]);
 #pragma unroll
