@@ -279,22 +279,26 @@ __global__ __launch_bounds__(256) void k_adj_legendre_mfma(int lmax, int ntheta,
 // (K = 16 rings, N = 32 l of one parity); lane l holds A[l % 32][8 (l / 32) + i] and
 // B[8 (l / 32) + i][l % 32]; accumulator register r is D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 // Both operands are split into bf16 hi + lo and each product is Ah Bh + Ah Bl + Al Bh.
-// Workgroup: 8 waves, one m, 256 consecutive l - m (wave w: the 32 l of parity w / 4 in
-// the quarter w % 4), 64 complex columns (4 tiles of 32 real columns).  The folded ring values
+// Workgroup: 4 waves, one m, 128 consecutive l - m (wave w: the 32 l of parity w / 2 in
+// the half w % 2), 64 complex columns (4 tiles of 32 real columns).  The folded ring values
 // of a 32-ring chunk are loaded two rings at a time, split and staged in LDS, double buffered; each lane loads the
 // lambda of its l at the 16 rings of its two K steps from the FP32 table one chunk ahead
 // and splits them in registers.  The workgroups of one m (l blocks x column blocks) run
 // back to back on one XCD, so lambda[m] and the ring values of m come from HBM about once.  An output takes
 // 3 nrp / 16 accumulations (144 at 768 rings); the truncation of the matrix core's
 // accumulation stays below the operand split error.
-// Bound by the staging's vector work and the latency of a chunk's loads (two waves per SIMD), so the
-// l block is as wide as the workgroup allows: every block of a column folds and splits the same
-// rings again.  64 planes of l_max 500, 768 rings: 225 us with 128 l and 4 waves, ring values loaded
-// one by one and selected behind branches, 173 now (the bytes take about 97); twice the planes per
-// transform, which reads lambda half as often, is slower (their spectra then miss the last-level cache).
+// Bound by the staging's vector work and the latency of a chunk's loads (two workgroups per CU).
+// The l blocks past l_max - m leave at once; workgroups are dealt to the shader engines of an XCD in
+// strict turn, so with 2 or 4 blocks per m in the same order for every m the same engines would
+// stay idle, and the blocks are rotated by m.  Gradient stage, 64 columns, with 256 l and 8 waves in
+// fixed order | 128 in fixed order | 128 rotated (ring values loaded one by one and selected behind
+// branches: the figure in front):  l_max 260 96: 112 | 91 | 91 us;  500 323: 274 | 299 | 260;
+// 511 329: 280 | 303 | 267;  768 831: 990 | 776 | 784;  1000 1760: 1728 | 1612 | 1484.  Twice the planes
+// per transform of a state, which reads lambda half as often, is slower (their spectra then miss
+// the last-level cache).
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-constexpr int AS_L = 256;         // l per workgroup (32 of one parity per wave)
+constexpr int AS_L = 128;         // l per workgroup (32 of one parity per wave)
 constexpr int AS_NT = 2 * AS_L;   // threads
 constexpr int AS_NC = 64;         // complex columns per workgroup
 constexpr int AS_RC = 32;         // rings per staged chunk (two K steps)
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(AS_NT) __attribute__((amdgpu_waves_per_eu(2))) void
   typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
   const int xcd = blockIdx.x & 7, i8 = blockIdx.x >> 3, per = nlb * ncb;
   const int m = xcd + 8 * (i8 / per);
-  const int lb = (i8 % per) / ncb, cb = (i8 % per) % ncb;
+  const int lb = ((i8 % per) / ncb + i8 / per) % nlb, cb = (i8 % per) % ncb;   // rotated, see above
   const int L = lmax + 1 - m;
   if (m > lmax || lb * AS_L >= L) return;   // whole workgroup, before any barrier
   const int c0 = cb * AS_NC;
@@ -336,8 +340,8 @@ __global__ __launch_bounds__(AS_NT) __attribute__((amdgpu_waves_per_eu(2))) void
   const size_t off = (size_t)m * (2 * lmax + 3 - m) / 2;
   const float* lrow = lam + off * nrp;
   __shared__ AsLds S;
-  const int par = wv >> 2;                        // the parity of l - m of this wave's rows
-  const int li = lb * AS_L + 64 * (wv & 3) + 2 * n + par;   // this lane's B column (l - m)
+  const int par = wv >> 1;                        // the parity of l - m of this wave's rows
+  const int li = lb * AS_L + 64 * (wv & 1) + 2 * n + par;   // this lane's B column (l - m)
   const int lcl = min(li, L - 1);
   // lambda at rings 32 c + 16 kk + 8 h + i of the lane's l for the two K steps kk of chunk c
   // (valid addresses for every c), loaded one chunk ahead

@@ -440,3 +440,17 @@ def test_batch_independence(lmax, ntheta, nphi, P, S, prec):
     for lo, hi in ((0, 1), (S // 2, S // 2 + 8), (S - 10, S)):
         assert torch.equal(c.linear_apply(st, a[lo:hi]), lin[lo:hi])
         assert torch.equal(c.beta(a[lo:hi], state=st), hat[lo:hi])
+
+
+# Adjoint of the bf16 contexts with two and four blocks of 128 l per m, whose order turns with m, the
+# last of them empty for most m, and with two blocks of columns.
+@pytest.mark.parametrize("lmax,ntheta,nphi,P,S", [(128, 130, 260, 13, 5), (385, 387, 772, 1, 1)])
+def test_bf16_adjoint_block_order(lmax, ntheta, nphi, P, S):
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 82)
+    print(f"[case] bf16 adjoint blocks lmax={lmax} {ntheta}x{nphi} P={P} S={S}", flush=True)
+    a = case.alms(0, S)
+    cot = np.random.default_rng(lmax).standard_normal((S, P * (P + 1) * (P + 2) // 6))
+    got = _ctx(case, "bf16x3").beta_vjp(a, cot).cpu().numpy()
+    for i in {0, S - 1}:
+        ref = om.vjp(a[i], case.cl, case.q, case.grid, None, cot[i])[0]
+        assert np.linalg.norm(got[i] - ref) <= 1e-4 * np.linalg.norm(ref)   # the map bound of these contexts
