@@ -102,15 +102,16 @@ __global__ __launch_bounds__(256) void k_pair_adjoint(int P, int npairs, int npi
 // accumulator register r is D[4 (l / 16) + r][l % 16]).  A = K of a 64-pair chunk (FP32,
 // in LDS), B = the pair product of the lane's pixel and pair, formed on the fly.  Each
 // chunk is a chain of 16 MFMAs from zero, added to the running sums with a vector add.
-// A wave owns 64 pixels, four column tiles, so that a K value and a pair read from LDS serve
-// four products; the map rows are 272 floats apart, 16 banks, so that the four neighbouring
-// pairs of a step read different banks.  The row tiles are as many as P needs.  Bound by
-// the matrix cores.  Four skies of 768 x 1536 pixels, P 30: 2.52 ms with three row tiles for
-// every P, two column tiles and the four pairs on one bank; 1.69 ms now (89 TF with the row tile padding).
+// A wave owns 32 pixels, two column tiles; the map rows are 144 floats apart, 16 banks, so that
+// the four neighbouring pairs of a step read different banks.  The row tiles are as many as P
+// needs.  Bound by the matrix cores.  Four skies of 768 x 1536 pixels, P 30: 2.67 ms with three row
+// tiles for every P and the four pairs on one bank; 1.52 ms now (100 TF with the row tile padding).
+// Four column tiles, whose K values and pairs serve twice the products, leave fewer waves per SIMD
+// and fewer workgroups: 1.69 ms there, and 88 us against 57 for two skies of 48 x 96 pixels, P 40.
 // The S skies of one pixel block are consecutive workgroups on one XCD (workgroups are
 // dealt to the 8 XCDs round-robin).
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-constexpr int kMx = 256;        // pixels per workgroup (64 per wave: four 16-column tiles)
+constexpr int kMx = 128;        // pixels per workgroup (32 per wave: two 16-column tiles)
 constexpr int kMs = kMx + 16;   // LDS row stride of the maps
 constexpr int kMc = 64;         // pairs per staged chunk (16 MFMA steps of 4)
 constexpr int kMt = 3;          // 16-mode tiles at most (P <= 48)
@@ -141,9 +142,9 @@ __global__ __launch_bounds__(256) void k_pair_adjoint_f32(int P, int npairs, int
     const float v = Ms[(size_t)p * npix + min(x0 + xx, npix - 1)];
     Mt[p * kMs + xx] = x0 + xx < npix ? v : 0.f;
   }
-  f32x4 acc[4][NT];
+  f32x4 acc[2][NT];
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+  for (int c = 0; c < 2; ++c)
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   const double* Kslab = K + (size_t)s * P * npairs;
@@ -170,34 +171,34 @@ __global__ __launch_bounds__(256) void k_pair_adjoint_f32(int P, int npairs, int
     if (tid < kMc) sab[tid] = make_int2(pa * kMs, pb * kMs);   // pairs past the last repeat it against K = 0
     __syncthreads();
     load_chunk(c0 + kMc);
-    f32x4 ch[4][NT];
+    f32x4 ch[2][NT];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int t = 0; t < NT; ++t) ch[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const float* Mx = Mt + 64 * wv + l16;
+    const float* Mx = Mt + 32 * wv + l16;
     const int nks = (nc + 3) / 4;
     for (int ks = 0; ks < nks; ++ks) {
       const int pc = 4 * ks + kq;
       const int2 ab = sab[pc];
-      float b[4], av[NT];
+      float b[2], av[NT];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) b[c] = Mx[ab.x + 16 * c] * Mx[ab.y + 16 * c];
+      for (int c = 0; c < 2; ++c) b[c] = Mx[ab.x + 16 * c] * Mx[ab.y + 16 * c];
 #pragma unroll
       for (int t = 0; t < NT; ++t) av[t] = Ks[16 * t + l16][pc];
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) ch[c][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t], b[c], ch[c][t], 0, 0, 0);
+        for (int c = 0; c < 2; ++c) ch[c][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t], b[c], ch[c][t], 0, 0, 0);
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[c][t] += ch[c][t];
   }
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int x = x0 + 64 * wv + 16 * c + l16;
+  for (int c = 0; c < 2; ++c) {
+    const int x = x0 + 32 * wv + 16 * c + l16;
     if (x >= npix) continue;
     const float wx = w[x];
 #pragma unroll
