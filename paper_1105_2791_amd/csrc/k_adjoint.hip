@@ -12,6 +12,8 @@
 // contraction (k_fft.hip, k_fisher.hip).
 #include "common.h"
 
+#include <type_traits>
+
 namespace modal {
 namespace {
 
@@ -448,10 +450,12 @@ __global__ __launch_bounds__(64 * SG_NW) __attribute__((amdgpu_waves_per_eu(2)))
     }
   };
   // Software pipeline: the A operands, map words and pair products of step t + 1 are read
-  // and formed among the MFMAs of step t (for the last step, those of the last step again,
-  // unused).  A chunks: chunks 0 and 1 are staged before the loop; in step t a barrier
-  // (all waves are then past their reads of chunk t's operands, and chunk t + 1 is visible)
-  // is followed by the store of chunk t + 2 into chunk t's buffer.
+  // and formed among the MFMAs of step t.  The last step only multiplies: with the next step's
+  // operands formed once more for nothing, P 20 (11 steps) took 612 us for four skies of 768 x 1536
+  // pixels, 578 now, P 17 574 and 540, P 40 251 and 248 (two skies of 400 x 640).  A chunks: chunks
+  // 0 and 1 are staged before the loop; in step t a barrier (all waves are then past their reads
+  // of chunk t's operands, and chunk t + 1 is visible) is followed by the store of chunk t + 2 into
+  // chunk t's buffer.
   load_chunk(0);
   store_chunk(0);
   load_chunk(1);
@@ -467,19 +471,21 @@ __global__ __launch_bounds__(64 * SG_NW) __attribute__((amdgpu_waves_per_eu(2)))
   }
   read_a(0, ah, al);
   int link = 0;
-  for (int t = 0; t < nch; ++t) {
-    const int tn = min(t + 1, nch - 1);
-    __syncthreads();
-    if (t + 2 < nch) store_chunk(t & 1);
-    load_chunk(t + 3);
-    const int gv = group(tn);
+  auto step = [&](int t, auto last_) {
+    constexpr bool last = decltype(last_)::value;
     f16x8 ahn[NT], aln[NT];
-    read_a(tn, ahn, aln);
-    Maps Rn[2];
-    read_maps(gv, 0, Rn[0]);
+    int gv = 0;
+    if (!last) {
+      __syncthreads();
+      if (t + 2 < nch) store_chunk(t & 1);
+      load_chunk(t + 3);
+      gv = group(t + 1);
+      read_a(t + 1, ahn, aln);
+    }
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
-      if (ct < 3) read_maps(gv, ct + 1, Rn[(ct + 1) & 1]);
+      Maps Rn;
+      if (!last) read_maps(gv, ct, Rn);
       // product by product over the row tiles, so that consecutive MFMAs feed different sums
 #pragma unroll
       for (int mt = 0; mt < NT; ++mt) cc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[mt], bh[ct], cc[mt][ct], 0, 0, 0);
@@ -487,14 +493,16 @@ __global__ __launch_bounds__(64 * SG_NW) __attribute__((amdgpu_waves_per_eu(2)))
       for (int mt = 0; mt < NT; ++mt) cc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[mt], bl[ct], cc[mt][ct], 0, 0, 0);
 #pragma unroll
       for (int mt = 0; mt < NT; ++mt) cc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[mt], bh[ct], cc[mt][ct], 0, 0, 0);
-      make_b(Rn[ct & 1], bh[ct], bl[ct]);
+      if (!last) make_b(Rn, bh[ct], bl[ct]);
     }
+    if (!last) {
 #pragma unroll
-    for (int mt = 0; mt < NT; ++mt) {
-      ah[mt] = ahn[mt];
-      al[mt] = aln[mt];
+      for (int mt = 0; mt < NT; ++mt) {
+        ah[mt] = ahn[mt];
+        al[mt] = aln[mt];
+      }
     }
-    if (++link == SG_CH || t + 1 == nch) {   // chains of SG_CH steps join the running sums
+    if (++link == SG_CH || last) {   // chains of SG_CH steps join the running sums
       link = 0;
 #pragma unroll
       for (int mt = 0; mt < NT; ++mt)
@@ -504,7 +512,9 @@ __global__ __launch_bounds__(64 * SG_NW) __attribute__((amdgpu_waves_per_eu(2)))
           cc[mt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
-  }
+  };
+  for (int t = 0; t + 1 < nch; ++t) step(t, std::false_type{});
+  step(nch - 1, std::true_type{});
   const float up = sc[s].y;   // 2^E
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
