@@ -170,12 +170,13 @@ size_t ws_size(const modal_ctx* c, int op, int S) {
     case MODAL_OP_FILTER_MAPS: cv.take(F_bytes(c, S)); break;
     case MODAL_OP_BETA:
     case MODAL_OP_BETA_LOO:
-      cv.take(F_bytes(c, S)); cv.take(maps_bytes(c, S)); cv.take(part_bytes(c, S)); cv.take(E_bytes(c, S));
+      cv.take(F_bytes(c, S)); cv.take(maps_bytes(c, S)); cv.take(part_bytes(c, S));
       cv.take(X_bytes(c, S)); cv.take(E_bytes(c, S));
       break;
     case MODAL_OP_LINEAR_APPLY: cv.take(X_bytes(c, S)); cv.take(E_bytes(c, S)); break;
     case MODAL_OP_LINEAR_FINALIZE:
-      cv.take(lam_bytes(c)); cv.take((size_t)fin_chunk(c) * c->npix * real_bytes(c));
+      cv.take(lam_bytes(c));
+      if (!c->fft_rg) cv.take((size_t)fin_chunk(c) * c->npix * real_bytes(c));
       cv.take((size_t)fin_chunk(c) * c->ntheta * (c->lmax + 1) * 2 * real_bytes(c));
       break;
     case MODAL_OP_LINEAR_ACCUMULATE: cv.take(F_bytes(c, S)); cv.take(maps_bytes(c, S)); break;
@@ -750,7 +751,6 @@ modal_status modal_beta(modal_ctx* c, const void* alm, int S, const void* state,
   void* F = cv.take(F_bytes(c, S));
   void* maps = cv.take(maps_bytes(c, S));
   double* part = part_region(c, F, cv.take(part_bytes(c, S)));
-  cv.take(E_bytes(c, S));
   double* X = (double*)cv.take(X_bytes(c, S));
   double* L = (double*)cv.take(E_bytes(c, S));
   if ((s = run_maps(c, alm, S, F, maps, st)) != MODAL_OK) return s;
@@ -773,7 +773,6 @@ modal_status modal_beta_loo(modal_ctx* c, const void* alm, int S, const void* st
   void* F = cv.take(F_bytes(c, S));
   void* maps = cv.take(maps_bytes(c, S));
   double* part = part_region(c, F, cv.take(part_bytes(c, S)));
-  cv.take(E_bytes(c, S));
   double* X = (double*)cv.take(X_bytes(c, S));
   double* L = (double*)cv.take(E_bytes(c, S));
   if ((s = run_maps(c, alm, S, F, maps, st)) != MODAL_OK) return s;
@@ -842,7 +841,7 @@ modal_status modal_linear_term(modal_ctx* c, int mode, const void* alm, int S, v
       Carver cv(ws);
       void* lam = cv.take(lam_bytes(c));
       const int nch = fin_chunk(c);
-      void* G = cv.take((size_t)nch * c->npix * real_bytes(c));
+      void* G = c->fft_rg ? nullptr : cv.take((size_t)nch * c->npix * real_bytes(c));
       void* Gh = cv.take((size_t)nch * c->ntheta * (c->lmax + 1) * 2 * real_bytes(c));
       STAGE(MODAL_STAGE_ADJ_LEGENDRE, launch_lambda_table(c, lam, st));
       char* Z = (char*)state + lin_V_bytes(c);

@@ -454,3 +454,50 @@ def test_bf16_adjoint_block_order(lmax, ntheta, nphi, P, S):
     for i in {0, S - 1}:
         ref = om.vjp(a[i], case.cl, case.q, case.grid, None, cot[i])[0]
         assert np.linalg.norm(got[i] - ref) <= 1e-4 * np.linalg.norm(ref)   # the map bound of these contexts
+
+
+# Workspaces hold what their call uses and no more: their sizes by region, and results with a buffer
+# of exactly that size, whose neighbourhood stays untouched.  Ring transforms with a register-pass
+# plan (a state's rows are weighted as they are loaded: no plane of them) and the general one.
+@pytest.mark.parametrize("prec,nphi", [("f32", 96), ("bf16x3", 96), ("f32", 94), ("f64", 96)])
+def test_workspaces_hold_what_is_used(prec, nphi):
+    from paper_1105_2791_amd import _lib as L
+    lmax, ntheta, P, S = 32, 48, 12, 2
+    case = Case("edge", lmax, ntheta, nphi, P, S, "wmap", 83)
+    print(f"[case] workspaces {prec} {ntheta}x{nphi}", flush=True)
+    c = _ctx(case, prec)
+    rb, npairs, planes = c.real_dtype.itemsize, P * (P + 1) // 2, min(P * (P + 1) // 2, 64)
+    F, maps, Lrow = S * P * ((ntheta + 7) // 8) * 8 * (lmax + 1) * 2 * rb, S * P * ntheta * nphi * rb, S * npairs * P * 8
+    X = S * npairs * (lmax + 1) * 8
+
+    def size(*regions):
+        return sum((b + 255) // 256 * 256 for b in regions)
+    part = c.workspace_size(L.OP_BETA, S) - size(F, maps, X, Lrow)
+    assert part > 0 and part % Lrow < 256   # the contraction's chunks alone, [S][chunk][pairs][P]
+    lam, Gh = c.nalm * ((ntheta + 1) // 2) * rb, planes * ntheta * (lmax + 1) * 2 * rb
+    general = prec == "f64" or nphi == 94
+    assert c.workspace_size(L.OP_LINEAR_FINALIZE, 1) == size(lam, *([planes * ntheta * nphi * rb] if general else []), Gh)
+
+    a, mc = case.alms(0, S), case.alms(60, 3)
+    guard = 4096
+
+    def run():
+        st = c.linear_state()
+        c.linear_reset(st)
+        c.linear_accumulate(st, mc)
+        c.linear_finalize(st)
+        return c.beta(a, state=st), c.beta(a), c.beta_loo(mc[:2], st)
+    ref = run()
+    bufs = []
+
+    def exact(op, n):
+        need = c.workspace_size(op, n)
+        t = torch.full((need + 2 * guard,), 255, dtype=torch.uint8, device="cuda")
+        bufs.append((t, need))
+        return t[guard:guard + need]
+    c.workspace = exact
+    got = run()
+    for x, y in zip(got, ref):
+        assert torch.equal(x, y)
+    for t, need in bufs:
+        assert bool((t[:guard] == 255).all()) and bool((t[guard + need:] == 255).all())
