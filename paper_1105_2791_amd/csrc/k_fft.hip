@@ -423,11 +423,12 @@ __device__ inline void rg_order() {
 // the arguments), so that the index arithmetic of a specialised plan folds to constants
 // WPR: the waves that share a ring (lane counts through them); with two, every wave of the
 // workgroup runs the pass and barriers keep its order
-// Always inlined where the plan is compiled in: called, a pass of 47 x 8 x 8 keeps 296 bytes per lane
-// in memory.  A plan run from its arguments leaves it to the compiler (rg_pass_args): with every
-// radix inlined its kernels of 32 and 48 points hold one wave per SIMD instead of two.
+// Called with [[clang::always_inline]] where the plan is compiled in: as a function, a pass of
+// 47 x 8 x 8 keeps 296 bytes per lane in memory.  A plan run from its arguments leaves it to the
+// compiler: inlined for every radix its kernels of 32 and 48 points hold one wave per SIMD instead of
+// two, and the twiddle products are contracted into other FMAs.
 template <int R, int PTS, bool OUT = false, int KC = 0, int NSC = 0, int WPR = 1>
-__device__ __forceinline__ void rg_pass(float2* b, int K_, int Ns_, int lane, const float2* twp, float2* out = nullptr) {
+__device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float2* twp, float2* out = nullptr) {
   static_assert(WPR == 1 || KC, "shared rings: compiled-in plans only");
   constexpr int NB = KC ? (KC / R + 64 * WPR - 1) / (64 * WPR) : (PTS + R - 1) / R;
   const int K = KC ? KC : K_;
@@ -468,11 +469,6 @@ __device__ __forceinline__ void rg_pass(float2* b, int K_, int Ns_, int lane, co
   if (WPR == 1 || !OUT) rg_order<WPR>();
 }
 
-template <int R, int PTS, bool OUT = false>
-__device__ inline void rg_pass_args(float2* b, int K, int Ns, int lane, const float2* twp, float2* out = nullptr) {
-  rg_pass<R, PTS, OUT>(b, K, Ns, lane, twp, out);
-}
-
 // cos and sin of 2 pi j / 47, j < 47, rounded to float
 __device__ constexpr float kC47[47] = {
     1.0f, 0.991077488f, 0.964469175f, 0.920649887f, 0.860401579f, 0.784799385f, 0.695192428f,
@@ -502,7 +498,7 @@ __device__ constexpr float kS47[47] = {
 // program order, of two by a barrier), so the pass is in place.  Of two waves both form all
 // sums s, d and half the outputs each.
 template <int WPR = 1>
-__device__ __forceinline__ void rg_pass47_first(float2* b, int lane, int half = 0) {
+__device__ inline void rg_pass47_first(float2* b, int lane, int half = 0) {
   float2 x[47];
 #pragma unroll
   for (int r = 0; r < 47; ++r) x[r] = b[padr(lane + 64 * r)];
@@ -632,20 +628,20 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
     float2* dst = (j < ntheta) ? reinterpret_cast<float2*>(maps + ((size_t)seq * ntheta + j) * plan.N) : nullptr;
     if constexpr (KC == 1536) {
       // passes 24, 8, 8 (strides 1, 24, 192; twiddle tables at 0, 23, 23 + 7 * 24)
-      rg_pass<24, PTS, false, KC, 1>(bw, K, 1, lane, twp);
-      rg_pass<8, PTS, false, KC, 24>(bw, K, 24, lane, twp + 23);
-      rg_pass<8, PTS, true, KC, 192>(bw, K, 192, lane, twp + 23 + 7 * 24, dst);
+      [[clang::always_inline]] rg_pass<24, PTS, false, KC, 1>(bw, K, 1, lane, twp);
+      [[clang::always_inline]] rg_pass<8, PTS, false, KC, 24>(bw, K, 24, lane, twp + 23);
+      [[clang::always_inline]] rg_pass<8, PTS, true, KC, 192>(bw, K, 192, lane, twp + 23 + 7 * 24, dst);
     } else if constexpr (KC == 768) {
       // passes 8, 8, 4, 3 (strides 1, 8, 64, 256; twiddle tables at 0, 7, 63, 255)
-      rg_pass<8, PTS, false, KC, 1>(bw, K, 1, lane, twp);
-      rg_pass<8, PTS, false, KC, 8>(bw, K, 8, lane, twp + 7);
-      rg_pass<4, PTS, false, KC, 64>(bw, K, 64, lane, twp + 63);
-      rg_pass<3, PTS, true, KC, 256>(bw, K, 256, lane, twp + 255, dst);
+      [[clang::always_inline]] rg_pass<8, PTS, false, KC, 1>(bw, K, 1, lane, twp);
+      [[clang::always_inline]] rg_pass<8, PTS, false, KC, 8>(bw, K, 8, lane, twp + 7);
+      [[clang::always_inline]] rg_pass<4, PTS, false, KC, 64>(bw, K, 64, lane, twp + 63);
+      [[clang::always_inline]] rg_pass<3, PTS, true, KC, 256>(bw, K, 256, lane, twp + 255, dst);
     } else if constexpr (KC == 3008) {
       // passes 47, 8, 8 (strides 1, 47, 376; twiddle tables at 46, 46 + 7 * 47)
-      rg_pass47_first<WPR>(bw, lane & 63, wv % WPR);
-      rg_pass<8, PTS, false, KC, 47, WPR>(bw, K, 47, lane, twp + 46);
-      rg_pass<8, PTS, true, KC, 376, WPR>(bw, K, 376, lane, twp + 46 + 7 * 47, dst);
+      [[clang::always_inline]] rg_pass47_first<WPR>(bw, lane & 63, wv % WPR);
+      [[clang::always_inline]] rg_pass<8, PTS, false, KC, 47, WPR>(bw, K, 47, lane, twp + 46);
+      [[clang::always_inline]] rg_pass<8, PTS, true, KC, 376, WPR>(bw, K, 376, lane, twp + 46 + 7 * 47, dst);
     } else {
       int Ns = 1;
       const float2* tf = twp;
@@ -654,13 +650,13 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
       const bool direct = plan.radix[plan.nf - 1] == 8;
       for (int f = 0; f < plan.nf; ++f) {
         const int R = plan.radix[f];
-        if (direct && f == plan.nf - 1) rg_pass_args<8, PTS, true>(bw, K, Ns, lane, tf, dst);
-        else if (R == 8) rg_pass_args<8, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 4) rg_pass_args<4, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 2) rg_pass_args<2, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 3) rg_pass_args<3, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 5) rg_pass_args<5, PTS>(bw, K, Ns, lane, tf);
-        else if constexpr (PTS >= 24) rg_pass_args<24, PTS>(bw, K, Ns, lane, tf);
+        if (direct && f == plan.nf - 1) rg_pass<8, PTS, true>(bw, K, Ns, lane, tf, dst);
+        else if (R == 8) rg_pass<8, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 4) rg_pass<4, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 2) rg_pass<2, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 3) rg_pass<3, PTS>(bw, K, Ns, lane, tf);
+        else if (R == 5) rg_pass<5, PTS>(bw, K, Ns, lane, tf);
+        else if constexpr (PTS >= 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
         tf += (R - 1) * Ns;
         Ns *= R;
       }
@@ -789,29 +785,29 @@ __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_r2c_rg(FftPlan plan, int 
       }
       wave_order();
       if constexpr (KC == 1536) {
-        rg_pass<24, PTS, false, KC, 1>(bw, K, 1, lane, twp);
-        rg_pass<8, PTS, false, KC, 24>(bw, K, 24, lane, twp + 23);
-        rg_pass<8, PTS, false, KC, 192>(bw, K, 192, lane, twp + 23 + 7 * 24);
+        [[clang::always_inline]] rg_pass<24, PTS, false, KC, 1>(bw, K, 1, lane, twp);
+        [[clang::always_inline]] rg_pass<8, PTS, false, KC, 24>(bw, K, 24, lane, twp + 23);
+        [[clang::always_inline]] rg_pass<8, PTS, false, KC, 192>(bw, K, 192, lane, twp + 23 + 7 * 24);
       } else if constexpr (KC == 768) {
-        rg_pass<8, PTS, false, KC, 1>(bw, K, 1, lane, twp);
-        rg_pass<8, PTS, false, KC, 8>(bw, K, 8, lane, twp + 7);
-        rg_pass<4, PTS, false, KC, 64>(bw, K, 64, lane, twp + 63);
-        rg_pass<3, PTS, false, KC, 256>(bw, K, 256, lane, twp + 255);
+        [[clang::always_inline]] rg_pass<8, PTS, false, KC, 1>(bw, K, 1, lane, twp);
+        [[clang::always_inline]] rg_pass<8, PTS, false, KC, 8>(bw, K, 8, lane, twp + 7);
+        [[clang::always_inline]] rg_pass<4, PTS, false, KC, 64>(bw, K, 64, lane, twp + 63);
+        [[clang::always_inline]] rg_pass<3, PTS, false, KC, 256>(bw, K, 256, lane, twp + 255);
       } else if constexpr (KC == 3008) {
-        rg_pass47_first(bw, lane);
-        rg_pass<8, PTS, false, KC, 47>(bw, K, 47, lane, twp + 46);
-        rg_pass<8, PTS, false, KC, 376>(bw, K, 376, lane, twp + 46 + 7 * 47);
+        [[clang::always_inline]] rg_pass47_first(bw, lane);
+        [[clang::always_inline]] rg_pass<8, PTS, false, KC, 47>(bw, K, 47, lane, twp + 46);
+        [[clang::always_inline]] rg_pass<8, PTS, false, KC, 376>(bw, K, 376, lane, twp + 46 + 7 * 47);
       } else {
         int Ns = 1;
         const float2* tf = twp;
         for (int f = 0; f < plan.nf; ++f) {
           const int R = plan.radix[f];
-          if (R == 8) rg_pass_args<8, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 4) rg_pass_args<4, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 2) rg_pass_args<2, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 3) rg_pass_args<3, PTS>(bw, K, Ns, lane, tf);
-          else if (R == 5) rg_pass_args<5, PTS>(bw, K, Ns, lane, tf);
-          else if constexpr (PTS >= 24) rg_pass_args<24, PTS>(bw, K, Ns, lane, tf);
+          if (R == 8) rg_pass<8, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 4) rg_pass<4, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 2) rg_pass<2, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 3) rg_pass<3, PTS>(bw, K, Ns, lane, tf);
+          else if (R == 5) rg_pass<5, PTS>(bw, K, Ns, lane, tf);
+          else if constexpr (PTS >= 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
           tf += (R - 1) * Ns;
           Ns *= R;
         }
