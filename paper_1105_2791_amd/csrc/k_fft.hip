@@ -434,6 +434,12 @@ __device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float
   const int K = KC ? KC : K_;
   const int Ns = NSC ? NSC : Ns_;
   const int KR = K / R;
+  // plans of at most 24 points run from their arguments: LDS addresses formed anew in every pass (kept
+  // over the loop for all radices they fill the registers), and bi / Ns as the high word of bi rNs (Ns > 1;
+  // both below 2^16)
+  constexpr bool mul = !NSC && PTS <= 24;
+  if (mul) asm volatile("" : "+v"(lane));
+  const uint32_t rNs = mul ? 0xffffffffu / (uint32_t)Ns + 1 : 0;
   float2 v[NB][R];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
@@ -448,13 +454,14 @@ __device__ inline void rg_pass(float2* b, int K_, int Ns_, int lane, const float
   for (int i = 0; i < NB; ++i) {
     const int bi = lane + 64 * WPR * i;
     if (bi < KR) {
-      const int k = bi % Ns;
+      const int d = !mul ? bi / Ns : Ns == 1 ? bi : (int)__umulhi((uint32_t)bi, rNs);
+      const int k = mul ? bi - d * Ns : bi % Ns;
       if (NSC != 1) {   // (the first pass's twiddles are all 1)
 #pragma unroll
         for (int q = 1; q < R; ++q) v[i][q] = cmulf(v[i][q], twp[(q - 1) * Ns + k]);
       }
       dft_plus<R>(v[i]);
-      const int ob = (bi / Ns) * Ns * R + k;
+      const int ob = d * Ns * R + k;
       if (OUT) {
         if (out) {
 #pragma unroll
@@ -542,16 +549,12 @@ __device__ inline void rg_pass47_first(float2* b, int lane, int half = 0) {
   rg_order<WPR>();
 }
 
-template <int PTS, int KC, int WPR = 1>
+template <int PTS, int KC, int WPR = 1, int ZE = 4>
 __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, int nseq,
                                             const float2* __restrict__ F, float* __restrict__ maps,
                                             const float2* __restrict__ twg, const float2* __restrict__ twpg) {
   extern __shared__ __attribute__((aligned(16))) float2 rbuf[];
-  // KC: a plan compiled in (24 x 8 x 8 of K = 1536, 47 x 8 x 8 of 3008, 8 x 8 x 4 x 3 of 768).
-  // The last keeps K an argument outside the passes: with it constant the compiler contracts
-  // the spectrum formula below into other FMAs, and the maps would differ in their last bit
-  // from the plan run with all its lengths as arguments.
-  const int K = KC && KC != 768 ? KC : plan.K;
+  const int K = KC ? KC : plan.K;   // KC: a plan compiled in (24 x 8 x 8 of K = 1536, 47 x 8 x 8 of 3008)
   const int KP = padr(K) + 1;
   float2* tw = rbuf + RG_RINGS * KP;   // e^{2 pi i t / N}, t <= K / 2, shared by the workgroup's rings
   float2* twp = tw + K / 2 + 1;          // the passes' twiddle tables, K - 1 entries in all
@@ -567,12 +570,10 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
   const int b = blockIdx.x;
   const int xcd = b & 7, half = (b >> 3) & 1, slot = b >> 4;
   const int nslot = gridDim.x >> 4;
-  // Spectrum loads: ZE elements per thread per round, as many as the register budget holds
-  // (rounds of 4, one of 6 or 3: 8 skies of 768 x 1536 pixels, 30 modes, 0.52 -> 0.46 ms; of
-  // 1536 x 3072, 40 modes, 2.35 -> 2.20; everything of a unit in one round costs a wave per SIMD).
-  // 3008 with two waves per ring: 12 8.88 ms, 6 8.27, 4 8.07, 3 7.99; the next round's or unit's
-  // loads ahead of their use 8.3 to 8.7.
-  constexpr int ZE = KC == 3008 ? 3 : KC == 1536 ? 6 : KC == 768 ? 3 : 4;
+  // Spectrum loads: ZE elements per thread per round, as many as the register budget holds: two waves per
+  // SIMD of the compiled plans 6 (8 skies of 1536 x 3072 pixels, 40 modes, 2.35 ms with 4, 2.20 with 6) and,
+  // two waves to a ring of 3008, 3 (12 8.88 ms, 6 8.27, 4 8.07, 3 7.99; the next round's or unit's loads
+  // ahead of their use 8.3 to 8.7); of the others 4 or 3, whichever fills its rounds better.
   typedef float f4 __attribute__((ext_vector_type(4)));
   f4 xa[ZE], xb[ZE];
   auto load_spectra = [&](int unit, int e0) {
@@ -631,12 +632,6 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
       [[clang::always_inline]] rg_pass<24, PTS, false, KC, 1>(bw, K, 1, lane, twp);
       [[clang::always_inline]] rg_pass<8, PTS, false, KC, 24>(bw, K, 24, lane, twp + 23);
       [[clang::always_inline]] rg_pass<8, PTS, true, KC, 192>(bw, K, 192, lane, twp + 23 + 7 * 24, dst);
-    } else if constexpr (KC == 768) {
-      // passes 8, 8, 4, 3 (strides 1, 8, 64, 256; twiddle tables at 0, 7, 63, 255)
-      [[clang::always_inline]] rg_pass<8, PTS, false, KC, 1>(bw, K, 1, lane, twp);
-      [[clang::always_inline]] rg_pass<8, PTS, false, KC, 8>(bw, K, 8, lane, twp + 7);
-      [[clang::always_inline]] rg_pass<4, PTS, false, KC, 64>(bw, K, 64, lane, twp + 63);
-      [[clang::always_inline]] rg_pass<3, PTS, true, KC, 256>(bw, K, 256, lane, twp + 255, dst);
     } else if constexpr (KC == 3008) {
       // passes 47, 8, 8 (strides 1, 47, 376; twiddle tables at 46, 46 + 7 * 47)
       [[clang::always_inline]] rg_pass47_first<WPR>(bw, lane & 63, wv % WPR);
@@ -645,34 +640,46 @@ __device__ __forceinline__ void c2r_rg_body(FftPlan plan, int lmax, int ntheta, 
     } else {
       int Ns = 1;
       const float2* tf = twp;
-      // (a last pass of radix 8, the common case, stores straight to the row; other plans
-      // finish in LDS and copy the row out; radix 24 occurs only where 24 points fit a lane)
-      const bool direct = plan.radix[plan.nf - 1] == 8;
+      // (the last pass stores straight to the row; of more than 24 points per lane only one of radix 8,
+      // the others finish in LDS and copy the row out.  Radix 24, which comes first, occurs only
+      // where 24 points fit a lane)
+      const bool direct = PTS <= 24 || plan.radix[plan.nf - 1] == 8;
       for (int f = 0; f < plan.nf; ++f) {
         const int R = plan.radix[f];
-        if (direct && f == plan.nf - 1) rg_pass<8, PTS, true>(bw, K, Ns, lane, tf, dst);
-        else if (R == 8) rg_pass<8, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 4) rg_pass<4, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 2) rg_pass<2, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 3) rg_pass<3, PTS>(bw, K, Ns, lane, tf);
-        else if (R == 5) rg_pass<5, PTS>(bw, K, Ns, lane, tf);
-        else if constexpr (PTS >= 24) rg_pass<24, PTS>(bw, K, Ns, lane, tf);
+        auto pass = [&](auto last) {
+          constexpr bool OUT = decltype(last)::value, ANY = !OUT || PTS <= 24;
+          if (R == 8) rg_pass<8, PTS, OUT>(bw, K, Ns, lane, tf, dst);
+          else if constexpr (ANY) {
+            if (R == 4) rg_pass<4, PTS, OUT>(bw, K, Ns, lane, tf, dst);
+            else if (R == 2) rg_pass<2, PTS, OUT>(bw, K, Ns, lane, tf, dst);
+            else if (R == 3) rg_pass<3, PTS, OUT>(bw, K, Ns, lane, tf, dst);
+            else if (R == 5) rg_pass<5, PTS, OUT>(bw, K, Ns, lane, tf, dst);
+            else if constexpr (PTS >= 24) rg_pass<24, PTS, OUT>(bw, K, Ns, lane, tf, dst);
+          }
+        };
+        if (direct && f == plan.nf - 1) pass(std::true_type{});
+        else pass(std::false_type{});
         tf += (R - 1) * Ns;
         Ns *= R;
       }
       if (!direct && dst) {
         for (int n = lane; n < K; n += 64) dst[n] = bw[padr(n)];
       }
+      if (plan.nf == 0 && dst && lane == 0) dst[0] = bw[0];   // rings of two pixels
     }
   }
 }
 
-template <int PTS>
-__global__ __launch_bounds__(64 * RG_RINGS) void k_fft_c2r_rg(FftPlan plan, int lmax, int ntheta, int nseq,
-                                                              const float2* __restrict__ F, float* __restrict__ maps,
-                                                              const float2* __restrict__ twg,
-                                                              const float2* __restrict__ twpg) {
-  c2r_rg_body<PTS, 0>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
+// Plans run from their arguments.  What bounded those of at most 24 points per lane was registers: with
+// the LDS addresses of every radix kept over the ring loop 172 of them and two waves per SIMD (240 above
+// 16 points).  Formed anew in each pass they leave 94 (five waves), with the division by Ns a
+// multiplication and every last pass storing to the row: 80 planes of 420 rings at nphi 1440
+// 165 -> 106 us, 1600 155 -> 104, 768 rings at nphi 1536 263 -> 177, 440 rings at nphi 2400 175 -> 162.
+template <int PTS, int ZE = 4>
+__global__ __launch_bounds__(64 * RG_RINGS) __attribute__((amdgpu_waves_per_eu(PTS <= 16 ? 4 : 1))) void k_fft_c2r_rg(
+    FftPlan plan, int lmax, int ntheta, int nseq, const float2* __restrict__ F, float* __restrict__ maps,
+    const float2* __restrict__ twg, const float2* __restrict__ twpg) {
+  c2r_rg_body<PTS, 0, 1, ZE>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
 }
 
 // the plan 24 x 8 x 8 of K = 1536 compiled in (the constant index arithmetic lets the
@@ -680,17 +687,7 @@ __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_c2r_rg(FftPlan plan, int 
 __global__ __launch_bounds__(64 * RG_RINGS) __attribute__((amdgpu_waves_per_eu(2))) void k_fft_c2r_rg_k1536(
     FftPlan plan, int lmax, int ntheta, int nseq, const float2* __restrict__ F, float* __restrict__ maps,
     const float2* __restrict__ twg, const float2* __restrict__ twpg) {
-  c2r_rg_body<24, 1536>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
-}
-
-// the plan 8 x 8 x 4 x 3 of K = 768 (the rings of nphi 1536, the l_max 500 grid): 117 registers
-// and four waves per SIMD where the plan run from its arguments takes 172 and two (8 skies of
-// 768 rings, 30 modes: 0.80 -> 0.46 ms, 4.1 TB/s, near the rate of a copy; r2c of 64 planes
-// 0.25 -> 0.15 ms)
-__global__ __launch_bounds__(64 * RG_RINGS) __attribute__((amdgpu_waves_per_eu(4))) void k_fft_c2r_rg_k768(
-    FftPlan plan, int lmax, int ntheta, int nseq, const float2* __restrict__ F, float* __restrict__ maps,
-    const float2* __restrict__ twg, const float2* __restrict__ twpg) {
-  c2r_rg_body<16, 768>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
+  c2r_rg_body<24, 1536, 1, 6>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
 }
 
 // the plan 47 x 8 x 8 of K = 3008 (the rings of nphi 6016, the l_max 2000 grid): its
@@ -702,7 +699,7 @@ constexpr int kW3008 = 2;   // waves per ring
 __global__ __launch_bounds__(64 * RG_RINGS * kW3008) __attribute__((amdgpu_waves_per_eu(2))) void k_fft_c2r_rg_k3008(
     FftPlan plan, int lmax, int ntheta, int nseq, const float2* __restrict__ F, float* __restrict__ maps,
     const float2* __restrict__ twg, const float2* __restrict__ twpg) {
-  c2r_rg_body<48, 3008, kW3008>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
+  c2r_rg_body<48, 3008, kW3008, 3>(plan, lmax, ntheta, nseq, F, maps, twg, twpg);
 }
 
 // r2c, register passes (the adjoint of k_fft_c2r_rg): same persistent ring-group order,
@@ -716,8 +713,8 @@ __global__ __launch_bounds__(64 * RG_RINGS * kW3008) __attribute__((amdgpu_waves
 // V = U scale (rounded to float, written back in place) and weighted, G = w V, as it is loaded;
 // as passes of their own over the planes the scaling and the weighting read and wrote 8 bytes
 // per pixel each (820 planes of 768 x 1536: 1.67 and 1.82 ms).
-template <int PTS, int KC = 0, bool STATE = false>
-__global__ __launch_bounds__(64 * RG_RINGS) void k_fft_r2c_rg(FftPlan plan, int lmax, int ntheta, int nseq,
+template <int PTS, int KC, bool STATE>
+__global__ __launch_bounds__(64 * RG_RINGS) __attribute__((amdgpu_waves_per_eu(PTS <= 16 ? 4 : 1))) void k_fft_r2c_rg(FftPlan plan, int lmax, int ntheta, int nseq,
                                                               std::conditional_t<STATE, float, const float>* __restrict__ G,
                                                               float2* __restrict__ Gh,
                                                               const float2* __restrict__ twg,
@@ -788,11 +785,6 @@ __global__ __launch_bounds__(64 * RG_RINGS) void k_fft_r2c_rg(FftPlan plan, int 
         [[clang::always_inline]] rg_pass<24, PTS, false, KC, 1>(bw, K, 1, lane, twp);
         [[clang::always_inline]] rg_pass<8, PTS, false, KC, 24>(bw, K, 24, lane, twp + 23);
         [[clang::always_inline]] rg_pass<8, PTS, false, KC, 192>(bw, K, 192, lane, twp + 23 + 7 * 24);
-      } else if constexpr (KC == 768) {
-        [[clang::always_inline]] rg_pass<8, PTS, false, KC, 1>(bw, K, 1, lane, twp);
-        [[clang::always_inline]] rg_pass<8, PTS, false, KC, 8>(bw, K, 8, lane, twp + 7);
-        [[clang::always_inline]] rg_pass<4, PTS, false, KC, 64>(bw, K, 64, lane, twp + 63);
-        [[clang::always_inline]] rg_pass<3, PTS, false, KC, 256>(bw, K, 256, lane, twp + 255);
       } else if constexpr (KC == 3008) {
         [[clang::always_inline]] rg_pass47_first(bw, lane);
         [[clang::always_inline]] rg_pass<8, PTS, false, KC, 47>(bw, K, 47, lane, twp + 46);
@@ -912,29 +904,20 @@ size_t fft_rg_lds(const modal_ctx* c) {
 }
 
 hipError_t fft_rg_set_lds(size_t bytes) {
-  hipError_t e = hipFuncSetAttribute((const void*)k_fft_c2r_rg<16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_fft_c2r_rg<24>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_fft_c2r_rg<32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_fft_c2r_rg<48>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)k_fft_c2r_rg_k1536, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)k_fft_c2r_rg_k3008, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  const void* r2c[] = {(const void*)k_fft_r2c_rg<16>,
-                       (const void*)k_fft_r2c_rg<24>,
-                       (const void*)k_fft_r2c_rg<32>,
-                       (const void*)k_fft_r2c_rg<48>,
-                       (const void*)k_fft_r2c_rg<24, 1536>,
-                       (const void*)k_fft_r2c_rg<48, 3008>,
-                       (const void*)k_fft_r2c_rg<16, 0, true>,
-                       (const void*)k_fft_r2c_rg<24, 0, true>,
-                       (const void*)k_fft_r2c_rg<32, 0, true>,
-                       (const void*)k_fft_r2c_rg<48, 0, true>,
-                       (const void*)k_fft_r2c_rg<24, 1536, true>,
-                       (const void*)k_fft_r2c_rg<48, 3008, true>};
-  for (const void* f : r2c)
-    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  return e;
+  // (the kernels of at most 16 points per lane, K up to 1024, stay below the 64 KB default)
+  const void* f[] = {(const void*)k_fft_c2r_rg<24>,           (const void*)k_fft_c2r_rg<32>,
+                     (const void*)k_fft_c2r_rg<48>,           (const void*)k_fft_c2r_rg_k1536,
+                     (const void*)k_fft_c2r_rg_k3008,         (const void*)k_fft_r2c_rg<24, 0, false>,
+                     (const void*)k_fft_r2c_rg<32, 0, false>, (const void*)k_fft_r2c_rg<48, 0, false>,
+                     (const void*)k_fft_r2c_rg<24, 1536, false>, (const void*)k_fft_r2c_rg<48, 3008, false>,
+                     (const void*)k_fft_r2c_rg<24, 0, true>,  (const void*)k_fft_r2c_rg<32, 0, true>,
+                     (const void*)k_fft_r2c_rg<48, 0, true>,  (const void*)k_fft_r2c_rg<24, 1536, true>,
+                     (const void*)k_fft_r2c_rg<48, 3008, true>};
+  for (const void* k : f) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 namespace {
@@ -947,11 +930,6 @@ bool plan_has_radix(const FftPlan& p, int r) {
 // the register plan compiled in (K = 1536: the rings of nphi 3072, the l_max 1000 grid)
 bool plan_is_k1536(const FftPlan& p) {
   return p.K == 1536 && p.nf == 3 && p.radix[0] == 24 && p.radix[1] == 8 && p.radix[2] == 8;
-}
-
-// K = 768 (the rings of nphi 1536, the l_max 500 grid)
-bool plan_is_k768(const FftPlan& p) {
-  return p.K == 768 && p.nf == 4 && p.radix[0] == 8 && p.radix[1] == 8 && p.radix[2] == 4 && p.radix[3] == 3;
 }
 
 // K = 3008 (nphi 6016, the l_max 2000 grid); the register kernels run it only compiled in
@@ -968,27 +946,21 @@ hipError_t launch_fft_c2r(const modal_ctx* c, const void* F, int S, void* maps, 
     int blocks = 16 * ((units + 7) / 8);
     blocks = std::min(blocks, 16 * 64);   // 1024 workgroups: 256 CUs x 4 rings x 2 x 2
     const int pts = fft_rg_points(c->fft_rg_plan);
-#define LAUNCH(PT)                                                                                                \
-  hipLaunchKernelGGL(k_fft_c2r_rg<PT>, dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st, c->fft_rg_plan,        \
-                     c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps, (const float2*)c->t.tw32,        \
-                     (const float2*)c->t.twp32)
-    if (plan_is_k1536(c->fft_rg_plan) && pts == 24)
-      hipLaunchKernelGGL(k_fft_c2r_rg_k1536, dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st,
-                         c->fft_rg_plan, c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps,
-                         (const float2*)c->t.tw32, (const float2*)c->t.twp32);
-    else if (plan_is_k768(c->fft_rg_plan))
-      hipLaunchKernelGGL(k_fft_c2r_rg_k768, dim3(blocks), dim3(64 * RG_RINGS), fft_rg_lds(c), st, c->fft_rg_plan,
-                         c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps, (const float2*)c->t.tw32,
-                         (const float2*)c->t.twp32);
-    else if (plan_is_k3008(c->fft_rg_plan))   // one workgroup per CU: 256 of them
-      hipLaunchKernelGGL(k_fft_c2r_rg_k3008, dim3(std::min(blocks, 256)), dim3(64 * RG_RINGS * kW3008), fft_rg_lds(c), st,
-                         c->fft_rg_plan, c->lmax, c->ntheta, nseq, (const float2*)F, (float*)maps,
-                         (const float2*)c->t.tw32, (const float2*)c->t.twp32);
-    else if (pts <= 16) LAUNCH(16);
-    else if (pts <= 24) LAUNCH(24);
-    else if (pts <= 32) LAUNCH(32);
-    else LAUNCH(48);
-#undef LAUNCH
+    auto launch = [&](auto kernel, int grid, int threads) {
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), fft_rg_lds(c), st, c->fft_rg_plan, c->lmax, c->ntheta, nseq,
+                         (const float2*)F, (float*)maps, (const float2*)c->t.tw32, (const float2*)c->t.twp32);
+    };
+    constexpr int NT = 64 * RG_RINGS;
+    const FftPlan& p = c->fft_rg_plan;
+    // rounds of 3 or 4 elements per thread over the 2 K of a unit, the fewest in all
+    const bool three = 3 * ((2 * p.K + 3 * NT - 1) / (3 * NT)) < 4 * ((2 * p.K + 4 * NT - 1) / (4 * NT));
+    if (plan_is_k1536(p) && pts == 24) launch(k_fft_c2r_rg_k1536, blocks, NT);
+    else if (plan_is_k3008(p)) launch(k_fft_c2r_rg_k3008, std::min(blocks, 256), NT * kW3008);   // one workgroup per CU
+    else if (pts <= 16 && three) launch(k_fft_c2r_rg<16, 3>, blocks, NT);
+    else if (pts <= 16) launch(k_fft_c2r_rg<16>, blocks, NT);
+    else if (pts <= 24) launch(k_fft_c2r_rg<24>, blocks, NT);
+    else if (pts <= 32) launch(k_fft_c2r_rg<32>, blocks, NT);
+    else launch(k_fft_c2r_rg<48>, blocks, NT);
     return hipGetLastError();
   }
   const int R = fft_rings_per_block(c);
@@ -1024,7 +996,6 @@ hipError_t fft_r2c_rg(const modal_ctx* c, std::conditional_t<STATE, float, const
                        (float2*)Gh, (const float2*)c->t.tw32, (const float2*)c->t.twp32, (const float*)c->t.w32, scale);
   };
   if (plan_is_k1536(p) && pts == 24) launch(k_fft_r2c_rg<24, 1536, STATE>, blocks);
-  else if (plan_is_k768(p)) launch(k_fft_r2c_rg<16, 768, STATE>, blocks);
   else if (plan_is_k3008(p)) launch(k_fft_r2c_rg<48, 3008, STATE>, std::min(blocks, 256));
   else if (pts <= 16) launch(k_fft_r2c_rg<16, 0, STATE>, blocks);
   else if (pts <= 24) launch(k_fft_r2c_rg<24, 0, STATE>, blocks);

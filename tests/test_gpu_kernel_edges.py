@@ -501,3 +501,26 @@ def test_workspaces_hold_what_is_used(prec, nphi):
         assert torch.equal(x, y)
     for t, need in bufs:
         assert bool((t[:guard] == 255).all()) and bool((t[guard + need:] == 255).all())
+
+
+# Ring transforms run from their plan's arguments, both directions: rings of two pixels (no pass), last
+# passes of every radix (8: nphi 16, 4: 8, 2: 20 x 2, 3: 6, 5: 30), strides that are and are not powers of
+# two, rounds of 3 and of 4 spectrum elements, and plans of up to 16, 24, 32 and 48 points per lane.
+@pytest.mark.parametrize("nphi", [2, 6, 8, 16, 20, 30, 54, 200, 720, 1536, 1600, 2048, 2400, 2700, 3000, 3600, 4050, 4096])
+def test_ring_transform_plans(nphi):
+    lmax, P = min(12, (nphi - 1) // 2), 2
+    ntheta = lmax + 2
+    case = Case("edge", lmax, ntheta, nphi, P, 1, "wmap", 84)
+    print(f"[case] ring plan {ntheta}x{nphi}", flush=True)
+    if lmax < 2:
+        case.__dict__.update(cl=np.ones(lmax + 1), q=np.linspace(0.5, 1.0, P * (lmax + 1)).reshape(P, lmax + 1))
+    a = case.alms(0, 1)
+    c = _ctx(case, "f32")
+    out = torch.full((1, P, ntheta, nphi), float("nan"), dtype=torch.float32, device="cuda")
+    got, ref = c.filter_maps(a, out=out).cpu().numpy()[0], case.maps(a)[0]
+    rms = np.sqrt(np.mean(ref * ref, axis=(1, 2)))
+    assert np.all(np.max(np.abs(got - ref), axis=(1, 2)) <= 1e-5 * rms)
+    cot = np.random.default_rng(5).standard_normal((1, 4))
+    g = c.beta_vjp(a, cot).cpu().numpy()[0]
+    gref = om.vjp(a[0], case.cl, case.q, case.grid, None, cot[0])[0]
+    assert np.linalg.norm(g - gref) <= 1e-5 * np.linalg.norm(gref)
