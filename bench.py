@@ -188,7 +188,7 @@ def kernel_rooflines(ctx, stages, prec, S, op="beta"):
     work = {
         # F[m][ring] = sum_l lambda_lm(ring) a_lm: one complex x real MAC per (l, m, ring, column)
         "legendre": (2.0 * ctx.nalm * nt * P * S, "flop", mfma_bound, mfma_peak,
-                     (4 if prec == "bf16x3" else 3) * 2.0 * ctx.nalm * nt * P * S if split else None),
+                     3 * 2.0 * ctx.nalm * nt * P * S if split else None),
         # read F (complex, m <= lmax per ring) and write the real rings
         "fft": ((lmax + 1) * nt * P * S * 2 * real + npix * P * S * real, "byte", "hbm", PEAK["hbm"], None),
         # beta_prs = sum_x (M_p M_r)(x) w(x) M_s(x): one MAC per (triple p <= r <= s, pixel)
