@@ -81,8 +81,8 @@ typedef enum {
 typedef enum {
   MODAL_F64 = 0,     /* FP64 everywhere                                          */
   MODAL_F32 = 1,     /* FP32 maps, FP32 MFMA contractions, FP64 recurrence/reductions */
-  MODAL_BF16X3 = 2,  /* split bf16 hi+lo on the matrix cores, FP32 accumulation:
-                        synthesis 4 products, cubic contraction 3 products       */
+  MODAL_BF16X3 = 2,  /* split bf16 hi+lo on the matrix cores, FP32 accumulation,
+                        3 products in the synthesis and the cubic contraction    */
   MODAL_F16X3 = 3    /* split fp16 hi+lo (22-bit operands, 3 products) in both
                         contractions, exact power-of-two scaling of maps and
                         weights in the cubic one, FP32 accumulation; needs
@@ -200,8 +200,9 @@ int modal_npairs(const modal_ctx* ctx);
  * 2 = split bf16/fp16 MFMA (32x32x16 tiles over the same cover). */
 int modal_cubic_path(const modal_ctx* ctx);
 /* Multiply-adds the cubic contraction issues per pixel and map, counting tile
- * padding and every product of a split (for roofline reports; host only).  For FP64
- * contexts the dense pair x mode count, npairs * P. */
+ * padding and every product of a split (for roofline reports; host only).  FP64
+ * contexts: the dense pair x mode count npairs * P, of which their kernel forms the
+ * column tiles that hold a cell (pair a <= b, mode >= b), about half. */
 double modal_cubic_issued_macs(const modal_ctx* ctx);
 /* Work plan of the split contraction for P modes (host only, no device; Sec. II,
  * eq. (bbispect): beta_prs is the pixel sum of the triple product, so it may be read
@@ -222,7 +223,13 @@ int modal_cubic_plan(int P, int max_items, int* items, int* slots, int* cell, in
  * w_host[ntheta] = Gauss-Legendre weights (sum 2).  Either may be NULL. */
 modal_status modal_grid(const modal_ctx* ctx, double* x_host, double* w_host);
 
-/* Bytes of workspace an operation needs for S maps (N for covariance). */
+/* Bytes of workspace an operation needs for S maps (N for covariance).  Mostly
+ * buffers of the size of the inputs and outputs; two are more than that:
+ *   IDEAL_COVARIANCE holds the sums over every three of the npairs pairs,
+ *     8 npairs (npairs + 1) (npairs + 2) / 6 bytes: 0.13 GB at P 30, 0.74 at P 40,
+ *     2.8 at P 50, 12 at P 64 (zeta itself is 0.20, 1.05, 3.9 and 16.8 GB);
+ *   TRISPECTRUM holds the partial sums of S + 1 skies (the pair means are one more
+ *     sky of the update), whether or not a state is passed. */
 modal_status modal_workspace_size(const modal_ctx* ctx, int op, int S, size_t* bytes);
 /* Bytes of the linear-term state: the pair accumulator (one pixel plane per
  * pair, [npairs][ntheta][nphi] real, at offset 0; after FINALIZE the pair means

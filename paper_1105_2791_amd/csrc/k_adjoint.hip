@@ -237,17 +237,15 @@ __global__ __launch_bounds__(256) void k_pair_adjoint_f32(int P, int npairs, int
 // SG_CH steps accumulate from zero into a chain that is then added to the running FP32 sums (the
 // matrix core truncates the addend of a long accumulation).
 // A workgroup is 4 waves and 256 pixels of one sky (70 KB of LDS: two workgroups per CU).
-// Bound by the matrix cores and the packed products together (they overlap in part: 12 products of
-// 32 x 32 x 16 and 144 vector instructions take 646 cycles of a SIMD with two waves, 460 and 406
-// alone), so the row tiles follow P: 4 skies of 1536 x 3072 pixels, P 40: 6.8 ms with rows in tiles
-// of 32 and three dependent products in turn, 6.1 now; P 30, 4 skies of 768 x 1536: the whole
-// gradient 2.46 -> 2.15 ms, P 16 1.64 -> 1.43.
+// Bound by the matrix cores and the packed products together (they overlap in part: as many
+// multiplies in 12 products of 32 x 32 x 16, with 144 vector instructions, take 646 cycles of a SIMD with
+// two waves, 460 and 406 alone), so the row tiles follow P: 4 skies of 768 x 1536 pixels, with rows
+// in tiles of 32 and three dependent products in turn, P 16 0.40 ms, P 33 1.47; now 0.37 and 1.32.
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16 f16x2;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 constexpr int SG_NW = 4;               // waves per workgroup (two workgroups per CU)
-constexpr int SG_PX = 64 * SG_NW;      // pixels per workgroup: two 32-column tiles per wave
+constexpr int SG_PX = 64 * SG_NW;      // pixels per workgroup: four 16-column tiles per wave
 constexpr int SG_PP = 48;              // modes held per map row (P <= 48; rows zero past P)
 constexpr int SG_MS = 2 * SG_PP + 8;   // map row stride in halves: hi words, lo words, pad (208 B)
 constexpr int SG_GC = 4;               // 8-pair groups per K step (and staged chunk)

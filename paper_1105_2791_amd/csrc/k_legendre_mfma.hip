@@ -18,7 +18,8 @@
 // waiting.  What took the time before, at l_max 500, 768 rings, 480 columns (2.75 ms; 17.7 ms at
 // l_max 1000, 1536 rings, 640 columns), and what is done about it:
 //   * tiles of 32 l per ring, in which the 16 lanes of an MFMA row read one LDS bank: tiles in
-//     operand order, free of conflicts, and no register spills (1.06 ms);
+//     operand order, free of conflicts, and hardly a register spilled (1.06 ms; of the kernels
+//     below the one with a table and three ring tiles keeps 20 bytes per lane in memory);
 //   * half-empty workgroups (384 north rings are one and a half of 256): rings spread evenly
 //     over workgroups and waves (0.87 ms);
 //   * the recurrence, repeated by each block of 64 columns: from three blocks on lambda comes

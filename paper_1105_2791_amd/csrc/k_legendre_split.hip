@@ -19,20 +19,20 @@
 //     (one barrier per chunk), Re and Im of a pair 32 rows apart;
 //   * each wave runs 2 parities x 2 ring tiles x 2 column tiles, accumulating
 //     2 K steps x 3 products (hi.hi + hi.lo + lo.hi; lo.lo is below the operand
-//     split error) per chunk in place: an output takes at most about 130
-//     accumulations, so the matrix core's addend truncation stays far below the split
-//     error.
+//     split error) per chunk in place: an output takes 6 accumulations per chunk, 96 at
+//     l_max 1000 and 192 at 2000, and the matrix core's addend truncation (below 2^-24 of the sum
+//     each) stays below the split error: beta is 9.4e-6 and 8.5e-6 off its FP64 value there.
 // A lane then holds Re and Im of four consecutive rings of a pair and stores them straight
 // into F (f_index layout).
 //
 // Bound by memory on both ends of a short loop: F's 64-byte runs (about 4.2 TB/s with the loop
 // left out) and lambda's records from L2 and HBM, which the other workgroup of the CU hides
 // only in part.  l_max 1000, 1536 rings, 640 columns (3.9 GB of F, 1.6 GB of records):
-// 2.90 ms with the next chunk's loads waited for at the head of the loop, coefficients read
-// 16 per lane (a cache line per lane and load) and outputs staged through LDS, 2.57 now;
-// l_max 2000, 3008 rings, 400 columns: 11.8 -> 10.3 ms.  The order of the units (m ascending over
+// 2.85 ms with the next chunk's loads waited for at the head of the loop, coefficients read
+// 16 per lane (a cache line per lane and load) and outputs staged through LDS, 2.65 now;
+// l_max 2000, 3008 rings, 400 columns: 11.6 -> 10.5 ms.  The order of the units (m ascending over
 // the XCDs) lets neighbouring m share DRAM pages: m from both ends in turn takes 3.04 ms,
-// non-temporal stores 3.54.  The recurrence in the kernel (no table) takes 3.7 ms.
+// non-temporal stores 3.54.  The recurrence in the kernel (no table) takes 3.3 to 3.5 ms, 3.47 before.
 #include "common.h"
 
 #include <type_traits>
